@@ -184,11 +184,9 @@ int dwf_apply(const dwf_op* op, int space, int dagger, int prec, void* out, cons
         const int* lex = L->lex_of_site_dev.as<int>();
         if (space == DWF_FULL5D) {
             DevBuf ie(bytes), io(bytes), oe(bytes), oo(bytes);
-            pack_full(k, ie.p, in, lex, Vh, Vhp, V, op->Ls, st);
-            pack_full(k, io.p, in, lex + Vh, Vh, Vhp, V, op->Ls, st);
+            pack_full(k, ie.p, io.p, in, lex, Vh, Vhp, V, op->Ls, st);
             apply_full(op, k, dagger, oe.p, oo.p, ie.p, io.p, 1, st);
-            unpack_full(k, out, oe.p, lex, Vh, Vhp, V, op->Ls, st);
-            unpack_full(k, out, oo.p, lex + Vh, Vh, Vhp, V, op->Ls, st);
+            unpack_full(k, out, oe.p, oo.p, lex, Vh, Vhp, V, op->Ls, st);
             DWF_HIP(hipStreamSynchronize(st));
         } else if (space == DWF_EVEN5D) {
             DevBuf ie(bytes), oe(bytes), to(bytes), te(bytes);
@@ -340,8 +338,7 @@ int dwf_source_4d(const dwf_op* op, void* b5, const void* b4, void* stream) {
                                hipMemcpyDeviceToDevice, st));
         DWF_HIP(hipMemcpyAsync(fo.as<char>() + slice * (Ls - 1), oo.as<char>() + slice, slice,
                                hipMemcpyDeviceToDevice, st));
-        unpack_full(ST_F64, b5, fe.p, lex, Vh, Vhp, V, Ls, st);
-        unpack_full(ST_F64, b5, fo.p, lex + Vh, Vh, Vhp, V, Ls, st);
+        unpack_full(ST_F64, b5, fe.p, fo.p, lex, Vh, Vhp, V, Ls, st);
         DWF_HIP(hipStreamSynchronize(st));
         return DWF_OK;
     });

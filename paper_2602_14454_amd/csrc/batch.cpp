@@ -545,8 +545,7 @@ int solve_batch(int n, const dwf_op* const* ops, void* const* x5, const void* co
         const int* lex = L->lex_of_site_dev.as<int>();
         const long sl = (long)it.op->Ls * it.nrhs;
         const void* src = b5[&it - B.items.data()];
-        pack_full(ST_F64, at(be.p, it.off), src, lex, L->Vh, L->Vhp, L->V, sl, cs.s);
-        pack_full(ST_F64, at(bo.p, it.off), src, lex + L->Vh, L->Vh, L->Vhp, L->V, sl, cs.s);
+        pack_full(ST_F64, at(be.p, it.off), at(bo.p, it.off), src, lex, L->Vh, L->Vhp, L->V, sl, cs.s);
         schur_rhs(it.op, ST_F64, at(bt.p, it.off), at(be.p, it.off), at(bo.p, it.off), at(to.p, it.off), it.nrhs,
                   cs.s);
     }
@@ -703,8 +702,7 @@ int solve_batch(int n, const dwf_op* const* ops, void* const* x5, const void* co
         const long sl = (long)it.op->Ls * it.nrhs;
         void* dst = x5[&it - B.items.data()];
         reconstruct_odd(it.op, ST_F64, at(xo.p, it.off), at(xe.p, it.off), at(bo.p, it.off), it.nrhs, cs.s);
-        unpack_full(ST_F64, dst, at(xe.p, it.off), lex, L->Vh, L->Vhp, L->V, sl, cs.s);
-        unpack_full(ST_F64, dst, at(xo.p, it.off), lex + L->Vh, L->Vh, L->Vhp, L->V, sl, cs.s);
+        unpack_full(ST_F64, dst, at(xe.p, it.off), at(xo.p, it.off), lex, L->Vh, L->Vhp, L->V, sl, cs.s);
     }
     DWF_HIP(hipEventRecord(e1.e, cs.s));
     // FP64 true 5D residual per slot (outside the timed region)

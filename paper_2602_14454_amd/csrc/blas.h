@@ -12,10 +12,10 @@ enum { CG_RR = 0, CG_QQ = 1, CG_ALPHA = 2, CG_BETA = 3, CG_RRNEW = 4, CG_NANFLAG
        CG_TMP = 7, CG_RROLD = 8, CG_NSLOTS = 16 };
 
 int blas_grid(long n);
-void pack_full(int kind, void* dst, const void* src, const int* lex, long Vh, long Vhp, long V, long nslices,
-               hipStream_t st);
-void unpack_full(int kind, void* dst, const void* src, const int* lex, long Vh, long Vhp, long V, long nslices,
-                 hipStream_t st);
+void pack_full(int kind, void* dst_e, void* dst_o, const void* src, const int* lex, long Vh, long Vhp, long V,
+               long nslices, hipStream_t st);
+void unpack_full(int kind, void* dst, const void* src_e, const void* src_o, const int* lex, long Vh, long Vhp,
+                 long V, long nslices, hipStream_t st);
 void pack_half(int kind, void* dst, const void* src, const int* lex, long Vh, long Vhp, long nslices,
                hipStream_t st);
 void unpack_half(int kind, void* dst, const void* src, const int* lex, long Vh, long Vhp, long nslices,

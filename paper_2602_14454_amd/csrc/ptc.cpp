@@ -210,8 +210,7 @@ dwf_ptc_pairs* ptc_pairs_create(const dwf_op* op, const void* b5, unsigned long 
     double fr = 0;
     if (b5) {
         // the Schur system of the 5D source; x* to 1e-10 (FP64 CGNR)
-        pack_full(ST_F64, be.p, b5, lex, L->Vh, L->Vhp, L->V, op->Ls, st);
-        pack_full(ST_F64, bo.p, b5, lex + L->Vh, L->Vh, L->Vhp, L->V, op->Ls, st);
+        pack_full(ST_F64, be.p, bo.p, b5, lex, L->Vh, L->Vhp, L->V, op->Ls, st);
         schur_rhs(op, ST_F64, bt.p, be.p, bo.p, to.p, 1, st);
         CgWork W(op, ST_F64, ST_F64, 1);
         cgnr(op, W, bt.p, 1e-10, 100000, 8, st, &fr, &nan_seen, nullptr);

@@ -420,8 +420,7 @@ int solve(const dwf_op* op, void* x5, const void* b5, const dwf_solve_params* pr
     DWF_HIP(hipMemsetAsync(scal.p, 0, CG_NSLOTS * sizeof(double), st));
 
     const int* lex = L->lex_of_site_dev.as<int>();
-    pack_full(ST_F64, be.p, b5, lex, Vh, Vhp, V, Ls, st);
-    pack_full(ST_F64, bo.p, b5, lex + Vh, Vh, Vhp, V, Ls, st);
+    pack_full(ST_F64, be.p, bo.p, b5, lex, Vh, Vhp, V, Ls, st);
     const double b2 = norm2_host(ST_F64, be.p, n, pp, sc, hs, st) + norm2_host(ST_F64, bo.p, n, pp, sc, hs, st);
     schur_rhs(op, ST_F64, bt.p, be.p, bo.p, to.p, 1, st);
 
@@ -536,8 +535,7 @@ int solve(const dwf_op* op, void* x5, const void* b5, const dwf_solve_params* pr
         prev_rel = rel5;
     }
     reconstruct_odd(op, ST_F64, xo.p, xe.p, bo.p, 1, st);
-    unpack_full(ST_F64, x5, xe.p, lex, Vh, Vhp, V, Ls, st);
-    unpack_full(ST_F64, x5, xo.p, lex + Vh, Vh, Vhp, V, Ls, st);
+    unpack_full(ST_F64, x5, xe.p, xo.p, lex, Vh, Vhp, V, Ls, st);
     DWF_HIP(hipEventRecord(e1, st));
     // final FP64 true residual of the 5D system (outside the timed region)
     apply_full(op, ST_F64, 0, te.p, to.p, xe.p, xo.p, 1, st);
@@ -577,10 +575,8 @@ double true_residual(const dwf_op* op, const void* x5, const void* b5, hipStream
     DevBuf partial((blas_grid(n) + 16) * sizeof(double)), scal(CG_NSLOTS * sizeof(double));
     Pinned hs(CG_NSLOTS);
     const int* lex = L->lex_of_site_dev.as<int>();
-    pack_full(ST_F64, xe.p, x5, lex, Vh, Vhp, V, Ls, st);
-    pack_full(ST_F64, xo.p, x5, lex + Vh, Vh, Vhp, V, Ls, st);
-    pack_full(ST_F64, be.p, b5, lex, Vh, Vhp, V, Ls, st);
-    pack_full(ST_F64, bo.p, b5, lex + Vh, Vh, Vhp, V, Ls, st);
+    pack_full(ST_F64, xe.p, xo.p, x5, lex, Vh, Vhp, V, Ls, st);
+    pack_full(ST_F64, be.p, bo.p, b5, lex, Vh, Vhp, V, Ls, st);
     apply_full(op, ST_F64, 0, te.p, to.p, xe.p, xo.p, 1, st);
     double* pp = partial.as<double>();
     double* sc = scal.as<double>();
@@ -622,11 +618,9 @@ double residual_4d(const dwf_op* op, const void* x4, const void* b4, double tol_
     convert(ST_F64, ST_F64, y.p, b4, n4, st);
     axpby(ST_F64, ST_F64, y.p, x4, n4, nullptr, 1.0 - op->m, nullptr, 1.0, nullptr, st);
     embed_4d(e5.p, y.p, V, Ls, st);
-    pack_full(ST_F64, ie.p, e5.p, lex, Vh, Vhp, V, Ls, st);
-    pack_full(ST_F64, io.p, e5.p, lex + Vh, Vh, Vhp, V, Ls, st);
+    pack_full(ST_F64, ie.p, io.p, e5.p, lex, Vh, Vhp, V, Ls, st);
     apply_full(&om, ST_F64, 0, oe.p, oo.p, ie.p, io.p, 1, st);
-    unpack_full(ST_F64, z5.p, oe.p, lex, Vh, Vhp, V, Ls, st);
-    unpack_full(ST_F64, z5.p, oo.p, lex + Vh, Vh, Vhp, V, Ls, st);
+    unpack_full(ST_F64, z5.p, oe.p, oo.p, lex, Vh, Vhp, V, Ls, st);
     dwf_solve_params prm;
     std::memset(&prm, 0, sizeof prm);
     prm.tol = tol_inner;

@@ -1,0 +1,52 @@
+"""Kernels at the edges of their tiles, against the FP64 CPU oracle.
+
+Tolerances as in test_gpu_operator.py: relative max-norm error FP64 1e-13,
+FP32 1e-5, BF16 3e-2.
+"""
+import numpy as np
+import pytest
+
+import dwfgen
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+TOL = {0: 1e-13, 1: 1e-5, 2: 3e-2}
+
+
+def _rel(a, b):
+    return float(np.abs(a - b).max() / max(np.abs(b).max(), 1e-300))
+
+
+def _dev(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
+
+
+def _make(dims, Ls, seed=5, b=1.0, c=0.0, alpha=0.6):
+    import paper_2602_14454_amd as dwf
+    U = dwfgen.random_su3_links(dims, 0.5, seed)
+    lat = dwf.Lattice(dims)
+    lat.set_gauge(U)
+    return lat, dwf.Op(lat, Ls, 1.6, 0.05, b, c, alpha), oracle.Params(dims=dims, Ls=Ls, M0=1.6, m=0.05, b=b, c=c, alpha=alpha), U
+
+
+# sites per parity: 8 (part of a tile), 32 and 64 (one tile of the full and of
+# the half conversion), 72 (remainder 8), 96, 120, 1008 (several bricks' rows)
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (4, 2, 2, 4), (4, 4, 2, 4), (6, 6, 2, 2), (4, 6, 4, 2), (6, 10, 2, 2),
+                                  (6, 6, 4, 14)])
+@pytest.mark.parametrize("prec", [0, 1, 2])
+def test_layout_conversion_tiles(dims, prec):
+    """Canonical <-> internal conversion of full and even vectors around the 64-site tiles."""
+    import torch
+
+    import paper_2602_14454_amd as dwf
+    lat, op, p, U = _make(dims, 3)
+    x = dwfgen.gaussian_source_5d(dims, 3, 9)
+    out = torch.full(x.shape, float("nan"), dtype=torch.complex128, device="cuda")
+    op.apply(out, _dev(x), dwf.FULL5D, False, prec)
+    assert _rel(out.cpu().numpy(), oracle.dwf_apply(p, U, x)) < TOL[prec]
+    xe = np.ascontiguousarray(x[:, : p.Vh])
+    oe = torch.full(xe.shape, float("nan"), dtype=torch.complex128, device="cuda")
+    op.apply(oe, _dev(xe), dwf.EVEN5D, True, prec)
+    assert _rel(oe.cpu().numpy(), oracle.dhat(p, U, xe, dagger=True)) < TOL[prec]

@@ -2,7 +2,6 @@
 // catches internal errors and turns them into status codes; the message is
 // kept per thread for dwf_last_error().
 #include <cmath>
-#include <complex>
 #include <cstring>
 #include <exception>
 #include <memory>
@@ -103,15 +102,7 @@ void dwf_lattice_destroy(dwf_lattice* lat) { delete lat; }
 int dwf_lattice_set_gauge(dwf_lattice* lat, const void* U, int on_device, void* stream) {
     return guarded([&] {
         DWF_REQUIRE(lat && U, DWF_EINVAL, "null argument");
-        const size_t n = (size_t)lat->V * 4 * 9;
-        std::vector<std::complex<double>> h(n);
-        if (on_device) {
-            DWF_HIP(hipMemcpyAsync(h.data(), U, n * 16, hipMemcpyDeviceToHost, S(stream)));
-            DWF_HIP(hipStreamSynchronize(S(stream)));
-        } else {
-            std::memcpy(h.data(), U, n * 16);
-        }
-        upload_gauge(lat, h.data());
+        upload_gauge(lat, U, on_device != 0, S(stream));
         return DWF_OK;
     });
 }

@@ -20,6 +20,9 @@ void pack_half(int kind, void* dst, const void* src, const int* lex, long Vh, lo
                hipStream_t st);
 void unpack_half(int kind, void* dst, const void* src, const int* lex, long Vh, long Vhp, long nslices,
                  hipStream_t st);
+// canonical complex128 links (device) to the FP64, FP32 and BF16 link tables of both parities
+void pack_links(void* l64, void* l32, void* l16, const void* U, const int* lex, const int dims[4], int antiperiodic,
+                long Vh, long Vhp, hipStream_t st);
 void pack_chiral_pair_f64(void* dst, const void* b4, const int* lex, long Vh, long Vhp, hipStream_t st);
 void project_4d(void* x4, const void* x5, long V, int Ls, hipStream_t st);
 void embed_4d(void* e5, const void* y, long V, int Ls, hipStream_t st);

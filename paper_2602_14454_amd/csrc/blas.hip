@@ -138,6 +138,51 @@ __global__ __launch_bounds__(256) void unpack_kernel(double2* __restrict__ dst, 
         }
 }
 
+// Canonical links U[lex][mu][3][3] to the three copies of the hop's tables
+// (precision.h): per output parity and direction the forward link U_mu(x) or
+// the backward one U_mu(x-mu)^dag, antiperiodic phase folded in.  A wave takes
+// 64 sites and one mu (both directions), so that a table row is written in
+// 1 KB runs; the reads (144 bytes a lane) meet in L2, where the four waves of
+// a block share the 576 bytes of a site.  Bound by the 272 bytes written per
+// link and direction.  Packing the tables on the host and copying them over
+// took 133 ms on 16^4 (this kernel: 44 us).
+__global__ __launch_bounds__(256) void links_kernel(double2* __restrict__ l64, float2* __restrict__ l32,
+                                                    uint32_t* __restrict__ l16, const double2* __restrict__ U,
+                                                    const int* __restrict__ lex, int Lx, int Ly, int Lz, int Lt,
+                                                    int antiperiodic, long Vh, long Vhp) {
+    const long i = (long)blockIdx.x * 64 + (threadIdx.x & 63);
+    const int mu = threadIdx.x >> 6, p = blockIdx.y;
+    if (i >= Vh) return;
+    const unsigned x = (unsigned)lex[p * Vh + i];
+    const unsigned ext = mu == 0 ? Lx : (mu == 1 ? Ly : (mu == 2 ? Lz : Lt));
+    const unsigned stride = mu == 0 ? 1u : (mu == 1 ? (unsigned)Lx : (mu == 2 ? (unsigned)Lx * Ly : (unsigned)Lx * Ly * Lz));
+    const unsigned c = x / stride % ext;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int d = mu + 4 * h;
+        const unsigned y = h == 0 ? x : (c == 0 ? x + stride * (ext - 1) : x - stride);
+        const double ph = (antiperiodic && mu == 3 && c == (h == 0 ? ext - 1 : 0u)) ? -1.0 : 1.0;
+        const double2* src = U + ((long)y * 4 + mu) * 9;
+        double2 u[12];
+#pragma unroll
+        for (int e = 0; e < 9; ++e) {
+            const double2 v = src[h == 0 ? e : (e % 3) * 3 + e / 3];
+            u[e] = make_double2(ph * v.x, h == 0 ? ph * v.y : ph * -v.y);
+        }
+#pragma unroll
+        for (int e = 9; e < 12; ++e) u[e] = make_double2(0.0, 0.0);   // unused elements of the last group
+        const long r64 = link_elems_parity(Vhp, 16), r32 = link_elems_parity(Vhp, 8), r16 = link_elems_parity(Vhp, 4);
+#pragma unroll
+        for (int e = 0; e < link_ng(16) * link_lp(16); ++e) l64[p * r64 + lidx(d, e, i, Vhp, 16)] = u[e];
+#pragma unroll
+        for (int e = 0; e < link_ng(8) * link_lp(8); ++e)
+            l32[p * r32 + lidx(d, e, i, Vhp, 8)] = make_float2((float)u[e].x, (float)u[e].y);
+#pragma unroll
+        for (int e = 0; e < link_ng(4) * link_lp(4); ++e)
+            l16[p * r16 + lidx(d, e, i, Vhp, 4)] = pack_bf16((float)u[e].x, (float)u[e].y);
+    }
+}
+
 // 4D canonical -> two-slice half field of one parity: slice 0 = P+ b4, slice 1 = P- b4
 template <class S>
 __global__ void pack_chiral_pair_kernel(void* dst, const double2* b4, const int* lex_of_site, long Vh, long Vhp) {
@@ -692,6 +737,13 @@ void pack_half(int kind, void* dst, const void* src, const int* lex, long Vh, lo
 void unpack_half(int kind, void* dst, const void* src, const int* lex, long Vh, long Vhp, long ns, hipStream_t st) {
     if (ns <= 0) return;
     DISPATCH1(kind, unpack_t, 1, dst, src, nullptr, lex, Vh, Vhp, Vh, ns, st);
+    DWF_HIP(hipGetLastError());
+}
+
+void pack_links(void* l64, void* l32, void* l16, const void* U, const int* lex, const int dims[4], int antiperiodic,
+                long Vh, long Vhp, hipStream_t st) {
+    hipLaunchKernelGGL(links_kernel, dim3((unsigned)((Vh + 63) / 64), 2), dim3(256), 0, st, (double2*)l64, (float2*)l32,
+                       (uint32_t*)l16, (const double2*)U, lex, dims[0], dims[1], dims[2], dims[3], antiperiodic, Vh, Vhp);
     DWF_HIP(hipGetLastError());
 }
 

@@ -1,27 +1,16 @@
 // Lattice geometry, gauge-link packing and operator coefficient setup.
 #include <algorithm>
 #include <cmath>
-#include <complex>
 #include <utility>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 
+#include "blas.h"
 #include "dwf_internal.h"
 #include "precision.h"
 
 namespace dwf {
-
-using cd = std::complex<double>;
-
-static uint16_t host_f32_to_bf16(float f) {
-    uint32_t u;
-    std::memcpy(&u, &f, 4);
-    if ((u & 0x7f800000u) == 0x7f800000u && (u & 0x007fffffu)) return (uint16_t)((u >> 16) | 0x40u);
-    const uint32_t lsb = (u >> 16) & 1u;
-    u += 0x7fffu + lsb;
-    return (uint16_t)(u >> 16);
-}
 
 // Internal site order.  Two orders exist; both are bijections onto the
 // sites of each parity, and every kernel goes through the site and
@@ -191,72 +180,26 @@ void build_geometry(dwf_lattice* L) {
 }
 
 // Hop links per output parity: forward U_mu(x), backward U_mu(x-mu)^dag,
-// antiperiodic t phase folded into the links that cross the boundary.
-void upload_gauge(dwf_lattice* L, const cd* U) {
-    const int ext[4] = {L->dims[0], L->dims[1], L->dims[2], L->dims[3]};
-    const long Vh = L->Vh, Vhp = L->Vhp;
-    const size_t nl = (size_t)2 * 8 * 9 * Vhp;
-    std::vector<cd> hl(nl, cd(0.0, 0.0));
-    for (int p = 0; p < 2; ++p)
-        for (long i = 0; i < Vh; ++i) {
-            const long x = L->lex_of_site[p * Vh + i];
-            int c[4];
-            long r = x;
-            for (int mu = 0; mu < 4; ++mu) { c[mu] = r % ext[mu]; r /= ext[mu]; }
-            for (int d = 0; d < 8; ++d) {
-                const int mu = d & 3;
-                double phase = 1.0;
-                const cd* src;
-                if (d < 4) {
-                    src = U + (x * 4 + mu) * 9;
-                    if (mu == 3 && L->antiperiodic_t && c[3] == ext[3] - 1) phase = -1.0;
-                } else {
-                    int cc[4] = {c[0], c[1], c[2], c[3]};
-                    cc[mu] = (cc[mu] - 1 + ext[mu]) % ext[mu];
-                    const long y = cc[0] + (long)ext[0] * (cc[1] + (long)ext[1] * (cc[2] + (long)ext[2] * cc[3]));
-                    src = U + (y * 4 + mu) * 9;
-                    if (mu == 3 && L->antiperiodic_t && c[3] == 0) phase = -1.0;
-                }
-                for (int a = 0; a < 3; ++a)
-                    for (int b = 0; b < 3; ++b) {
-                        cd u = d < 4 ? src[a * 3 + b] : std::conj(src[b * 3 + a]);
-                        hl[((size_t)(p * 8 + d) * 9 + a * 3 + b) * Vhp + i] = phase * u;
-                    }
-            }
-        }
-    // per storage kind: 16-byte groups of link elements (see precision.h)
+// antiperiodic t phase folded into the links that cross the boundary
+// (pack_links).  Work in flight on any stream may still read the old tables:
+// the call waits for it before it overwrites them, and for the new tables
+// before it returns.
+void upload_gauge(dwf_lattice* L, const void* U, bool on_device, hipStream_t st) {
+    const size_t bytes = (size_t)L->V * 4 * 9 * 16;
     for (int kind : {ST_F64, ST_F32, ST_BF16}) {
         const int cb = (int)complex_bytes(kind);
-        const long per = link_elems_parity(Vhp, cb);
-        std::vector<double> re(2 * (size_t)per, 0.0), im(2 * (size_t)per, 0.0);
-        for (int p = 0; p < 2; ++p)
-            for (int d = 0; d < 8; ++d)
-                for (int e = 0; e < 9; ++e)
-                    for (long i = 0; i < Vh; ++i) {
-                        const cd u = hl[((size_t)(p * 8 + d) * 9 + e) * Vhp + i];
-                        const size_t k = (size_t)p * per + lidx(d, e, i, Vhp, cb);
-                        re[k] = u.real();
-                        im[k] = u.imag();
-                    }
-        const size_t n = 2 * (size_t)per;
-        L->links[kind].alloc(n * cb);
-        if (kind == ST_F64) {
-            std::vector<double> h(2 * n);
-            for (size_t k = 0; k < n; ++k) { h[2 * k] = re[k]; h[2 * k + 1] = im[k]; }
-            DWF_HIP(hipMemcpy(L->links[kind].p, h.data(), n * cb, hipMemcpyHostToDevice));
-        } else if (kind == ST_F32) {
-            std::vector<float> h(2 * n);
-            for (size_t k = 0; k < n; ++k) { h[2 * k] = (float)re[k]; h[2 * k + 1] = (float)im[k]; }
-            DWF_HIP(hipMemcpy(L->links[kind].p, h.data(), n * cb, hipMemcpyHostToDevice));
-        } else {
-            std::vector<uint16_t> h(2 * n);
-            for (size_t k = 0; k < n; ++k) {
-                h[2 * k] = host_f32_to_bf16((float)re[k]);
-                h[2 * k + 1] = host_f32_to_bf16((float)im[k]);
-            }
-            DWF_HIP(hipMemcpy(L->links[kind].p, h.data(), n * cb, hipMemcpyHostToDevice));
-        }
+        const size_t need = 2 * (size_t)link_elems_parity(L->Vhp, cb) * cb;
+        if (L->links[kind].bytes != need) L->links[kind].alloc(need);
     }
+    DevBuf staged;
+    if (!on_device) {
+        staged.alloc(bytes);
+        DWF_HIP(hipMemcpy(staged.p, U, bytes, hipMemcpyHostToDevice));
+    }
+    DWF_HIP(hipDeviceSynchronize());
+    pack_links(L->links[ST_F64].p, L->links[ST_F32].p, L->links[ST_BF16].p, on_device ? U : staged.p,
+               L->lex_of_site_dev.as<int>(), L->dims, L->antiperiodic_t, L->Vh, L->Vhp, st);
+    DWF_HIP(hipStreamSynchronize(st));
     L->has_gauge = true;
 }
 

@@ -3,8 +3,6 @@
 // nrhs fields are stored back to back.
 #pragma once
 
-#include <complex>
-
 #include "dwf_internal.h"
 #include "hop.h"
 
@@ -49,7 +47,7 @@ void source_pair(const dwf_op* op, void* out_pair_p, const void* pair_other, con
 
 // objects.cpp
 void build_geometry(dwf_lattice* L);
-void upload_gauge(dwf_lattice* L, const std::complex<double>* U);
+void upload_gauge(dwf_lattice* L, const void* U, bool on_device, hipStream_t st);
 void setup_op(dwf_op* op);
 
 }  // namespace dwf

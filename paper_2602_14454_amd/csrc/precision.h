@@ -221,7 +221,7 @@ __host__ __device__ __forceinline__ long lidx(int d, int e, long site, long Vhp,
     return (((long)d * link_ng(cb) + e / link_lp(cb)) * Vhp + site) * link_lp(cb) + e % link_lp(cb);
 }
 // complex elements of the link table of one parity
-inline long link_elems_parity(long Vhp, int cb) { return 8L * link_ng(cb) * link_lp(cb) * Vhp; }
+__host__ __device__ inline long link_elems_parity(long Vhp, int cb) { return 8L * link_ng(cb) * link_lp(cb) * Vhp; }
 
 // Components 4g .. 4g+3 of one site with whole-group accesses (16 bytes per
 // access when the layout packs 16 bytes per group): v = re0, im0, ..., re3, im3.

@@ -50,3 +50,25 @@ def test_layout_conversion_tiles(dims, prec):
     oe = torch.full(xe.shape, float("nan"), dtype=torch.complex128, device="cuda")
     op.apply(oe, _dev(xe), dwf.EVEN5D, True, prec)
     assert _rel(oe.cpu().numpy(), oracle.dhat(p, U, xe, dagger=True)) < TOL[prec]
+
+
+# 8 and 24 sites per parity (part of a wave), 64, 72 and 1008; extents of 2 (both neighbours the same site)
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (2, 2, 6, 2), (4, 4, 2, 4), (2, 6, 6, 2), (6, 6, 4, 14)])
+@pytest.mark.parametrize("antiperiodic", [True, False])
+def test_link_tables(dims, antiperiodic):
+    """Links of host and device arrays, of a second configuration on the same lattice, in every precision."""
+    import torch
+
+    import paper_2602_14454_amd as dwf
+    p = oracle.Params(dims=dims, Ls=2, M0=1.6, m=0.05, alpha=0.6, antiperiodic_t=int(antiperiodic))
+    lat = dwf.Lattice(dims, antiperiodic)
+    op = dwf.Op(lat, 2, 1.6, 0.05, 1.0, 0.0, 0.6)
+    x = dwfgen.gaussian_source_5d(dims, 2, 4)
+    out = torch.empty(x.shape, dtype=torch.complex128, device="cuda")
+    for seed, host in ((1, True), (2, False), (3, True)):
+        U = dwfgen.random_su3_links(dims, 0.7, seed)
+        lat.set_gauge(U if host else _dev(U))
+        want = oracle.dwf_apply(p, U, x)
+        for prec in (0, 1, 2):
+            op.apply(out, _dev(x), dwf.FULL5D, False, prec)
+            assert _rel(out.cpu().numpy(), want) < TOL[prec]

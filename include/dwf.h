@@ -145,7 +145,10 @@ int dwf_lattice_maps(const dwf_lattice* lat, int* lex_of_site, int* nbr);
 /* ---- operator ------------------------------------------------------- */
 
 /* D^(alpha) with s-independent (b, c) (Sec. 2.2; Sec. 2.3 eq. domainwall_neff).
- * 2 <= Ls <= 16.  The op references lat (lat must outlive it). */
+ * 2 <= Ls <= 16.  The op references lat (lat must outlive it).  Calls that
+ * apply the operator keep their temporaries (up to six half fields per
+ * precision) with it from one call to the next, until dwf_op_destroy; the
+ * library frees idle ones by itself when it runs out of device memory. */
 int dwf_op_create(dwf_lattice* lat, int Ls, double M0, double m, double b, double c,
                   double alpha, dwf_op** out);
 /* The same with s-dependent coefficients: D_+^(s) = b[s] D_W + 1 and

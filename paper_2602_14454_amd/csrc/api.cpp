@@ -169,18 +169,17 @@ int dwf_apply(const dwf_op* op, int space, int dagger, int prec, void* out, cons
         const int k = kind_of(prec);
         const dwf_lattice* L = op->lat;
         DWF_REQUIRE(L->has_gauge, DWF_ESTATE, "gauge field not set");
-        const long Vh = L->Vh, Vhp = L->Vhp, V = L->V, n = (long)op->Ls * 12 * Vhp;
-        const size_t bytes = complex_bytes_of(k) * n;
+        const long Vh = L->Vh, Vhp = L->Vhp, V = L->V;
         hipStream_t st = S(stream);
         const int* lex = L->lex_of_site_dev.as<int>();
         if (space == DWF_FULL5D) {
-            DevBuf ie(bytes), io(bytes), oe(bytes), oo(bytes);
+            FieldScratch ie(op, k), io(op, k), oe(op, k), oo(op, k);
             pack_full(k, ie.p, io.p, in, lex, Vh, Vhp, V, op->Ls, st);
             apply_full(op, k, dagger, oe.p, oo.p, ie.p, io.p, 1, st);
             unpack_full(k, out, oe.p, oo.p, lex, Vh, Vhp, V, op->Ls, st);
             DWF_HIP(hipStreamSynchronize(st));
         } else if (space == DWF_EVEN5D) {
-            DevBuf ie(bytes), oe(bytes), to(bytes), te(bytes);
+            FieldScratch ie(op, k), oe(op, k), to(op, k), te(op, k);
             pack_half(k, ie.p, in, lex, Vh, Vhp, op->Ls, st);
             apply_dhat(op, k, dagger, oe.p, ie.p, to.p, te.p, 1, st);
             unpack_half(k, out, oe.p, lex, Vh, Vhp, op->Ls, st);
@@ -198,10 +197,9 @@ int dwf_apply_normal(const dwf_op* op, int prec, void* out, const void* in, void
         DWF_REQUIRE(out != in, DWF_EINVAL, "in and out must not alias");
         const int k = kind_of(prec);
         DWF_REQUIRE(op->lat->has_gauge, DWF_ESTATE, "gauge field not set");
-        const long Vh = op->lat->Vh, Vhp = op->lat->Vhp, n = (long)op->Ls * 12 * Vhp;
-        const size_t bytes = complex_bytes_of(k) * n;
+        const long Vh = op->lat->Vh, Vhp = op->lat->Vhp;
         hipStream_t st = S(stream);
-        DevBuf ie(bytes), oe(bytes), to(bytes), tv(bytes);
+        FieldScratch ie(op, k), oe(op, k), to(op, k), tv(op, k);
         const int* lex = op->lat->lex_of_site_dev.as<int>();
         pack_half(k, ie.p, in, lex, Vh, Vhp, op->Ls, st);
         apply_normal(op, k, oe.p, ie.p, to.p, tv.p, nullptr, 1, st);
@@ -279,15 +277,14 @@ int dwf_cg_residual_update(const dwf_op* op, int prec, void* r, const void* p, d
         DWF_REQUIRE(op->lat->has_gauge, DWF_ESTATE, "gauge field not set");
         const long Vh = op->lat->Vh, Vhp = op->lat->Vhp, n = (long)op->Ls * 12 * Vhp;
         hipStream_t st = S(stream);
-        DevBuf rb(complex_bytes_of(kx) * n), pb(complex_bytes_of(k) * n), to(complex_bytes_of(k) * n),
-            tv(complex_bytes_of(k) * n);
-        DevBuf partial((std::max<long>(hop_partials(op, 1), blas_grid(n)) + 16) * sizeof(double)),
-            scal(CG_NSLOTS * sizeof(double));
+        FieldScratch rb(op, kx), pb(op, k), to(op, k), tv(op, k);
+        const long np = std::max<long>(hop_partials(op, 1), blas_grid(n)) + 16;
+        SmallScratch partial(op, (np + CG_NSLOTS) * sizeof(double));
         const int* lex = op->lat->lex_of_site_dev.as<int>();
         pack_half(kx, rb.p, r, lex, Vh, Vhp, op->Ls, st);
         pack_half(k, pb.p, p, lex, Vh, Vhp, op->Ls, st);
         double* pp = partial.as<double>();
-        double* sc = scal.as<double>();
+        double* sc = pp + np;
         norm2_partial(kx, rb.p, n, pp, st);
         finalize(pp, blas_grid(n), 1, sc + CG_RR, 0, st);
         apply_normal_update_r(op, k, rb.p, pb.p, to.p, tv.p, pp, sc, 1, st);
@@ -311,25 +308,16 @@ int dwf_source_4d(const dwf_op* op, void* b5, const void* b4, void* stream) {
         const int Ls = op->Ls;
         hipStream_t st = S(stream);
         const int* lex = L->lex_of_site_dev.as<int>();
-        const size_t pair_bytes = 16 * (size_t)2 * 12 * Vhp;
-        DevBuf pe(pair_bytes), po(pair_bytes), oe(pair_bytes), oo(pair_bytes);
+        PairScratch pe(op), po(op), oe(op), oo(op);
         pack_chiral_pair_f64(pe.p, b4, lex, Vh, Vhp, st);
         pack_chiral_pair_f64(po.p, b4, lex + Vh, Vh, Vhp, st);
         source_pair(op, oe.p, po.p, pe.p, 0, st);
         source_pair(op, oo.p, pe.p, po.p, 1, st);
-        // b5 = 0 except s = 0 (slice 0 of the pair) and s = Ls-1 (slice 1)
-        DWF_HIP(hipMemsetAsync(b5, 0, (size_t)16 * Ls * V * 12, st));
-        const size_t slice = (size_t)16 * 12 * Vhp;
-        DevBuf fe((size_t)16 * Ls * 12 * Vhp), fo((size_t)16 * Ls * 12 * Vhp);
-        DWF_HIP(hipMemsetAsync(fe.p, 0, fe.bytes, st));
-        DWF_HIP(hipMemsetAsync(fo.p, 0, fo.bytes, st));
-        DWF_HIP(hipMemcpyAsync(fe.p, oe.p, slice, hipMemcpyDeviceToDevice, st));
-        DWF_HIP(hipMemcpyAsync(fo.p, oo.p, slice, hipMemcpyDeviceToDevice, st));
-        DWF_HIP(hipMemcpyAsync(fe.as<char>() + slice * (Ls - 1), oe.as<char>() + slice, slice,
-                               hipMemcpyDeviceToDevice, st));
-        DWF_HIP(hipMemcpyAsync(fo.as<char>() + slice * (Ls - 1), oo.as<char>() + slice, slice,
-                               hipMemcpyDeviceToDevice, st));
-        unpack_full(ST_F64, b5, fe.p, fo.p, lex, Vh, Vhp, V, Ls, st);
+        // b5 = 0 except s = 0 (slice 0 of the pair) and s = Ls-1 (slice 1):
+        // the pair is unpacked with a slice stride of Ls-1 slices
+        const size_t slice = (size_t)16 * V * 12;
+        if (Ls > 2) DWF_HIP(hipMemsetAsync(static_cast<char*>(b5) + slice, 0, slice * (Ls - 2), st));
+        unpack_full(ST_F64, b5, oe.p, oo.p, lex, Vh, Vhp, V * (Ls - 1), 2, st);
         DWF_HIP(hipStreamSynchronize(st));
         return DWF_OK;
     });
@@ -539,8 +527,7 @@ int dwf_ptc_apply(dwf_ptc* m, const dwf_op* op, void* out_e, const void* in_e, v
         const dwf_lattice* L = op->lat;
         DWF_REQUIRE(L->has_gauge, DWF_ESTATE, "gauge field not set");
         hipStream_t st = S(stream);
-        const long n = ptc_field_elems(op);
-        DevBuf a(8 * (size_t)n), b(8 * (size_t)n);
+        FieldScratch a(op, ST_F32), b(op, ST_F32);
         const int* lex = L->lex_of_site_dev.as<int>();
         pack_half(ST_F32, a.p, in_e, lex, L->Vh, L->Vhp, op->Ls, st);
         m->forward(op, a.as<float2>(), b.as<float2>(), st);
@@ -584,8 +571,7 @@ int dwf_ptc_gradient(dwf_ptc* m, const dwf_op* op, const void* r_e, const void* 
         const dwf_lattice* L = op->lat;
         DWF_REQUIRE(L->has_gauge, DWF_ESTATE, "gauge field not set");
         hipStream_t st = S(stream);
-        const long n = ptc_field_elems(op);
-        DevBuf r(8 * (size_t)n), e(8 * (size_t)n);
+        FieldScratch r(op, ST_F32), e(op, ST_F32);
         const int* lex = L->lex_of_site_dev.as<int>();
         pack_half(ST_F32, r.p, r_e, lex, L->Vh, L->Vhp, op->Ls, st);
         pack_half(ST_F32, e.p, e_e, lex, L->Vh, L->Vhp, op->Ls, st);

@@ -22,6 +22,7 @@
 #include <hip/hip_bf16.h>
 
 #include <cstdint>
+#include <exception>
 #include <memory>
 #include <mutex>
 #include <string>
@@ -52,6 +53,10 @@ struct Error {
         if (!(cond)) throw ::dwf::Error{(code), (msg)};                            \
     } while (0)
 
+// Frees the idle scratch buffers of every operator (ScratchPool below); false
+// if there were none.
+bool release_scratch();
+
 // ---------------------------------------------------------------------
 // device buffer (RAII)
 // ---------------------------------------------------------------------
@@ -72,6 +77,10 @@ struct DevBuf {
         release();
         if (n == 0) return;
         hipError_t e = hipMalloc(&p, n);
+        if (e == hipErrorOutOfMemory && release_scratch()) {   // give back idle scratch first
+            (void)hipGetLastError();
+            e = hipMalloc(&p, n);
+        }
         if (e != hipSuccess) {
             p = nullptr;
             throw Error{DWF_ENOMEM, "hipMalloc(" + std::to_string(n) + " bytes) failed"};
@@ -85,6 +94,47 @@ struct DevBuf {
         if (p) (void)hipFree(p);
         p = nullptr;
         bytes = 0;
+    }
+    template <class T> T* as() const { return static_cast<T*>(p); }
+};
+
+// Idle scratch buffers of one operator, kept between calls: hipMalloc and
+// hipFree of the temporaries of one operator application cost more than the
+// application (24^3x48, Ls = 16, FP32 normal operator: 2.3 ms of kernels in a
+// call of 5 to 58 ms).  One list per class of buffer (all of one size and
+// layout, so that the zero padding of a field stays valid), at most MAX_IDLE
+// buffers each; freed with the operator, or by release_scratch() when an
+// allocation of the library finds no memory.  A call takes its own buffers, so
+// calls from several threads never share one.
+struct ScratchPool {
+    // half fields by StoreKind; two-slice FP64 fields; scalars; half fields of the 5D split (no padding)
+    enum Class { F64 = 0, F32 = 1, BF16 = 2, PAIR = 3, SMALL = 4, EO5 = 5, EO5_F32 = 6, NCLASS };
+    static constexpr size_t MAX_IDLE = 6;
+    std::mutex mu;
+    std::vector<DevBuf> idle[NCLASS];
+    ScratchPool();
+    ~ScratchPool();
+    DevBuf take(int cls, size_t bytes);
+    void give(int cls, DevBuf&& b);
+    bool clear();
+};
+
+// A scratch buffer for the length of one call.  It goes back to its pool at
+// the end of the scope, when the work that uses it must have completed; a scope
+// left by an exception, with work possibly in flight, frees it instead.
+class Scratch {
+    ScratchPool& pool_;
+    int cls_;
+    int exc_;
+    DevBuf b_;
+public:
+    void* p;
+    Scratch(ScratchPool& pool, int cls, size_t bytes)
+        : pool_(pool), cls_(cls), exc_(std::uncaught_exceptions()), b_(pool.take(cls, bytes)), p(b_.p) {}
+    Scratch(const Scratch&) = delete;
+    Scratch& operator=(const Scratch&) = delete;
+    ~Scratch() {
+        if (std::uncaught_exceptions() == exc_) pool_.give(cls_, std::move(b_));
     }
     template <class T> T* as() const { return static_cast<T*>(p); }
 };
@@ -153,14 +203,36 @@ struct dwf_op {
     // the type); solves on one operator run one at a time
     mutable std::shared_ptr<void> solve_ws;
     mutable std::mutex solve_mu;
+    mutable dwf::ScratchPool scratch;
     const void* mat(int store_kind, int slot) const {
         const int ck = store_kind == dwf::ST_F64 ? 0 : 1;
         const size_t esz = ck == 0 ? 8 : 4;
         return static_cast<const char*>(mats[ck].p) + (size_t)slot * MAT_ELEMS * esz;
     }
+    // one half field of storage kind `kind` (ops.h: complex_bytes_of) as call scratch
+    size_t field_bytes(int kind) const { return (size_t)Ls * 12 * lat->Vhp * (kind == 0 ? 16 : (kind == 1 ? 8 : 4)); }
     const void* pre(int store_kind, int slot) const {
         const int ck = store_kind == dwf::ST_F64 ? 0 : 1;
         const size_t esz = ck == 0 ? 8 : 4;
         return static_cast<const char*>(pres[ck].p) + (size_t)slot * PRE_ELEMS * esz;
     }
 };
+
+namespace dwf {
+// Call scratch of an operator: a half field, a two-slice FP64 half field
+// (4D sources), and room for `doubles` reduction partials and scalars.
+struct FieldScratch : Scratch {
+    FieldScratch(const dwf_op* op, int kind) : Scratch(op->scratch, kind, op->field_bytes(kind)) {}
+};
+struct PairScratch : Scratch {
+    explicit PairScratch(const dwf_op* op) : Scratch(op->scratch, ScratchPool::PAIR, (size_t)2 * 12 * op->lat->Vhp * 16) {}
+};
+struct SmallScratch : Scratch {
+    SmallScratch(const dwf_op* op, size_t bytes) : Scratch(op->scratch, ScratchPool::SMALL, bytes) {}
+};
+// half field of the 5D split, storage kind F64 or F32
+struct Eo5Scratch : Scratch {
+    Eo5Scratch(const dwf_op* op, int kind)
+        : Scratch(op->scratch, ScratchPool::EO5 + kind, (size_t)op->Ls * 12 * op->lat->Vh * (kind == 0 ? 16 : 8)) {}
+};
+}  // namespace dwf

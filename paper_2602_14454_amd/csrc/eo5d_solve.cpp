@@ -164,11 +164,11 @@ void apply_eo5_schur(const dwf_op* op, int kind, int dagger, void* out5, const v
     DWF_REQUIRE(kind == ST_F64 || kind == ST_F32, DWF_EINVAL, "the 5D even-odd split runs in FP64 or FP32");
     double hc[EO5_NCOEF];
     eo5_coefficients(op, hc);
-    DevBuf coef(sizeof hc);
+    SmallScratch coef(op, sizeof hc);
     DWF_HIP(hipMemcpyAsync(coef.p, hc, sizeof hc, hipMemcpyHostToDevice, st));
     const long n = (long)op->Ls * L->Vh * 12;
     const int* lex = L->lex_of_site_dev.as<int>();
-    DevBuf e64(16 * n), ek(complex_bytes_of(kind) * n), ok(complex_bytes_of(kind) * n), tk(complex_bytes_of(kind) * n);
+    Eo5Scratch e64(op, ST_F64), ek(op, kind), ok(op, kind), tk(op, kind);
     eo5_pack(e64.p, in5, lex, L->Vh, L->V, op->Ls, 0, st);
     eo5_convert(kind, ST_F64, ek.p, e64.p, n, st);
     eo5_dhat(op, kind, dagger, ok.p, ek.p, tk.p, coef.as<double>(), st);

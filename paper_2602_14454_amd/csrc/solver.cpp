@@ -571,15 +571,15 @@ double true_residual(const dwf_op* op, const void* x5, const void* b5, hipStream
     const long Vh = L->Vh, Vhp = L->Vhp, V = L->V;
     const int Ls = op->Ls;
     const long n = (long)Ls * 12 * Vhp;
-    DevBuf xe(16 * n), xo(16 * n), be(16 * n), bo(16 * n), te(16 * n), to(16 * n);
-    DevBuf partial((blas_grid(n) + 16) * sizeof(double)), scal(CG_NSLOTS * sizeof(double));
+    FieldScratch xe(op, ST_F64), xo(op, ST_F64), be(op, ST_F64), bo(op, ST_F64), te(op, ST_F64), to(op, ST_F64);
+    SmallScratch partial(op, (size_t)(blas_grid(n) + CG_NSLOTS) * sizeof(double));
     Pinned hs(CG_NSLOTS);
     const int* lex = L->lex_of_site_dev.as<int>();
     pack_full(ST_F64, xe.p, xo.p, x5, lex, Vh, Vhp, V, Ls, st);
     pack_full(ST_F64, be.p, bo.p, b5, lex, Vh, Vhp, V, Ls, st);
     apply_full(op, ST_F64, 0, te.p, to.p, xe.p, xo.p, 1, st);
     double* pp = partial.as<double>();
-    double* sc = scal.as<double>();
+    double* sc = pp + blas_grid(n);
     const double b2 = norm2_host(ST_F64, be.p, n, pp, sc, hs, st) + norm2_host(ST_F64, bo.p, n, pp, sc, hs, st);
     axpby(ST_F64, ST_F64, te.p, be.p, n, nullptr, 1.0, nullptr, -1.0, nullptr, st);
     axpby(ST_F64, ST_F64, to.p, bo.p, n, nullptr, 1.0, nullptr, -1.0, nullptr, st);

@@ -72,3 +72,54 @@ def test_link_tables(dims, antiperiodic):
         for prec in (0, 1, 2):
             op.apply(out, _dev(x), dwf.FULL5D, False, prec)
             assert _rel(out.cpu().numpy(), want) < TOL[prec]
+
+
+def test_call_scratch_is_private_and_clean():
+    """Scratch kept by an operator between calls: what earlier calls of other kinds left in it changes no
+    result, and calls from two threads on two streams do not share it."""
+    import threading
+
+    import torch
+
+    import paper_2602_14454_amd as dwf
+    dims, Ls = (6, 6, 4, 14), 4
+    lat, op, p, U = _make(dims, Ls)
+    _, fresh, _, _ = _make(dims, Ls)
+    V = p.V
+    x5 = [_dev(dwfgen.gaussian_source_5d(dims, Ls, 20 + k)) for k in range(2)]
+    out5 = torch.empty_like(x5[0])
+    for prec in (0, 1, 2):
+        op.apply(out5, x5[0], dwf.FULL5D, False, prec)
+        op.apply_normal(out5[:, : V // 2].contiguous(), x5[0][:, : V // 2].contiguous(), prec)
+    op.apply_eo5(out5, x5[0], False, 0)
+    op.apply_eo5(out5, x5[0], True, 1)
+    op.source_4d(out5, x5[0][0].contiguous())
+    pvec = x5[1][:, : V // 2].contiguous()
+    for prec in (0, 1, 2):
+        got = []
+        for o in (op, fresh):
+            r = x5[0][:, : V // 2].contiguous()
+            got.append((o.cg_residual_update(r, pvec, prec), r))
+        assert got[0][0] == got[1][0] and torch.equal(got[0][1], got[1][1])
+    assert op.true_residual(x5[0], x5[1]) == fresh.true_residual(x5[0], x5[1])
+
+    want = [fresh.apply(torch.empty_like(x), x).clone() for x in x5]
+    torch.cuda.synchronize()
+    bad = []
+
+    def work(k):
+        st = torch.cuda.Stream()
+        out = torch.empty_like(x5[k])
+        for _ in range(20):
+            out.fill_(float("nan"))
+            torch.cuda.synchronize()
+            op.apply(out, x5[k], stream=st.cuda_stream)
+            if not torch.equal(out, want[k]):
+                bad.append(k)
+
+    ts = [threading.Thread(target=work, args=(k,)) for k in range(2)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    assert not bad

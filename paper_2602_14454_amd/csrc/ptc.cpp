@@ -1,7 +1,8 @@
 // Learned preconditioner: model object, forward, training step, training
 // pairs and checkpoint files.  The network (ptc_kernels.hip) is linear:
 //   M r = PTC_2(PTC_1(r)),  PTC_1: 1 -> H channels (even input, hidden on
-//   both parities),  PTC_2: H -> 1 channel (even output).
+//   both parities),  PTC_2: H -> 1 channel (even output),
+// and runs as one sum over pairs of paths unless H = 1.
 // Training minimises |M r - e|^2 / |e|^2 over pairs (r_k = A e_k, e_k =
 // x* - x_k) taken from CGNR runs on D^dag D^, with Adam; forward, backward
 // and the update all run in the kernels of ptc_kernels.hip.
@@ -33,7 +34,7 @@ static const int* nbr_of(const dwf_op* op, int parity) {
 }
 
 static PtcLayerParams layer_params(const dwf_op* op, int parity, const float2* in_loc, const float2* in_hop,
-                                   float2* out, const float2* W, int A, int B) {
+                                   float2* out, const float2* W) {
     PtcLayerParams P{};
     P.in_loc = in_loc;
     P.in_hop = in_hop;
@@ -44,9 +45,6 @@ static PtcLayerParams layer_params(const dwf_op* op, int parity, const float2* i
     P.Vh = op->lat->Vh;
     P.Vhp = op->lat->Vhp;
     P.Ls = op->Ls;
-    P.A = A;
-    P.B = B;
-    P.accumulate = 0;
     return P;
 }
 
@@ -59,39 +57,43 @@ dwf_ptc::dwf_ptc(int hidden) : H(hidden) {
     nw = 2L * 11 * H * 16;
     W.alloc(nw * sizeof(float2));
     G.alloc(nw * sizeof(float2));
-    Wt.alloc((size_t)11 * H * 16 * sizeof(float2));
     m.alloc(2 * nw * sizeof(float));
     v.alloc(2 * nw * sizeof(float));
     stats.alloc(8 * sizeof(double));
-    // weight-gradient rows (path, b, first a)
-    std::vector<int> r2, r1e, r1o;
-    for (int q = 0; q < 11; ++q)
-        for (int b = 0; b < H; ++b) r2.insert(r2.end(), {q, b, 0});
-    const int ac = ptc_wgrad_ac(H);
-    for (int q : {0, 9, 10})
-        for (int a = 0; a < H; a += ac) r1e.insert(r1e.end(), {q, 0, a});
-    for (int q = 1; q <= 8; ++q)
-        for (int a = 0; a < H; a += ac) r1o.insert(r1o.end(), {q, 0, a});
-    n2 = (int)r2.size() / 3;
-    n1e = (int)r1e.size() / 3;
-    n1o = (int)r1o.size() / 3;
-    rows.alloc((r2.size() + r1e.size() + r1o.size()) * sizeof(int));
-    int* rp = rows.as<int>();
-    DWF_HIP(hipMemcpy(rp, r2.data(), r2.size() * sizeof(int), hipMemcpyHostToDevice));
-    DWF_HIP(hipMemcpy(rp + r2.size(), r1e.data(), r1e.size() * sizeof(int), hipMemcpyHostToDevice));
-    DWF_HIP(hipMemcpy(rp + r2.size() + r1e.size(), r1o.data(), r1o.size() * sizeof(int), hipMemcpyHostToDevice));
+    pair_w.alloc(4096 * sizeof(float) + 2 * 7 * 16 * sizeof(float2));
 }
 
 const float2* dwf_ptc::W1() const { return W.as<float2>(); }
 const float2* dwf_ptc::W2() const { return W.as<float2>() + 11L * H * 16; }
 
-void dwf_ptc::reserve(const dwf_op* op) {
+static PtcPairParams pair_params(const dwf_ptc* M, const dwf_op* op) {
+    PtcPairParams P{};
+    P.W1 = M->W1();
+    P.W2 = M->W2();
+    for (int p = 0; p < 2; ++p) {
+        P.links[p] = links32(op, p);
+        P.nbr[p] = nbr_of(op, p);
+    }
+    P.Vh = op->lat->Vh;
+    P.Vhp = op->lat->Vhp;
+    P.Ls = op->Ls;
+    P.H = M->H;
+    P.mid = M->hid.as<float2>();
+    P.el = M->pair_w.as<float>();
+    P.al = reinterpret_cast<float2*>(P.el + 4096);
+    return P;
+}
+
+// Pair sums for two and more hidden channels: their cost does not grow with the
+// channels (16^3x32, Ls = 16: 0.67 ms).  The layers take 0.48 ms with one
+// channel, 0.71 ms with two, 2.5 ms with eight (8^4, Ls = 8: 36, 54 and 135 us
+// against 47).
+static bool by_pairs(int H) { return H >= 2; }
+
+void dwf_ptc::reserve(const dwf_op* op, hipStream_t st) {
     const long n = ptc_field_elems(op);
     if (n > cap_n) {
-        he.alloc((size_t)H * n * sizeof(float2));
-        ho.alloc((size_t)H * n * sizeof(float2));
-        ghe.alloc((size_t)H * n * sizeof(float2));
-        gho.alloc((size_t)H * n * sizeof(float2));
+        hid.alloc((size_t)(by_pairs(H) ? 8 : 2) * n * sizeof(float2));
         y.alloc(n * sizeof(float2));
         g.alloc(n * sizeof(float2));
         lpartial.alloc(2 * (size_t)ptc_loss_blocks(n) * sizeof(double));
@@ -101,17 +103,24 @@ void dwf_ptc::reserve(const dwf_op* op) {
         to.alloc(n * sizeof(float2));
         tv.alloc(n * sizeof(float2));
         cap_n = n;
+    } else if (lay_n != n || lay_vhp != op->lat->Vhp) {
+        // another lattice: the loss sums run over whole rows, padding included
+        for (DevBuf* b : {&y, &d, &u}) DWF_HIP(hipMemsetAsync(b->p, 0, b->bytes, st));
     }
-    PtcLayerParams P = layer_params(op, 0, nullptr, nullptr, nullptr, nullptr, 1, H);
-    const size_t need = (size_t)std::max(n2, std::max(n1e, n1o)) * ptc_wgrad_blocks(P) * 64 * sizeof(float);
-    if (need > wpart.bytes) wpart.alloc(need);
+    lay_n = n;
+    lay_vhp = op->lat->Vhp;
 }
 
 void dwf_ptc::forward(const dwf_op* op, const float2* r, float2* out, hipStream_t st) {
-    reserve(op);
-    ptc_layer(layer_params(op, 0, r, nullptr, he.as<float2>(), W1(), H, 1), st);
-    ptc_layer(layer_params(op, 1, nullptr, r, ho.as<float2>(), W1(), H, 1), st);
-    ptc_layer(layer_params(op, 0, he.as<float2>(), ho.as<float2>(), out, W2(), 1, H), st);
+    reserve(op, st);
+    if (by_pairs(H)) {
+        ptc_pairs_forward(pair_params(this, op), r, out, st);
+        return;
+    }
+    float2 *he = hid.as<float2>(), *ho = he + ptc_field_elems(op);
+    ptc_layer(layer_params(op, 0, r, nullptr, he, W1()), st);
+    ptc_layer(layer_params(op, 1, nullptr, r, ho, W1()), st);
+    ptc_layer(layer_params(op, 0, he, ho, out, W2()), st);
 }
 
 // Loss of one pair and its gradient with respect to the output y = M r:
@@ -120,7 +129,7 @@ void dwf_ptc::forward(const dwf_op* op, const float2* r, float2* out, hipStream_
 // (A = D^dag D^ Hermitian; with r = A e the second is |A M r - r|^2 / |r|^2,
 // the residual left by the right-preconditioned operator).
 void dwf_ptc::loss(const dwf_op* op, const float2* r, const float2* e, bool value_only, hipStream_t st) {
-    reserve(op);
+    reserve(op, st);
     const long n = ptc_field_elems(op);
     forward(op, r, y.as<float2>(), st);
     if (loss_kind == 0) {
@@ -138,22 +147,10 @@ void dwf_ptc::loss(const dwf_op* op, const float2* r, const float2* e, bool valu
 
 void dwf_ptc::gradient(const dwf_op* op, const float2* r, const float2* e, hipStream_t st) {
     loss(op, r, e, false, st);
-    DWF_HIP(hipMemsetAsync(G.p, 0, nw * sizeof(float2), st));
-    float2* G1 = G.as<float2>();
-    float2* G2 = G.as<float2>() + 11L * H * 16;
-    const int* rp = rows.as<int>();
-    float* wp = wpart.as<float>();
-    // layer 2: dL/dW2 from (he, ho) and g
-    ptc_wgrad(layer_params(op, 0, he.as<float2>(), ho.as<float2>(), nullptr, W2(), 1, H), g.as<float2>(), rp, n2, wp,
-              G2, st);
-    // hidden gradients through the adjoint layer
-    ptc_adjoint(W2(), Wt.as<float2>(), 1, H, st);
-    ptc_layer(layer_params(op, 0, g.as<float2>(), nullptr, ghe.as<float2>(), Wt.as<float2>(), H, 1), st);
-    ptc_layer(layer_params(op, 1, nullptr, g.as<float2>(), gho.as<float2>(), Wt.as<float2>(), H, 1), st);
-    // layer 1: even outputs (paths 0, +-s), odd outputs (link paths)
-    ptc_wgrad(layer_params(op, 0, r, nullptr, nullptr, W1(), H, 1), ghe.as<float2>(), rp + 3 * n2, n1e, wp, G1, st);
-    ptc_wgrad(layer_params(op, 1, nullptr, r, nullptr, W1(), H, 1), gho.as<float2>(), rp + 3 * (n2 + n1e), n1o, wp,
-              G1, st);
+    const PtcPairParams P = pair_params(this, op);
+    const size_t need = ptc_corr_bytes(P);
+    if (need > corr.bytes) corr.alloc(need);
+    ptc_pairs_gradient(P, r, g.as<float2>(), corr.as<double>(), G.as<float2>(), G.as<float2>() + 11L * H * 16, st);
 }
 
 void dwf_ptc::train_step(const dwf_op* op, const float2* r, const float2* e, double lr, hipStream_t st) {
@@ -276,7 +273,6 @@ double ptc_eval(dwf_ptc* M, int nsets, dwf_ptc_pairs* const* sets, hipStream_t s
     double h = 0;
     for (int i = 0; i < nsets; ++i) {
         const dwf_ptc_pairs* S = sets[i];
-        M->reserve(S->op);
         for (int j = 0; j < S->count; ++j) {
             M->loss(S->op, S->r.as<float2>() + (size_t)j * S->n, S->e.as<float2>() + (size_t)j * S->n, true, st);
             DWF_HIP(hipMemcpyAsync(&h, M->stats.p, sizeof(double), hipMemcpyDeviceToHost, st));

@@ -10,6 +10,18 @@
 // backward, boundary phase folded; the same tables as the Wilson hop), W is
 // a complex 4x4 spin matrix and in_loc / in_hop live on parity p / 1 - p.
 // Path numbering: 0 identity, 1..8 = direction d + 1, 9 = +s, 10 = -s.
+//
+// The network is linear, and a weight (spin) commutes with a transport
+// (colour, site), so the two layers are one sum over pairs of paths:
+//   M r = sum_{q, q'} E_{qq'} T_q T_q' r,   E_{qq'} = sum_b W2_q^b W1_q'^b  (4x4),
+// q, q' both local (even hidden sites) or both links (odd hidden sites).  Its
+// cost does not depend on the number of hidden channels, and neither does that
+// of the gradient, which needs the 4x4 correlations dL/dE_{qq'} =
+// sum (T_q^dag g) (T_q' r)^dag and then only products of small matrices:
+//   dL/dW2_q^b = sum_q' dL/dE_{qq'} W1_q'^b^dag,  dL/dW1_q'^b = sum_q W2_q^b^dag dL/dE_{qq'}.
+// E is summed in FP64 and rounded once.
+#include <algorithm>
+
 #include "dwf_internal.h"
 #include "precision.h"
 #include "ptc.h"
@@ -17,16 +29,7 @@
 namespace dwf {
 
 constexpr int PT = 256;
-#ifndef DWF_PTC_COMMUTE
-#define DWF_PTC_COMMUTE 1
-#endif
 
-__device__ __forceinline__ float2 cmul(float2 a, float2 b) {
-    return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-__device__ __forceinline__ float2 cmulc(float2 a, float2 b) {   // a * conj(b)
-    return make_float2(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
-}
 __device__ __forceinline__ void cfma(float2& acc, float2 a, float2 b) {
     acc.x += a.x * b.x - a.y * b.y;
     acc.y += a.x * b.y + a.y * b.x;
@@ -99,210 +102,389 @@ __device__ __forceinline__ void spin_apply(const float2* __restrict__ W, const f
         }
 }
 
-// Input of path q for channel b at (site i, slice s): true if nonzero.
-__device__ __forceinline__ bool path_input(const PtcLayerParams& P, int q, int b, int s, long i, float2 (&t)[12]) {
-    const long Vhp = P.Vhp;
-    if (q == 0 || q >= 9) {
-        if (!P.in_loc) return false;
-        const int ss = q == 0 ? s : (q == 9 ? s + 1 : s - 1);
-        if (ss < 0 || ss >= P.Ls) return false;
-        load12(P.in_loc, ((long)b * P.Ls + ss) * 12, i, Vhp, t);
-        return true;
-    }
-    if (!P.in_hop) return false;
-    const int d = q - 1;
-    const long y = P.nbr[(long)d * Vhp + i];
-    float2 v[12];
-    load12(P.in_hop, ((long)b * P.Ls + s) * 12, y, Vhp, v);
-    transport(P.links, d, i, Vhp, v, t);
-    return true;
-}
-
-// grid (ceil(Vh / PT), Ls, A / AC); AC output channels per thread.  The
-// path loop is outside the channel loop: a hop path's link (9 complex) and
-// neighbour index are loaded once per thread and serve every input channel,
-// and the weights of a path are read with wave-uniform addresses.
-// COMMUTE: the spin weights act on spin and the link on colour, so
-//   sum_b W^{ab} L v^b = L (sum_b W^{ab} v^b);
-// with more input than output channels (the second layer, 8 -> 1) the
-// channels are combined first and transported once per output channel.
-template <int AC, bool COMMUTE>
+// One layer from one channel to one: one thread per (site, slice).
 __global__ __launch_bounds__(PT) void ptc_layer_kernel(PtcLayerParams P) {
     const long i = (long)blockIdx.x * PT + threadIdx.x;
     if (i >= P.Vh) return;
     const int s = blockIdx.y;
-    const int a0 = blockIdx.z * AC;
     const long Vhp = P.Vhp;
-    float2 acc[AC][12];
+    float2 acc[12];
 #pragma unroll
-    for (int a = 0; a < AC; ++a)
-#pragma unroll
-        for (int k = 0; k < 12; ++k) acc[a][k] = make_float2(0.f, 0.f);
+    for (int k = 0; k < 12; ++k) acc[k] = make_float2(0.f, 0.f);
     // local paths: 0 (same slice), 9 (s + 1), 10 (s - 1)
     if (P.in_loc) {
         for (int qi = 0; qi < 3; ++qi) {
             const int q = qi == 0 ? 0 : 8 + qi;
             const int ss = qi == 0 ? s : (qi == 1 ? s + 1 : s - 1);
             if (ss < 0 || ss >= P.Ls) continue;
-            for (int b = 0; b < P.B; ++b) {
-                float2 t[12];
-                load12(P.in_loc, ((long)b * P.Ls + ss) * 12, i, Vhp, t);
-#pragma unroll
-                for (int a = 0; a < AC; ++a)
-                    spin_apply(P.W + (((long)q * P.A + a0 + a) * P.B + b) * 16, t, acc[a]);
-            }
+            float2 t[12];
+            load12(P.in_loc, (long)ss * 12, i, Vhp, t);
+            spin_apply(P.W + q * 16, t, acc);
         }
     }
-    // link paths 1..8: the link and neighbour of direction d once for all channels
+    // link paths 1..8
     if (P.in_hop) {
         for (int d = 0; d < 8; ++d) {
             const long y = P.nbr[(long)d * Vhp + i];
-            float2 L[10];
-            if constexpr (link_lp(8) == 2) {
-#pragma unroll
-                for (int g = 0; g < 5; ++g) {
-                    const float4 v4 = *reinterpret_cast<const float4*>(P.links + lidx(d, 2 * g, i, Vhp, 8));
-                    L[2 * g] = make_float2(v4.x, v4.y);
-                    L[2 * g + 1] = make_float2(v4.z, v4.w);
-                }
-            } else {
-#pragma unroll
-                for (int e = 0; e < 9; ++e) L[e] = P.links[lidx(d, e, i, Vhp, 8)];
-            }
-            if constexpr (COMMUTE) {
-                float2 m[AC][12];
-#pragma unroll
-                for (int a = 0; a < AC; ++a)
-#pragma unroll
-                    for (int k = 0; k < 12; ++k) m[a][k] = make_float2(0.f, 0.f);
-                for (int b = 0; b < P.B; ++b) {
-                    float2 v[12];
-                    load12(P.in_hop, ((long)b * P.Ls + s) * 12, y, Vhp, v);
-#pragma unroll
-                    for (int a = 0; a < AC; ++a)
-                        spin_apply(P.W + (((long)(1 + d) * P.A + a0 + a) * P.B + b) * 16, v, m[a]);
-                }
-#pragma unroll
-                for (int a = 0; a < AC; ++a)
-#pragma unroll
-                    for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-                        for (int c3 = 0; c3 < 3; ++c3)
-#pragma unroll
-                            for (int bb = 0; bb < 3; ++bb) cfma(acc[a][sp * 3 + c3], L[c3 * 3 + bb], m[a][sp * 3 + bb]);
-            } else {
-                for (int b = 0; b < P.B; ++b) {
-                    float2 v[12], t[12];
-                    load12(P.in_hop, ((long)b * P.Ls + s) * 12, y, Vhp, v);
-#pragma unroll
-                    for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-                        for (int a = 0; a < 3; ++a) {
-                            float2 c = make_float2(0.f, 0.f);
-#pragma unroll
-                            for (int bb = 0; bb < 3; ++bb) cfma(c, L[a * 3 + bb], v[sp * 3 + bb]);
-                            t[sp * 3 + a] = c;
-                        }
-#pragma unroll
-                    for (int a = 0; a < AC; ++a)
-                        spin_apply(P.W + (((long)(1 + d) * P.A + a0 + a) * P.B + b) * 16, t, acc[a]);
-                }
-            }
+            float2 v[12], t[12];
+            load12(P.in_hop, (long)s * 12, y, Vhp, v);
+            transport(P.links, d, i, Vhp, v, t);
+            spin_apply(P.W + (1 + d) * 16, t, acc);
         }
     }
-#pragma unroll
-    for (int a = 0; a < AC; ++a) {
-        const long row0 = ((long)(a0 + a) * P.Ls + s) * 12;
-        if (P.accumulate) {
-            float2 o[12];
-            load12(P.out, row0, i, P.Vhp, o);
-#pragma unroll
-            for (int k = 0; k < 12; ++k) {
-                acc[a][k].x += o[k].x;
-                acc[a][k].y += o[k].y;
+    store12(P.out, (long)s * 12, i, P.Vhp, acc);
+}
+
+// ---------------------------------------------------------------------
+// the two layers as one (E_{qq'} above)
+// ---------------------------------------------------------------------
+typedef float v16f __attribute__((ext_vector_type(16)));
+
+// Link part of E as the MFMA A operand of ptc_mid_kernel, then the local part:
+//   el[((d' * 4 + j) * 2 + tile) * 64 + lane], lane = 32 h + 4 d + i:
+//     the factor of (re, im)[h] of t_{d', j} in (re, im)[tile] of g_{d, i}
+//   al[k * 16 + i * 4 + j]: k = 0..4 the factor of r(s + k - 2); k = 5, 6 the
+//     terms through s + 1 and s - 1 and back, present where that slice is;
+//     al[112 + ..] what rounding these to FP32 left (they hold the identity that
+//     a trained network stays near: their rounding would be the same at every
+//     site, and the gradients' error against 64 bits 15 % larger with it).
+__global__ __launch_bounds__(PT) void ptc_pair_weights(const float2* __restrict__ W1, const float2* __restrict__ W2,
+                                                       int H, float* __restrict__ el, float2* __restrict__ al) {
+    const int t = blockIdx.x * PT + threadIdx.x;
+    if (t >= 1024 + 7 * 16) return;
+    int q[2] = {0, 0}, p[2] = {0, 0}, n = 1, i, j;
+    if (t < 1024) {   // t = d' * 128 + j * 32 + d * 4 + i
+        i = t & 3;
+        q[0] = 1 + ((t >> 2) & 7);
+        j = (t >> 5) & 3;
+        p[0] = 1 + (t >> 7);
+    } else {
+        const int k = (t - 1024) >> 4;
+        i = ((t - 1024) >> 2) & 3;
+        j = t & 3;
+        if (k == 0) { q[0] = 10; p[0] = 10; }
+        if (k == 1) { q[0] = 0; p[0] = 10; q[1] = 10; p[1] = 0; n = 2; }
+        if (k == 3) { q[0] = 0; p[0] = 9; q[1] = 9; p[1] = 0; n = 2; }
+        if (k == 4) { q[0] = 9; p[0] = 9; }
+        if (k == 5) { q[0] = 9; p[0] = 10; }
+        if (k == 6) { q[0] = 10; p[0] = 9; }
+    }
+    double re = 0.0, im = 0.0;
+    for (int m = 0; m < n; ++m)
+        for (int b = 0; b < H; ++b)
+            for (int k = 0; k < 4; ++k) {
+                const float2 x = W2[((long)q[m] * H + b) * 16 + i * 4 + k], y = W1[((long)p[m] * H + b) * 16 + k * 4 + j];
+                re += (double)x.x * y.x - (double)x.y * y.y;
+                im += (double)x.x * y.y + (double)x.y * y.x;
             }
-        }
-        store12(P.out, row0, i, P.Vhp, acc[a]);
+    if (t < 1024) {
+        const int d = q[0] - 1, ks = (p[0] - 1) * 4 + j;
+        float* o = el + (long)ks * 128 + 4 * d + i;
+        o[0] = (float)re;
+        o[32] = (float)-im;
+        o[64] = (float)im;
+        o[96] = (float)re;
+    } else {
+        const float2 hi = make_float2((float)re, (float)im);
+        al[t - 1024] = hi;
+        al[t - 1024 + 112] = make_float2((float)(re - hi.x), (float)(im - hi.y));
     }
 }
 
-// Weight gradient rows: row = (path index in `paths`, b, a-group); each block
-// sums over its PT (site, slice) pairs
-//   G[a][i][j] = sum_c g^a_i conj(t^b_j)   (t = path input of channel b)
-// and writes AC * 16 complex partials.  The per-block order is fixed, so the
-// result is deterministic.
-template <int AC>
-__global__ __launch_bounds__(PT) void ptc_wgrad_kernel(PtcLayerParams P, const float2* __restrict__ g,
-                                                       const int* __restrict__ rows, float* __restrict__ partial) {
-    __shared__ float red[PT / 64][AC * 32];
-    const int row = blockIdx.y;
-    const int q = rows[3 * row], b = rows[3 * row + 1], a0 = rows[3 * row + 2];
-    const long t_id = (long)blockIdx.x * PT + threadIdx.x;
-    const long Vh = P.Vh, Vhp = P.Vhp;
-    float2 acc[AC][16];
+// g_d(y, s) = sum_{d'} E_{dd'} (T_d' r)(y, s) for the eight d at the sites y of
+// one parity (odd), as 32 x 32 complex times 32 x (sites x colours) on
+// v_mfma_f32_32x32x2: a wave takes 32 sites of one slice, and the two halves
+// of its lanes hold the real and the imaginary part of the same t, which is
+// the B operand (column = site, k = re/im).  A lane ends up with four of the
+// eight g_d of its site.  Links, neighbours and E are in LDS for the block's
+// 32 sites and all slices.  Bound by the matrix cores: 12288 multiply-adds per
+// site and slice against 3 KB read or written; 403 us on
+// 16^3x32, Ls = 16 (96 TFLOP/s of the 152 a large FP32 product reaches).  The
+// whole network there: 0.67 ms for any number of channels; two layers of 8
+// channels, one thread per site and slice, took 2.5 to 2.8 ms.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void ptc_mid_kernel(
+    const float2* __restrict__ r, float2* __restrict__ g, const float2* __restrict__ links,
+    const int* __restrict__ nbr, const float* __restrict__ el, long Vh, long Vhp, int Ls) {
+    __shared__ u32x4 lnk[8 * 5 * 32];
+    __shared__ u32x4 ew4[1024];
+    __shared__ int lnb[8 * 32];
+    const long tile = blockIdx.x;
+    const int nthr = blockDim.x;
+    for (int e = threadIdx.x; e < 8 * 5 * 32; e += nthr) {
+        const long site = tile * 32 + (e & 31);
+        lnk[e] = reinterpret_cast<const u32x4*>(links)[(long)(e >> 5) * Vhp + (site < Vh ? site : Vh - 1)];
+    }
+    for (int e = threadIdx.x; e < 8 * 32; e += nthr) {
+        const long site = tile * 32 + (e & 31);
+        lnb[e] = nbr[(long)(e >> 5) * Vhp + (site < Vh ? site : Vh - 1)];
+    }
+    for (int e = threadIdx.x; e < 1024; e += nthr) ew4[e] = reinterpret_cast<const u32x4*>(el)[e];
+    __syncthreads();
+    const float* ew = reinterpret_cast<const float*>(ew4);
+    const int lane = threadIdx.x & 63, j = lane & 31, h = lane >> 5;
+    const long site = tile * 32 + j;
+    const long n = (long)Ls * 12 * Vhp;
+    const float4* r4 = reinterpret_cast<const float4*>(r);
+    for (int s = threadIdx.x >> 6; s < Ls; s += nthr >> 6) {
+        v16f acc[3][2];
 #pragma unroll
-    for (int a = 0; a < AC; ++a)
+        for (int c = 0; c < 3; ++c)
 #pragma unroll
-        for (int k = 0; k < 16; ++k) acc[a][k] = make_float2(0.f, 0.f);
-    if (t_id < Vh * P.Ls) {
-        const int s = (int)(t_id / Vh);
-        const long i = t_id % Vh;
-        float2 t[12];
-        if (path_input(P, q, b, s, i, t)) {
+            for (int k = 0; k < 16; ++k) { acc[c][0][k] = 0.f; acc[c][1][k] = 0.f; }
+        float4 nx[6];
 #pragma unroll
-            for (int a = 0; a < AC; ++a) {
-                float2 gv[12];
-                load12(g, ((long)(a0 + a) * P.Ls + s) * 12, i, Vhp, gv);
+        for (int q = 0; q < 6; ++q) nx[q] = r4[(long)(s * 6 + q) * Vhp + lnb[j]];
+#pragma unroll 1
+        for (int d = 0; d < 8; ++d) {
+            // real lanes use (re, -im) of the spinor, imaginary lanes (im, re)
+            float a[12], b[12];
 #pragma unroll
-                for (int ii = 0; ii < 4; ++ii)
+            for (int q = 0; q < 6; ++q) {
+                a[2 * q] = h ? nx[q].y : nx[q].x;
+                b[2 * q] = h ? nx[q].x : -nx[q].y;
+                a[2 * q + 1] = h ? nx[q].w : nx[q].z;
+                b[2 * q + 1] = h ? nx[q].z : -nx[q].w;
+            }
+            const int y = lnb[(d < 7 ? d + 1 : 7) * 32 + j];   // the next direction's spinor, in flight meanwhile
 #pragma unroll
-                    for (int jj = 0; jj < 4; ++jj)
+            for (int q = 0; q < 6; ++q) nx[q] = r4[(long)(s * 6 + q) * Vhp + y];
+            float U[20];
 #pragma unroll
-                        for (int c = 0; c < 3; ++c) {
-                            const float2 pr = cmulc(gv[ii * 3 + c], t[jj * 3 + c]);
-                            acc[a][ii * 4 + jj].x += pr.x;
-                            acc[a][ii * 4 + jj].y += pr.y;
-                        }
+            for (int k = 0; k < 5; ++k) {
+                const u32x4 w = lnk[(d * 5 + k) * 32 + j];
+                U[4 * k] = __uint_as_float(w.x);
+                U[4 * k + 1] = __uint_as_float(w.y);
+                U[4 * k + 2] = __uint_as_float(w.z);
+                U[4 * k + 3] = __uint_as_float(w.w);
+            }
+#pragma unroll
+            for (int sp = 0; sp < 4; ++sp) {
+                const float e0 = ew[((d * 4 + sp) * 2) * 64 + lane], e1 = ew[((d * 4 + sp) * 2 + 1) * 64 + lane];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    float t = U[6 * c] * a[sp * 3];
+                    t = __builtin_fmaf(U[6 * c + 1], b[sp * 3], t);
+#pragma unroll
+                    for (int k = 1; k < 3; ++k) {
+                        t = __builtin_fmaf(U[6 * c + 2 * k], a[sp * 3 + k], t);
+                        t = __builtin_fmaf(U[6 * c + 2 * k + 1], b[sp * 3 + k], t);
+                    }
+                    acc[c][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(e0, t, acc[c][0], 0, 0, 0);
+                    acc[c][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(e1, t, acc[c][1], 0, 0, 0);
+                }
+            }
+        }
+        if (site < Vh) {
+            // rows of accumulator slot 4 k + i: 8 k + 4 h + i = 4 (2 k + h) + i, spin i of direction 2 k + h
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                float2* gd = g + (long)(2 * k + h) * n;
+#pragma unroll
+                for (int q = 0; q < 6; ++q) {
+                    const int c0 = (2 * q) % 3, s0 = (2 * q) / 3, c1 = (2 * q + 1) % 3, s1 = (2 * q + 1) / 3;
+                    reinterpret_cast<float4*>(gd)[(long)(s * 6 + q) * Vhp + site] =
+                        make_float4(acc[c0][0][4 * k + s0], acc[c0][1][4 * k + s0], acc[c1][0][4 * k + s1],
+                                    acc[c1][1][4 * k + s1]);
+                }
             }
         }
     }
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+}
+
+// out(x, s) = local pairs of r + sum_d L_d(x) g_d(nbr_d(x), s) at the even
+// sites; one thread per (site, slice), one slice per wave.  Bound by memory:
+// every g_d is read once (8 fields; 271 us on 16^3x32, Ls = 16, 3.7 TB/s), r and
+// the links from cache.
+__global__ __launch_bounds__(256) void ptc_out_kernel(const float2* __restrict__ r, const float2* __restrict__ g,
+                                                      float2* __restrict__ out, const float2* __restrict__ links,
+                                                      const int* __restrict__ nbr, const float2* __restrict__ al,
+                                                      long Vh, long Vhp, int Ls) {
+    const long i = (long)blockIdx.x * 64 + (threadIdx.x & 63);
+    const int s = __builtin_amdgcn_readfirstlane((int)blockIdx.y * 4 + (int)(threadIdx.x >> 6));
+    if (s >= Ls || i >= Vh) return;
+    const long n = (long)Ls * 12 * Vhp;
+    float2 acc[12];
 #pragma unroll
-    for (int a = 0; a < AC; ++a)
+    for (int k = 0; k < 12; ++k) acc[k] = make_float2(0.f, 0.f);
+#pragma unroll 2
+    for (int d = 0; d < 8; ++d) {
+        const long y = nbr[(long)d * Vhp + i];
+        float2 m[12], t[12];
+        load12(g + d * n, (long)s * 12, y, Vhp, m);
+        transport(links, d, i, Vhp, m, t);
+#pragma unroll
+        for (int k = 0; k < 12; ++k) {
+            acc[k].x += t[k].x;
+            acc[k].y += t[k].y;
+        }
+    }
+    for (int k = 0; k < 5; ++k) {
+        const int ss = s + k - 2;
+        if (ss < 0 || ss >= Ls) continue;
+        float2 v[12];
+        load12(r, (long)ss * 12, i, Vhp, v);
+#pragma unroll
+        for (int lo = 112; lo >= 0; lo -= 112) {
+            spin_apply(al + lo + k * 16, v, acc);
+            if (k == 2 && s + 1 < Ls) spin_apply(al + lo + 5 * 16, v, acc);
+            if (k == 2 && s > 0) spin_apply(al + lo + 6 * 16, v, acc);
+        }
+    }
+    store12(out, (long)s * 12, i, Vhp, acc);
+}
+
+// Correlations C[a][b] = sum_{site, s, colour} u_a conj(t_b), a, b = 0..31 = 4 x
+// slot + spin, of one parity's sites:
+//   links (LOCAL 0, odd sites): u slot d = T_d g, t slot d = T_d r;
+//   local (LOCAL 1, even sites): t slots 0..4 = r(s + slot - 2), u slots 0..2 =
+//   g everywhere, where slice s + 1 exists, where s - 1 exists; others zero.
+// A block forms both sides for 32 sites of one slice (a thread per site and
+// slot; a link serves both), passes them through LDS, and its four waves
+// multiply a quarter of the 96 (site, colour) terms each on
+// v_mfma_f32_32x32x2.  Sums of 24 terms are kept in FP32, everything beyond
+// in FP64 (a fixed order: the same bits on every run).  16^4, Ls = 8: 107 and
+// 83 us, against 2.5 ms for the weight gradients of 8 channels path by path.  The LDS row stride of
+// 33 puts the 32 sites of a write on different banks.
+template <int LOCAL>
+__global__ __launch_bounds__(256) void ptc_corr_kernel(const float2* __restrict__ r, const float2* __restrict__ g,
+                                                       const float2* __restrict__ links, const int* __restrict__ nbr,
+                                                       long Vh, long Vhp, int Ls, long ntiles,
+                                                       double* __restrict__ partial) {
+    constexpr int NK = 96, ST = 33;
+    __shared__ double smem[4 * NK * ST / 2];
+    float* ur = reinterpret_cast<float*>(smem);
+    float *ui = ur + NK * ST, *tr = ui + NK * ST, *ti = tr + NK * ST;
+    const int j = threadIdx.x & 31, slot = threadIdx.x >> 5;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    double cr[16], ci[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) { cr[k] = 0.0; ci[k] = 0.0; }
+    for (long tl = blockIdx.x; tl < ntiles; tl += gridDim.x) {
+        const int s = (int)(tl % Ls);
+        const long site = tl / Ls * 32 + j;
+        float2 t[12], u[12];
+#pragma unroll
+        for (int k = 0; k < 12; ++k) {
+            t[k] = make_float2(0.f, 0.f);
+            u[k] = make_float2(0.f, 0.f);
+        }
+        if (site < Vh) {
+            if constexpr (LOCAL) {
+                const int ss = s + slot - 2;
+                if (slot < 5 && ss >= 0 && ss < Ls) load12(r, (long)ss * 12, site, Vhp, t);
+                if (slot == 0 || (slot == 1 && s + 1 < Ls) || (slot == 2 && s > 0)) load12(g, (long)s * 12, site, Vhp, u);
+            } else {
+                const long y = nbr[(long)slot * Vhp + site];
+                float2 v[12], v2[12];
+                load12(r, (long)s * 12, y, Vhp, v);
+                load12(g, (long)s * 12, y, Vhp, v2);
+                transport(links, slot, site, Vhp, v, t);
+                transport(links, slot, site, Vhp, v2, u);
+            }
+        }
+        __syncthreads();   // the previous tile's reads
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int at = (j * 3 + c) * ST + slot * 4 + i;
+                ur[at] = u[i * 3 + c].x;
+                ui[at] = u[i * 3 + c].y;
+                tr[at] = t[i * 3 + c].x;
+                ti[at] = t[i * 3 + c].y;
+            }
+        __syncthreads();
+        v16f ar, ai;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) { ar[k] = 0.f; ai[k] = 0.f; }
+#pragma unroll
+        for (int m = 0; m < NK / 8; ++m) {
+            const int at = (2 * (w * (NK / 8) + m) + (lane >> 5)) * ST + (lane & 31);
+            const float xr = ur[at], xi = ui[at], yr = tr[at], yi = ti[at];
+            ar = __builtin_amdgcn_mfma_f32_32x32x2f32(xr, yr, ar, 0, 0, 0);
+            ai = __builtin_amdgcn_mfma_f32_32x32x2f32(xi, yr, ai, 0, 0, 0);
+            ar = __builtin_amdgcn_mfma_f32_32x32x2f32(xi, yi, ar, 0, 0, 0);
+            ai = __builtin_amdgcn_mfma_f32_32x32x2f32(-xr, yi, ai, 0, 0, 0);
+        }
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
-            float x = acc[a][k].x, y = acc[a][k].y;
+            cr[k] += (double)ar[k];
+            ci[k] += (double)ai[k];
+        }
+    }
+    // the four waves in turn; accumulator slot k of a lane: row 8 (k / 4) + 4 (lane / 32) + k % 4, column lane % 32
+    double* red = smem;   // [re, im][32][32]
+    for (int ww = 0; ww < 4; ++ww) {
+        __syncthreads();
+        if (w == ww) {
 #pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) {
-                x += __shfl_xor(x, off, 64);
-                y += __shfl_xor(y, off, 64);
-            }
-            if (lane == 0) {
-                red[w][(a * 16 + k) * 2] = x;
-                red[w][(a * 16 + k) * 2 + 1] = y;
+            for (int k = 0; k < 16; ++k) {
+                const int at = (8 * (k / 4) + 4 * (lane >> 5) + k % 4) * 32 + (lane & 31);
+                red[at] = (ww ? red[at] : 0.0) + cr[k];
+                red[1024 + at] = (ww ? red[1024 + at] : 0.0) + ci[k];
             }
         }
+    }
     __syncthreads();
-    if (threadIdx.x < AC * 32) {
-        float sum = 0.f;
-        for (int ww = 0; ww < PT / 64; ++ww) sum += red[ww][threadIdx.x];
-        partial[((long)row * gridDim.x + blockIdx.x) * (AC * 32) + threadIdx.x] = sum;
+    for (int e = threadIdx.x; e < 2048; e += 256) partial[(long)blockIdx.x * 2048 + e] = red[e];
+}
+
+// c[set][e] = sum over blocks, e < 2048; eight threads per value, fixed order
+__global__ __launch_bounds__(256) void ptc_corr_finalize(const double* __restrict__ partial, int nblocks,
+                                                         double* __restrict__ c) {
+    __shared__ double red[8][32];
+    const int e = threadIdx.x & 31, part = threadIdx.x >> 5;
+    const double* p = partial + (long)blockIdx.y * nblocks * 2048 + blockIdx.x * 32 + e;
+    double a = 0.0;
+#pragma unroll 4
+    for (int b = part; b < nblocks; b += 8) a += p[(long)b * 2048];
+    red[part][e] = a;
+    __syncthreads();
+    if (part == 0) {
+        for (int k = 1; k < 8; ++k) a += red[k][e];
+        c[(long)blockIdx.y * 2048 + blockIdx.x * 32 + e] = a;
     }
 }
 
-// grad[(q, a0 + a, b)] += sum over blocks (FP64), one block per row
-template <int AC>
-__global__ __launch_bounds__(PT) void ptc_wgrad_finalize(const float* __restrict__ partial, int nblocks,
-                                                         const int* __restrict__ rows, int A, int B,
-                                                         float2* __restrict__ grad) {
-    const int row = blockIdx.x;
-    const int q = rows[3 * row], b = rows[3 * row + 1], a0 = rows[3 * row + 2];
-    if (threadIdx.x >= AC * 32) return;
-    double sum = 0.0;
-    for (int k = 0; k < nblocks; ++k) sum += partial[((long)row * nblocks + k) * (AC * 32) + threadIdx.x];
-    const int v = threadIdx.x >> 1, a = v / 16, e = v % 16;
-    float* gp = reinterpret_cast<float*>(grad + (((long)q * A + a0 + a) * B + b) * 16 + e) + (threadIdx.x & 1);
-    *gp += (float)sum;
+// dL/dE_{qq'}[i][j] from the correlations (set 0: links, set 1: local)
+__device__ __forceinline__ double2 pair_grad(const double* c, int q, int p, int i, int j) {
+    int set, a, b;
+    if (q >= 1 && q <= 8) {
+        // g meets T_d at the far end: T_d^dag = T of the reversed direction
+        set = 0;
+        a = (q - 1) ^ 4;
+        b = p - 1;
+    } else {
+        set = 1;
+        const int dq = q == 0 ? 0 : (q == 9 ? 1 : -1), dp = p == 0 ? 0 : (p == 9 ? 1 : -1);
+        a = dq * dp == -1 ? (q == 9 ? 1 : 2) : 0;
+        b = dq + dp + 2;
+    }
+    const long at = (long)set * 2048 + (a * 4 + i) * 32 + b * 4 + j;
+    return make_double2(c[at], c[at + 1024]);
+}
+
+// weight gradients of both layers (products of 4x4 matrices, FP64)
+__global__ __launch_bounds__(PT) void ptc_weight_grad(const double* __restrict__ c, const float2* __restrict__ W1,
+                                                      const float2* __restrict__ W2, int H, float2* __restrict__ G1,
+                                                      float2* __restrict__ G2) {
+    const int t = blockIdx.x * PT + threadIdx.x;
+    if (t >= 2 * 11 * H * 16) return;
+    const int layer = t / (11 * H * 16), w = t % (11 * H * 16);
+    const int j = w & 3, i = (w >> 2) & 3, b = (w >> 4) % H, q = (w >> 4) / H;
+    const bool link = q >= 1 && q <= 8;
+    double re = 0.0, im = 0.0;
+    for (int m = 0; m < (link ? 8 : 3); ++m) {
+        const int p = link ? 1 + m : (m == 0 ? 0 : 8 + m);
+        for (int k = 0; k < 4; ++k) {
+            // layer 2: dE_{qp}[i][k] conj(W1_p[j][k]); layer 1: conj(W2_p[k][i]) dE_{pq}[k][j]
+            const double2 e = layer ? pair_grad(c, q, p, i, k) : pair_grad(c, p, q, k, j);
+            const float2 x = layer ? W1[((long)p * H + b) * 16 + j * 4 + k] : W2[((long)p * H + b) * 16 + k * 4 + i];
+            re += e.x * x.x + e.y * x.y;
+            im += e.y * x.x - e.x * x.y;
+        }
+    }
+    (layer ? G2 : G1)[w] = make_float2((float)re, (float)im);
 }
 
 // partial sums of |y - e|^2 and |e|^2 (FP64) over one half field
@@ -332,10 +514,19 @@ __global__ __launch_bounds__(PT) void ptc_loss_partial(const float2* y, const fl
 }
 
 // out[0] = |y-e|^2 / |e|^2 (loss), out[1] = |e|^2, out[2] = |y-e|^2
-__global__ void ptc_loss_finalize(const double* partial, int nparts, double* out) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+__global__ __launch_bounds__(PT) void ptc_loss_finalize(const double* partial, int nparts, double* out) {
+    __shared__ double red[2][PT / 64];
     double a = 0, b = 0;
-    for (int k = 0; k < nparts; ++k) { a += partial[2 * k]; b += partial[2 * k + 1]; }
+    for (int k = threadIdx.x; k < nparts; k += PT) { a += partial[2 * k]; b += partial[2 * k + 1]; }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        a += __shfl_xor(a, off, 64);
+        b += __shfl_xor(b, off, 64);
+    }
+    if ((threadIdx.x & 63) == 0) { red[0][threadIdx.x >> 6] = a; red[1][threadIdx.x >> 6] = b; }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int k = 1; k < PT / 64; ++k) { a += red[0][k]; b += red[1][k]; }
     out[0] = b > 0 ? a / b : 0.0;
     out[1] = b;
     out[2] = a;
@@ -408,57 +599,41 @@ __global__ __launch_bounds__(PT) void ptc_adam_kernel(float* w, const float* g, 
     w[k] -= lr * (mk / bc1) / (sqrtf(vk / bc2) + eps);
 }
 
-// Wt[rev(q)][b][a] = W[q][a][b]^dag (weights of the adjoint layer)
-__global__ __launch_bounds__(PT) void ptc_adjoint_weights(const float2* W, float2* Wt, int A, int B) {
-    const int k = blockIdx.x * PT + threadIdx.x;
-    if (k >= 11 * A * B * 16) return;
-    const int e = k % 16, rest = k / 16;
-    const int b = rest % B, a = (rest / B) % A, q = rest / (A * B);
-    const int i = e / 4, j = e % 4;
-    const int rq = q == 0 ? 0 : (q <= 4 ? q + 4 : (q <= 8 ? q - 4 : 19 - q));
-    const float2 w = W[(((long)q * A + a) * B + b) * 16 + i * 4 + j];
-    Wt[(((long)rq * B + b) * A + a) * 16 + j * 4 + i] = make_float2(w.x, -w.y);
-}
-
 // ---------------------------------------------------------------------
 void ptc_layer(const PtcLayerParams& P, hipStream_t st) {
-    DWF_REQUIRE(P.A >= 1 && P.B >= 1 && P.Ls >= 1 && P.Vh >= 1, DWF_EINVAL, "bad PTC layer shape");
-    const int ac = P.A % 4 == 0 ? 4 : (P.A % 2 == 0 ? 2 : 1);
-    dim3 grid((unsigned)((P.Vh + PT - 1) / PT), (unsigned)P.Ls, (unsigned)(P.A / ac));
-    const bool commute = DWF_PTC_COMMUTE && P.B > ac;   // fewer transports when the channels are combined first
-    if (ac == 4) {
-        if (commute) hipLaunchKernelGGL((ptc_layer_kernel<4, true>), grid, dim3(PT), 0, st, P);
-        else hipLaunchKernelGGL((ptc_layer_kernel<4, false>), grid, dim3(PT), 0, st, P);
-    } else if (ac == 2) {
-        if (commute) hipLaunchKernelGGL((ptc_layer_kernel<2, true>), grid, dim3(PT), 0, st, P);
-        else hipLaunchKernelGGL((ptc_layer_kernel<2, false>), grid, dim3(PT), 0, st, P);
-    } else {
-        if (commute) hipLaunchKernelGGL((ptc_layer_kernel<1, true>), grid, dim3(PT), 0, st, P);
-        else hipLaunchKernelGGL((ptc_layer_kernel<1, false>), grid, dim3(PT), 0, st, P);
-    }
+    DWF_REQUIRE(P.Ls >= 1 && P.Vh >= 1, DWF_EINVAL, "bad PTC layer shape");
+    hipLaunchKernelGGL(ptc_layer_kernel, dim3((unsigned)((P.Vh + PT - 1) / PT), (unsigned)P.Ls), dim3(PT), 0, st, P);
     DWF_HIP(hipGetLastError());
 }
 
-int ptc_wgrad_blocks(const PtcLayerParams& P) { return (int)((P.Vh * P.Ls + PT - 1) / PT); }
-
-void ptc_wgrad(const PtcLayerParams& P, const float2* g, const int* rows_dev, int nrows, float* partial,
-               float2* grad, hipStream_t st) {
-    if (nrows == 0) return;
-    const int nb = ptc_wgrad_blocks(P);
-    const int ac = P.A % 2 == 0 ? 2 : 1;
-    if (ac == 2) {
-        hipLaunchKernelGGL(ptc_wgrad_kernel<2>, dim3(nb, nrows), dim3(PT), 0, st, P, g, rows_dev, partial);
-        hipLaunchKernelGGL(ptc_wgrad_finalize<2>, dim3(nrows), dim3(PT), 0, st, partial, nb, rows_dev, P.A, P.B,
-                           grad);
-    } else {
-        hipLaunchKernelGGL(ptc_wgrad_kernel<1>, dim3(nb, nrows), dim3(PT), 0, st, P, g, rows_dev, partial);
-        hipLaunchKernelGGL(ptc_wgrad_finalize<1>, dim3(nrows), dim3(PT), 0, st, partial, nb, rows_dev, P.A, P.B,
-                           grad);
-    }
+void ptc_pairs_forward(const PtcPairParams& P, const float2* r, float2* out, hipStream_t st) {
+    DWF_REQUIRE(P.Ls >= 1 && P.Vh >= 1 && P.H >= 1, DWF_EINVAL, "bad PTC shape");
+    hipLaunchKernelGGL(ptc_pair_weights, dim3((1024 + 7 * 16 + PT - 1) / PT), dim3(PT), 0, st, P.W1, P.W2, P.H, P.el,
+                       P.al);
+    hipLaunchKernelGGL(ptc_mid_kernel, dim3((unsigned)((P.Vh + 31) / 32)), dim3(64 * (P.Ls < 4 ? P.Ls : 4)), 0, st, r,
+                       P.mid, P.links[1], P.nbr[1], P.el, P.Vh, P.Vhp, P.Ls);
+    hipLaunchKernelGGL(ptc_out_kernel, dim3((unsigned)((P.Vh + 63) / 64), (unsigned)((P.Ls + 3) / 4)), dim3(256), 0, st,
+                       r, P.mid, out, P.links[0], P.nbr[0], P.al, P.Vh, P.Vhp, P.Ls);
     DWF_HIP(hipGetLastError());
 }
 
-int ptc_wgrad_ac(int A) { return A % 2 == 0 ? 2 : 1; }
+static long corr_tiles(const PtcPairParams& P) { return (P.Vh + 31) / 32 * P.Ls; }
+static int corr_blocks(const PtcPairParams& P) { return (int)std::min<long>(corr_tiles(P), 768); }
+size_t ptc_corr_bytes(const PtcPairParams& P) { return ((size_t)2 * corr_blocks(P) + 2) * 2048 * sizeof(double); }
+
+void ptc_pairs_gradient(const PtcPairParams& P, const float2* r, const float2* g, double* corr, float2* G1,
+                        float2* G2, hipStream_t st) {
+    const int nb = corr_blocks(P);
+    double* c = corr + (size_t)2 * nb * 2048;
+    hipLaunchKernelGGL(ptc_corr_kernel<0>, dim3(nb), dim3(256), 0, st, r, g, P.links[1], P.nbr[1], P.Vh, P.Vhp, P.Ls,
+                       corr_tiles(P), corr);
+    hipLaunchKernelGGL(ptc_corr_kernel<1>, dim3(nb), dim3(256), 0, st, r, g, P.links[0], P.nbr[0], P.Vh, P.Vhp, P.Ls,
+                       corr_tiles(P), corr + (size_t)nb * 2048);
+    hipLaunchKernelGGL(ptc_corr_finalize, dim3(64, 2), dim3(256), 0, st, corr, nb, c);
+    hipLaunchKernelGGL(ptc_weight_grad, dim3((2 * 11 * P.H * 16 + PT - 1) / PT), dim3(PT), 0, st, c, P.W1, P.W2, P.H, G1,
+                       G2);
+    DWF_HIP(hipGetLastError());
+}
 
 int ptc_loss_blocks(long n) {
     long b = (n + PT - 1) / PT;
@@ -468,7 +643,7 @@ int ptc_loss_blocks(long n) {
 void ptc_loss(const float2* y, const float2* e, long n, double* partial, double* stats, float2* g, hipStream_t st) {
     const int nb = ptc_loss_blocks(n);
     hipLaunchKernelGGL(ptc_loss_partial, dim3(nb), dim3(PT), 0, st, y, e, n, partial);
-    hipLaunchKernelGGL(ptc_loss_finalize, dim3(1), dim3(64), 0, st, partial, nb, stats);
+    hipLaunchKernelGGL(ptc_loss_finalize, dim3(1), dim3(PT), 0, st, partial, nb, stats);
     if (g) hipLaunchKernelGGL(ptc_loss_grad, dim3(nb), dim3(PT), 0, st, y, e, n, stats, g);
     DWF_HIP(hipGetLastError());
 }
@@ -481,7 +656,7 @@ void ptc_sub(const float2* y, const float2* e, long n, float2* d, hipStream_t st
 void ptc_norms(const float2* u, const float2* r, long n, double* partial, double* stats, hipStream_t st) {
     const int nb = ptc_loss_blocks(n);
     hipLaunchKernelGGL(ptc_norms_partial, dim3(nb), dim3(PT), 0, st, u, r, n, partial);
-    hipLaunchKernelGGL(ptc_loss_finalize, dim3(1), dim3(64), 0, st, partial, nb, stats);
+    hipLaunchKernelGGL(ptc_loss_finalize, dim3(1), dim3(PT), 0, st, partial, nb, stats);
     DWF_HIP(hipGetLastError());
 }
 
@@ -495,12 +670,6 @@ void ptc_adam(float* w, const float* g, float* m, float* v, int n, float lr, flo
     const float bc1 = 1.f - std::pow(b1, (float)step), bc2 = 1.f - std::pow(b2, (float)step);
     hipLaunchKernelGGL(ptc_adam_kernel, dim3((n + PT - 1) / PT), dim3(PT), 0, st, w, g, m, v, n, lr, b1, b2, eps, bc1,
                        bc2);
-    DWF_HIP(hipGetLastError());
-}
-
-void ptc_adjoint(const float2* W, float2* Wt, int A, int B, hipStream_t st) {
-    const int n = 11 * A * B * 16;
-    hipLaunchKernelGGL(ptc_adjoint_weights, dim3((n + PT - 1) / PT), dim3(PT), 0, st, W, Wt, A, B);
     DWF_HIP(hipGetLastError());
 }
 

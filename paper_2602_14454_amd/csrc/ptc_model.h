@@ -11,15 +11,16 @@ struct dwf_ptc {
     long nw;                 // complex weights: W1 [11][H][1][16] then W2 [11][1][H][16]
     int step = 0;            // Adam steps taken
     int loss_kind = 1;       // 0: |M r - e|^2/|e|^2;  1: |A (M r - e)|^2/|r|^2 = |A M r - r|^2/|r|^2
-    dwf::DevBuf W, G, Wt, m, v, stats, rows;
-    int n2 = 0, n1e = 0, n1o = 0;
+    dwf::DevBuf W, G, m, v, stats, pair_w;
     long cap_n = 0;
-    dwf::DevBuf he, ho, ghe, gho, y, g, lpartial, wpart, d, u, w, to, tv;
+    long lay_n = 0, lay_vhp = 0;   // field layout of the workspace's last use (its zero padding)
+    // hid: the intermediate fields (8 pair sums, or the two parities of one hidden channel)
+    dwf::DevBuf hid, y, g, lpartial, corr, d, u, w, to, tv;
 
     explicit dwf_ptc(int hidden);
     const float2* W1() const;
     const float2* W2() const;
-    void reserve(const dwf_op* op);
+    void reserve(const dwf_op* op, hipStream_t st);
     // out = M r on FP32 internal even half fields (1 channel)
     void forward(const dwf_op* op, const float2* r, float2* out, hipStream_t st);
     // loss in stats[0] (and g = dL/dy unless value_only), dL/dW in G

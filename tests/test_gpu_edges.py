@@ -123,3 +123,47 @@ def test_call_scratch_is_private_and_clean():
     for t in ts:
         t.join()
     assert not bad
+
+
+# sites per parity 8 (a quarter of a 32-site tile), 32, 72 and 1008; every form of the hidden layer
+@pytest.mark.parametrize("dims,Ls,H", [((2, 2, 2, 2), 2, 4), ((4, 4, 2, 2), 5, 1), ((6, 6, 2, 2), 16, 5),
+                                       ((4, 2, 4, 2), 3, 3), ((6, 6, 4, 14), 2, 64)])
+def test_network_tiles(dims, Ls, H):
+    """Network output and weight gradient around the tiles and the number of hidden channels."""
+    import torch
+
+    import paper_2602_14454_amd as dwf
+    from oracle import ptc as optc
+    lat, op, p, U = _make(dims, Ls, alpha=0.5)
+    W1, W2 = (w.astype(np.complex64).astype(np.complex128) for w in optc.random_weights(H, 5))
+    M = dwf.PtcModel(H)
+    M.set_weights(W1, W2)
+    M.set_loss(0)
+    r, e = (dwfgen.gaussian_source_5d(dims, Ls, k)[:, : p.Vh].astype(np.complex64).astype(np.complex128) for k in (6, 7))
+    out = torch.full(r.shape, float("nan"), dtype=torch.complex128, device="cuda")
+    M.apply(op, out, _dev(r))
+    assert _rel(out.cpu().numpy(), optc.forward(U, dims, W1, W2, r)[0]) < 2e-5
+    loss, grads = M.gradient(op, _dev(r), _dev(e))
+    L, *want = optc.gradients(U, dims, W1, W2, r, e, kind=0)
+    assert abs(loss - L) < 3e-5 * L
+    for g, o in zip(grads, want):
+        assert np.linalg.norm(g - o) < 3e-5 * np.linalg.norm(o)
+
+
+@pytest.mark.parametrize("kind", [0, 1])
+def test_network_on_two_lattices(kind):
+    """One model on a large and then a smaller lattice gives what a new model gives on the small one."""
+    import paper_2602_14454_amd as dwf
+    from oracle import ptc as optc
+    big, small = _make((6, 6, 4, 14), 4)[:2], _make((6, 2, 2, 6), 3)[:2]
+    W = optc.random_weights(4, 5)
+    got = []
+    for ops in ((big, small), (small,)):
+        M = dwf.PtcModel(4)
+        M.set_weights(*W)
+        M.set_loss(kind)
+        for lat, op in ops:
+            r, e = (_dev(np.ascontiguousarray(dwfgen.gaussian_source_5d(lat.dims, op.Ls, k)[:, : lat.Vh])) for k in (6, 7))
+            loss, (g1, g2) = M.gradient(op, r, e)
+        got.append((loss, g1, g2))
+    assert got[0][0] == got[1][0] and np.array_equal(got[0][1], got[1][1]) and np.array_equal(got[0][2], got[1][2])

@@ -1,4 +1,5 @@
-// Launch interface of the fused hop and local-mix kernels (hop.hip).
+// Launch interface of the fused hop and local-mix kernels (hop_tile.h; hop.hip,
+// hop_few.hip, hop_batch.hip).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -59,6 +60,9 @@ int hop_grid_blocks(long Vh);
 // blocks of a mix launch per right-hand side (partials it writes, with partial set)
 int mix_grid_blocks(long Vh);
 void launch_hop(int kind, const HopParams& P, int nrhs, hipStream_t st, int bench_tag = 0);
+// FP64 hop on a lattice so small that the form for few blocks applies (false:
+// not launched); ek: hop_epilogue_kind of P.
+bool launch_hop_few(const HopParams& P, int nrhs, int ek, hipStream_t st);
 // One work-list launch over `nitems` HopParams (device array `items`, same
 // ceil(Ls/4) = KK for all) with block prefix sums and RHS counts in `meta`
 // (device, 2 * nitems + 1 ints); `blocks` = meta[nitems].  has_loc: the

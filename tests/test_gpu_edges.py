@@ -167,3 +167,36 @@ def test_network_on_two_lattices(kind):
             loss, (g1, g2) = M.gradient(op, r, e)
         got.append((loss, g1, g2))
     assert got[0][0] == got[1][0] and np.array_equal(got[0][1], got[1][1]) and np.array_equal(got[0][2], got[1][2])
+
+
+# FP64 launches of 768 waves take the form for few blocks, of 784 and 896 the general one; Ls with a remainder
+@pytest.mark.parametrize("dims,Ls", [((8, 8, 8, 12), 16), ((8, 8, 8, 14), 14), ((4, 14, 14, 8), 13), ((8, 8, 4, 6), 2)])
+@pytest.mark.parametrize("b,c", [(1.0, 0.0), (1.5, 0.5)])
+def test_hop_forms_by_lattice_size(dims, Ls, b, c):
+    """Every kind of hop launch (plain, local term dense or not, two outputs, residual update) on both sides of
+    the size rule, in FP64, and the specialised epilogues in FP32."""
+    import torch
+
+    import paper_2602_14454_amd as dwf
+    lat, op, p, U = _make(dims, Ls, b=b, c=c)
+    x = dwfgen.gaussian_source_5d(dims, Ls, 9)
+    out = torch.empty(x.shape, dtype=torch.complex128, device="cuda")
+    xe = np.ascontiguousarray(x[:, : p.Vh])
+    oe = torch.empty(xe.shape, dtype=torch.complex128, device="cuda")
+    q = oracle.dhat(p, U, xe)
+    normal = oracle.dhat(p, U, q, dagger=True)
+    for prec in (0, 1):
+        for dagger in (False, True):
+            op.apply(out, _dev(x), dwf.FULL5D, dagger, prec)
+            assert _rel(out.cpu().numpy(), oracle.dwf_apply(p, U, x, dagger=dagger)) < TOL[prec]
+        op.apply(oe, _dev(xe), dwf.EVEN5D, True, prec)
+        assert _rel(oe.cpu().numpy(), oracle.dhat(p, U, xe, dagger=True)) < TOL[prec]
+        op.apply_normal(oe, _dev(xe), prec)
+        assert _rel(oe.cpu().numpy(), normal) < TOL[prec]
+        r = _dev(np.ascontiguousarray(x[:, p.Vh:]))
+        r0 = r.cpu().numpy()
+        alpha, rr = op.cg_residual_update(r, _dev(xe), prec)
+        want_a = np.linalg.norm(r0) ** 2 / np.linalg.norm(q) ** 2
+        want = r0 - want_a * normal
+        assert abs(alpha / want_a - 1) < TOL[prec]
+        assert _rel(r.cpu().numpy(), want) < TOL[prec] and abs(rr / np.linalg.norm(want) ** 2 - 1) < TOL[prec]

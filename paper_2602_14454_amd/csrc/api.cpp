@@ -652,10 +652,7 @@ int dwf_gauge_sweeps(const int dims[4], void* U, double beta, int nsweeps, int n
         const double V = (double)dims[0] * dims[1] * dims[2] * dims[3];
         DWF_REQUIRE(V * 4.0 * 3.0 * 4096.0 < 1.8e19, DWF_EDIMS, "lattice too large for the random-number counters");
         hipStream_t st = S(stream);
-        for (int k = 0; k < nsweeps; ++k) {
-            gauge_sweep(U, dims, beta, seed, sweep0 + k, true, st);
-            for (int o = 0; o < n_or; ++o) gauge_sweep(U, dims, beta, seed, sweep0 + k, false, st);
-        }
+        gauge_sweeps(U, dims, beta, nsweeps, n_or, seed, sweep0, st);
         DWF_HIP(hipStreamSynchronize(st));
         return DWF_OK;
     });
@@ -669,8 +666,10 @@ int dwf_gauge_plaquette(const int dims[4], const void* U, double* plaq, void* st
         DevBuf partial((size_t)(gauge_plaquette_partials(dims) + 1) * sizeof(double));
         double* out = partial.as<double>() + gauge_plaquette_partials(dims);
         gauge_plaquette(U, dims, partial.as<double>(), out, st);
-        DWF_HIP(hipMemcpyAsync(plaq, out, sizeof(double), hipMemcpyDeviceToHost, st));
+        double sum = 0.0;
+        DWF_HIP(hipMemcpyAsync(&sum, out, sizeof(double), hipMemcpyDeviceToHost, st));
         DWF_HIP(hipStreamSynchronize(st));
+        *plaq = sum * (1.0 / (18.0 * (double)dims[0] * dims[1] * dims[2] * dims[3]));
         return DWF_OK;
     });
 }

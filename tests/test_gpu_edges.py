@@ -200,3 +200,24 @@ def test_hop_forms_by_lattice_size(dims, Ls, b, c):
         want = r0 - want_a * normal
         assert abs(alpha / want_a - 1) < TOL[prec]
         assert _rel(r.cpu().numpy(), want) < TOL[prec] and abs(rr / np.linalg.norm(want) ** 2 - 1) < TOL[prec]
+
+
+# 8, 24, 80 and 144 site pairs: part of a 32-pair tile, remainders of several; extents of 2 and 10
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (2, 6, 2, 2), (10, 2, 2, 4), (6, 2, 6, 4)])
+def test_gauge_tiles(dims):
+    """A heatbath and an over-relaxation sweep around the tiles of the working layout; tolerance of the
+    single sweep in test_gpu_gauge.py, ten times for the second."""
+    import paper_2602_14454_amd as dwf
+    from oracle import gauge as G
+    U0 = dwfgen.random_su3_links(dims, 0.5, 5)
+    for n_or, tol in ((0, 1e-11), (1, 1e-10)):
+        Ud = _dev(U0)
+        dwf.gauge_sweeps(Ud, dims, 6.0, nsweeps=1, n_or=n_or, seed=77, sweep0=3)
+        Uo = U0.copy()
+        G.sweep(Uo, dims, 6.0, 77, 3, heatbath=True)
+        for _ in range(n_or):
+            G.sweep(Uo, dims, 6.0, 77, 3, heatbath=False)
+        assert np.abs(Ud.cpu().numpy() - Uo).max() < tol
+    Ud = _dev(U0)
+    dwf.gauge_sweeps(Ud, dims, 6.0, nsweeps=0, n_or=2)
+    assert np.array_equal(Ud.cpu().numpy(), U0)

@@ -16,6 +16,12 @@ void pack_full(int kind, void* dst_e, void* dst_o, const void* src, const int* l
                long nslices, hipStream_t st);
 void unpack_full(int kind, void* dst, const void* src_e, const void* src_o, const int* lex, long Vh, long Vhp,
                  long V, long nslices, hipStream_t st);
+// half fields of the split by 5D parity (row stride Vh; eo5d.h), kind F64 or F32; a null
+// field is not packed, and unpacks as zeros
+void pack_eo5(int kind, void* dst_e, void* dst_o, const void* src, const int* lex, long Vh, long V, int Ls,
+              hipStream_t st);
+void unpack_eo5(int kind, void* dst, const void* src_e, const void* src_o, const int* lex, long Vh, long V, int Ls,
+                hipStream_t st);
 void pack_half(int kind, void* dst, const void* src, const int* lex, long Vh, long Vhp, long nslices,
                hipStream_t st);
 void unpack_half(int kind, void* dst, const void* src, const int* lex, long Vh, long Vhp, long nslices,

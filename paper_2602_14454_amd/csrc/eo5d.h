@@ -12,9 +12,9 @@
 // eq. even-odd_linear_equation needs no dense fifth-dimension algebra.
 //
 // Half fields of 5D parity P: slice s holds the 4D sites of parity
-// (P + s) mod 2 in the lattice's internal site order, component-major
-// [s][spin * 3 + colour][site] (Vh sites per row, consecutive lanes read
-// consecutive sites).  The 4D neighbours of such a site at
+// (P + s) mod 2 in the lattice's internal site order, in the component groups
+// of the 4D half fields (precision.h) with row stride Vh (pack_eo5, unpack_eo5
+// in blas.h).  The 4D neighbours of such a site at
 // slice s, and the same site at slices s -/+ 1, are then entries of the
 // opposite half field at the indices of the 4D tables.
 #pragma once
@@ -46,13 +46,6 @@ struct Eo5Params {
 
 // out = a loc + sgn D_{P,P'} in with the scalings of Eo5Params (kind F64 or F32).
 void launch_eo5(int kind, const Eo5Params& P, hipStream_t st);
-// canonical 5D (FP64, [s][lex][12]) <-> FP64 half field of 5D parity par
-void eo5_pack(void* half, const void* full5, const int* lex_of_site, long Vh, long V, int Ls, int par,
-              hipStream_t st);
-void eo5_unpack(void* full5, const void* half, const int* lex_of_site, long Vh, long V, int Ls, int par,
-                hipStream_t st);
-// elementwise FP64 <-> FP32 copy of n complex numbers (kinds ST_F64 / ST_F32)
-void eo5_convert(int kd, int ks, void* dst, const void* src, long n, hipStream_t st);
 // out = M_ss(chirality) in over one FP64 half field (the 5D-diagonal block)
 void eo5_diag(void* out, const void* in, const double* coef, long Vh, int Ls, hipStream_t st);
 

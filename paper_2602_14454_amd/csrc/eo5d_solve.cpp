@@ -166,15 +166,11 @@ void apply_eo5_schur(const dwf_op* op, int kind, int dagger, void* out5, const v
     eo5_coefficients(op, hc);
     SmallScratch coef(op, sizeof hc);
     DWF_HIP(hipMemcpyAsync(coef.p, hc, sizeof hc, hipMemcpyHostToDevice, st));
-    const long n = (long)op->Ls * L->Vh * 12;
     const int* lex = L->lex_of_site_dev.as<int>();
-    Eo5Scratch e64(op, ST_F64), ek(op, kind), ok(op, kind), tk(op, kind);
-    eo5_pack(e64.p, in5, lex, L->Vh, L->V, op->Ls, 0, st);
-    eo5_convert(kind, ST_F64, ek.p, e64.p, n, st);
+    Eo5Scratch ek(op, kind), ok(op, kind), tk(op, kind);
+    pack_eo5(kind, ek.p, nullptr, in5, lex, L->Vh, L->V, op->Ls, st);
     eo5_dhat(op, kind, dagger, ok.p, ek.p, tk.p, coef.as<double>(), st);
-    eo5_convert(ST_F64, kind, e64.p, ok.p, n, st);
-    DWF_HIP(hipMemsetAsync(out5, 0, (size_t)op->Ls * L->V * 12 * 16, st));
-    eo5_unpack(out5, e64.p, lex, L->Vh, L->V, op->Ls, 0, st);
+    unpack_eo5(kind, out5, ok.p, nullptr, lex, L->Vh, L->V, op->Ls, st);
     DWF_HIP(hipStreamSynchronize(st));
 }
 
@@ -213,8 +209,7 @@ int solve_eo5(const dwf_op* op, void* x5, const void* b5, const dwf_solve_params
     DWF_HIP(hipEventCreate(&e1));
     DWF_HIP(hipEventRecord(e0, st));
     const int* lex = L->lex_of_site_dev.as<int>();
-    eo5_pack(be.p, b5, lex, Vh, V, Ls, 0, st);
-    eo5_pack(bo.p, b5, lex, Vh, V, Ls, 1, st);
+    pack_eo5(ST_F64, be.p, bo.p, b5, lex, Vh, V, Ls, st);
     const double b2 = norm2_of(ST_F64, be.p, n, pp, sc, hs, st) + norm2_of(ST_F64, bo.p, n, pp, sc, hs, st);
     // b~_e = D_ee^-1 b_e - D_ee^-1 D_eo D_oo^-1 b_o
     piece(op, ST_F64, 0, 0, 1, 1, 1, 1.0, -1.0, bt.p, bo.p, be.p, cf, st);
@@ -236,7 +231,7 @@ int solve_eo5(const dwf_op* op, void* x5, const void* b5, const dwf_solve_params
     }
     while (!converged && total < maxiter && outer < 100) {
         Eo5Cg& W = cg_of(kp);
-        eo5_convert(kp, ST_F64, W.rin.p, rh.p, n, st);
+        convert(kp, ST_F64, W.rin.p, rh.p, n, st, Vh);
         const bool plain = prm->paper_mode || (kp == ST_F64 && outer == 0);
         const double itol = plain ? inner_tol : dc_target(tol, rel5, kp, inner_tol, f_ratio);
         const int it = cgnr5(op, W, cf, itol, maxiter - total, prm->check_every, pp, sc, hs, st, &last_inner_rel,
@@ -244,7 +239,7 @@ int solve_eo5(const dwf_op* op, void* x5, const void* b5, const dwf_solve_params
         total += it;
         ++outer;
         if (nan_seen) break;
-        eo5_convert(ST_F64, kp, te.p, W.x.p, n, st);
+        convert(ST_F64, kp, te.p, W.x.p, n, st, Vh);
         axpby(ST_F64, ST_F64, xe.p, te.p, n, nullptr, 1.0, nullptr, 1.0, nullptr, st);
         // r^ = b~ - D^5 x_e (FP64); the 5D residual is (D_ee r^, 0) after reconstruction
         eo5_dhat(op, ST_F64, 0, te.p, xe.p, to.p, cf, st);
@@ -270,8 +265,7 @@ int solve_eo5(const dwf_op* op, void* x5, const void* b5, const dwf_solve_params
     }
     // x_o = D_oo^-1 b_o - D_oo^-1 D_oe x_e
     piece(op, ST_F64, 1, 0, 0, 1, 1, 1.0, -1.0, xo.p, xe.p, bo.p, cf, st);
-    eo5_unpack(x5, xe.p, lex, Vh, V, Ls, 0, st);
-    eo5_unpack(x5, xo.p, lex, Vh, V, Ls, 1, st);
+    unpack_eo5(ST_F64, x5, xe.p, xo.p, lex, Vh, V, Ls, st);
     DWF_HIP(hipEventRecord(e1, st));
     DWF_HIP(hipEventSynchronize(e1));
     float ms = 0;

@@ -221,3 +221,21 @@ def test_gauge_tiles(dims):
     Ud = _dev(U0)
     dwf.gauge_sweeps(Ud, dims, 6.0, nsweeps=0, n_or=2)
     assert np.array_equal(Ud.cpu().numpy(), U0)
+
+
+# sites per parity 8 (part of a 64-site tile), 72 (remainder), 1008 (two tiles per XCD); slices of one parity 1 to 8
+@pytest.mark.parametrize("dims,Ls", [((2, 2, 2, 2), 2), ((6, 6, 2, 2), 6), ((6, 6, 4, 14), 10), ((4, 2, 4, 2), 16)])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_eo5_tiles(dims, Ls, prec):
+    """Schur operator of the 5D split around its tiles: even entries against the oracle, odd ones zero."""
+    import torch
+
+    from oracle import eo5
+    lat, op, p, U = _make(dims, Ls, alpha=0.6)
+    x = dwfgen.gaussian_source_5d(dims, Ls, 9)
+    odd = ~eo5.even_mask(p)
+    for dagger in (False, True):
+        out = torch.full(x.shape, float("nan"), dtype=torch.complex128, device="cuda")
+        op.apply_eo5(out, _dev(x), dagger, prec)
+        got = out.cpu().numpy()
+        assert _rel(got, eo5.dhat5(p, U, x, dagger=dagger)) < TOL[prec] and np.all(got[odd] == 0)

@@ -119,7 +119,7 @@ int dwf_lattice_maps(const dwf_lattice* lat, int* lex_of_site, int* nbr) {
             for (int p = 0; p < 2; ++p)
                 for (int d = 0; d < 8; ++d)
                     for (long i = 0; i < lat->Vh; ++i)
-                        nbr[(p * 8 + d) * lat->Vh + i] = lx[(1 - p) * lat->Vh + nb[(p * 8 + d) * lat->Vhp + i]];
+                        nbr[(p * 8 + d) * lat->Vh + i] = lx[(1 - p) * lat->Vh + nb[p * 8 * lat->Vhp + ((i >> 4) * 8 + d) * 16 + (i & 15)]];
         return DWF_OK;
     });
 }
@@ -309,8 +309,8 @@ int dwf_source_4d(const dwf_op* op, void* b5, const void* b4, void* stream) {
         hipStream_t st = S(stream);
         const int* lex = L->lex_of_site_dev.as<int>();
         PairScratch pe(op), po(op), oe(op), oo(op);
-        pack_chiral_pair_f64(pe.p, b4, lex, Vh, Vhp, st);
-        pack_chiral_pair_f64(po.p, b4, lex + Vh, Vh, Vhp, st);
+        pack_chiral_pair_f64(pe.p, b4, lex, Vh, st);
+        pack_chiral_pair_f64(po.p, b4, lex + Vh, Vh, st);
         source_pair(op, oe.p, po.p, pe.p, 0, st);
         source_pair(op, oo.p, pe.p, po.p, 1, st);
         // b5 = 0 except s = 0 (slice 0 of the pair) and s = Ls-1 (slice 1):
@@ -392,8 +392,8 @@ int dwf_bench_hop(const dwf_op* op, int prec, int nrep, double* ms_per_launch, d
             for (int i = 0; i < nsets; ++i) {
                 ins[i].alloc(fb);
                 outs[i].alloc(fb);
-                random_fill_f64(tmp.p, (long)op->Ls * 12, Vh, L->Vhp, 0x5eedULL + (unsigned long long)i, st);
-                convert(k, ST_F64, ins[i].p, tmp.p, n, st, L->Vhp);
+                random_fill_f64(tmp.p, (long)op->Ls * 12, Vh, 0x5eedULL + (unsigned long long)i, st);
+                convert(k, ST_F64, ins[i].p, tmp.p, n, st);
             }
             DWF_HIP(hipStreamSynchronize(st));
         }
@@ -545,8 +545,8 @@ int dwf_ptc_bench_apply(dwf_ptc* m, const dwf_op* op, int nrep, double* ms_per_a
         hipStream_t st = S(stream);
         const long n = ptc_field_elems(op);
         DevBuf a(8 * (size_t)n), b(8 * (size_t)n), t(16 * (size_t)n);
-        random_fill_f64(t.p, (long)op->Ls * 12, L->Vh, L->Vhp, 0x7ee5ULL, st);
-        convert(ST_F32, ST_F64, a.p, t.p, n, st, L->Vhp);
+        random_fill_f64(t.p, (long)op->Ls * 12, L->Vh, 0x7ee5ULL, st);
+        convert(ST_F32, ST_F64, a.p, t.p, n, st);
         m->forward(op, a.as<float2>(), b.as<float2>(), st);   // warm-up (workspace)
         hipEvent_t e0, e1;
         DWF_HIP(hipEventCreate(&e0));

@@ -326,7 +326,6 @@ void make_batch(Batch& B, int n, const dwf_op* const* ops, const int* nrhs) {
             d.nb = slot_blocks(it.n1);
             d.block0 = B.vblocks;
             d.nhop = hop_grid_blocks(op->lat->Vh);
-            d.Vhp = op->lat->Vhp;
             B.vblocks += d.nb;
             pst = std::max<long>(pst, std::max(d.nb, d.nhop));
             B.slots.push_back(d);
@@ -543,9 +542,8 @@ int solve_batch(int n, const dwf_op* const* ops, void* const* x5, const void* co
     for (const Item& it : B.items) {
         const dwf_lattice* L = it.op->lat;
         const int* lex = L->lex_of_site_dev.as<int>();
-        const long sl = (long)it.op->Ls * it.nrhs;
         const void* src = b5[&it - B.items.data()];
-        pack_full(ST_F64, at(be.p, it.off), at(bo.p, it.off), src, lex, L->Vh, L->Vhp, L->V, sl, cs.s);
+        pack_full(ST_F64, at(be.p, it.off), at(bo.p, it.off), src, lex, L->Vh, L->Vhp, L->V, it.op->Ls, cs.s, it.nrhs);
         schur_rhs(it.op, ST_F64, at(bt.p, it.off), at(be.p, it.off), at(bo.p, it.off), at(to.p, it.off), it.nrhs,
                   cs.s);
     }
@@ -592,9 +590,9 @@ int solve_batch(int n, const dwf_op* const* ops, void* const* x5, const void* co
             const Item& it = B.items[i];
             apply_dhat(it.op, ST_F64, 1, at(te.p, it.off), at(rh.p, it.off), at(to.p, it.off), at(tmp.p, it.off),
                        it.nrhs, cs.s);
-            convert(I->kx, ST_F64, rat(it), at(te.p, it.off), it.n1 * it.nrhs, cs.s, it.op->lat->Vhp);
+            convert(I->kx, ST_F64, rat(it), at(te.p, it.off), it.n1 * it.nrhs, cs.s);
             convert(I->kp, I->kx, static_cast<char*>(I->pslot(0)) + complex_bytes_of(I->kp) * it.off, rat(it),
-                    it.n1 * it.nrhs, cs.s, it.op->lat->Vhp);
+                    it.n1 * it.nrhs, cs.s);
             DWF_HIP(hipMemsetAsync(xat(it), 0, complex_bytes_of(I->kx) * it.n1 * it.nrhs, cs.s));
             for (int v = it.slot0; v < it.slot0 + it.nrhs; ++v) {
                 const bool plain = I->kp == ST_F64 && outer[v] == 0;
@@ -651,7 +649,7 @@ int solve_batch(int n, const dwf_op* const* ops, void* const* x5, const void* co
             }
             // x^ += x; r^ = b~ - D^ x^; 5D residual |M r^| / |b5|
             axpby(ST_F64, I->kx, at(xe.p, it.off), xat(it), it.n1 * it.nrhs, nullptr, 1.0, nullptr, 1.0, nullptr,
-                  cs.s, it.op->lat->Vhp);
+                  cs.s);
             apply_dhat(it.op, ST_F64, 0, at(te.p, it.off), at(xe.p, it.off), at(to.p, it.off), nullptr, it.nrhs,
                        cs.s);
             convert(ST_F64, ST_F64, at(rh.p, it.off), at(bt.p, it.off), it.n1 * it.nrhs, cs.s);
@@ -699,10 +697,9 @@ int solve_batch(int n, const dwf_op* const* ops, void* const* x5, const void* co
     for (const Item& it : B.items) {
         const dwf_lattice* L = it.op->lat;
         const int* lex = L->lex_of_site_dev.as<int>();
-        const long sl = (long)it.op->Ls * it.nrhs;
         void* dst = x5[&it - B.items.data()];
         reconstruct_odd(it.op, ST_F64, at(xo.p, it.off), at(xe.p, it.off), at(bo.p, it.off), it.nrhs, cs.s);
-        unpack_full(ST_F64, dst, at(xe.p, it.off), at(xo.p, it.off), lex, L->Vh, L->Vhp, L->V, sl, cs.s);
+        unpack_full(ST_F64, dst, at(xe.p, it.off), at(xo.p, it.off), lex, L->Vh, L->Vhp, L->V, it.op->Ls, cs.s, it.nrhs);
     }
     DWF_HIP(hipEventRecord(e1.e, cs.s));
     // FP64 true 5D residual per slot (outside the timed region)

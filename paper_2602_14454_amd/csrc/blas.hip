@@ -40,7 +40,10 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
 // one slice through LDS, so that both sides are read and written in whole
 // 16-byte pieces by consecutive lanes (a thread per site instead, 192 bytes a
 // lane on the canonical side, took 794 us to pack and 923 us to unpack the even
-// vector of 24^3x48, Ls = 16, in FP32; now 314 us, 4.9 TB/s, and 264 us, 5.8 TB/s).  The
+// vector of 24^3x48, Ls = 16, in FP32; now 193 and 181 us, 1.5 GB moved, part of
+// it still in the last-level cache).  Consecutive blocks take the slices of the
+// same sites, whose internal data are adjacent: with the sites of one slice in
+// sequence instead, each slice a stream of its own, it took 337 and 279 us.  The
 // two parities of a site pair are adjacent in the canonical field, hence the
 // common launch.  EO5 (NP = 2): the two fields are split by 5D parity, site
 // parity p of slice s belongs to field (p + s) & 1; a missing field is skipped
@@ -64,18 +67,24 @@ __device__ __forceinline__ long tp_canonical(int e, unsigned tile, long Vh, long
     return (rs * vstride + (NP == 2 ? x : x >> 1)) * 12 + cp;
 }
 
+// LDS site of thread e of NG * 64 on the internal side, in the order of memory:
+// 16 sites x NG groups of one slice of a tile are one run.
+template <int NG>
+__device__ __forceinline__ int tp_site(int e) { return e / (NG * 16) * 16 + (e & 15); }
+
 template <class S, int NP, bool EO5 = false>
 __global__ __launch_bounds__(256) void pack_kernel(void* d0, void* d1, const double2* __restrict__ src,
                                                    const int* __restrict__ lex, long Vh, long Vhp, long vstride,
-                                                   unsigned tiles) {
+                                                   unsigned tiles, int Ls) {
     using C = typename Traits<S>::C;
     using R = typename Traits<S>::R;
     constexpr int P = fpack<S>(), NG = 12 / P, ST = tp_stride<S>();
     static_assert(P * cbytes<S>() == 16, "16-byte field groups expected");
     __shared__ u32x4 smem[(TP_SITES * ST * sizeof(C) + 15) / 16];
     C* t = reinterpret_cast<C*>(smem);
-    const unsigned tile = blockIdx.x % tiles;
-    const long rs = blockIdx.x / tiles;
+    const unsigned tile = blockIdx.x / (gridDim.x / tiles);
+    const unsigned rs = blockIdx.x % (gridDim.x / tiles), r = rs / (unsigned)Ls, s = rs - r * (unsigned)Ls;
+    const long ng = (long)Ls * NG, field = r * ng * Vhp;   // groups per site, and before this right-hand side
     double2 v[3];
     int at[3];
 #pragma unroll
@@ -91,35 +100,36 @@ __global__ __launch_bounds__(256) void pack_kernel(void* d0, void* d1, const dou
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < (NG * TP_SITES + 255) / 256; ++k) {
-        const int e = (int)threadIdx.x + k * 256, q = e & (TP_SITES - 1), g = e / TP_SITES;
+        const int e = (int)threadIdx.x + k * 256, q = tp_site<NG>(e), g = (e >> 4) % NG;
         const int par = NP == 2 ? q / (TP_SITES / NP) : 0;
         const long site = (long)tile * (TP_SITES / NP) + q % (TP_SITES / NP);
         void* d = (EO5 ? (par ^ (int)rs) & 1 : par) ? d1 : d0;
-        if (g < NG && site < Vh && (!EO5 || d))
-            static_cast<u32x4*>(d)[(rs * NG + g) * Vhp + site] = *reinterpret_cast<const u32x4*>(t + q * ST + P * g);
+        if (e < NG * TP_SITES && site < Vh && (!EO5 || d))
+            static_cast<u32x4*>(d)[field + gidx(s * NG + g, site, ng)] = *reinterpret_cast<const u32x4*>(t + q * ST + P * g);
     }
 }
 
 template <class S, int NP, bool EO5 = false>
 __global__ __launch_bounds__(256) void unpack_kernel(double2* __restrict__ dst, const void* s0, const void* s1,
                                                      const int* __restrict__ lex, long Vh, long Vhp, long vstride,
-                                                     unsigned tiles) {
+                                                     unsigned tiles, int Ls) {
     using C = typename Traits<S>::C;
     constexpr int P = fpack<S>(), NG = 12 / P, ST = tp_stride<S>();
     constexpr int NK = (NG * TP_SITES + 255) / 256;
     __shared__ u32x4 smem[(TP_SITES * ST * sizeof(C) + 15) / 16];
     C* t = reinterpret_cast<C*>(smem);
-    const unsigned tile = blockIdx.x % tiles;
-    const long rs = blockIdx.x / tiles;
+    const unsigned tile = blockIdx.x / (gridDim.x / tiles);
+    const unsigned rs = blockIdx.x % (gridDim.x / tiles), r = rs / (unsigned)Ls, s = rs - r * (unsigned)Ls;
+    const long ng = (long)Ls * NG, field = r * ng * Vhp;   // groups per site, and before this right-hand side
     u32x4 v[NK];
 #pragma unroll
     for (int k = 0; k < NK; ++k) {
-        const int e = (int)threadIdx.x + k * 256, q = e & (TP_SITES - 1), g = e / TP_SITES;
+        const int e = (int)threadIdx.x + k * 256, q = tp_site<NG>(e), g = (e >> 4) % NG;
         const int par = NP == 2 ? q / (TP_SITES / NP) : 0;
         const long site = (long)tile * (TP_SITES / NP) + q % (TP_SITES / NP);
         const void* sp = (EO5 ? (par ^ (int)rs) & 1 : par) ? s1 : s0;
         if (EO5 && !sp) v[k] = u32x4{0u, 0u, 0u, 0u};
-        else if (g < NG && site < Vh) v[k] = static_cast<const u32x4*>(sp)[(rs * NG + g) * Vhp + site];
+        else if (e < NG * TP_SITES && site < Vh) v[k] = static_cast<const u32x4*>(sp)[field + gidx(s * NG + g, site, ng)];
     }
     long a[3];
     int at[3];
@@ -131,8 +141,8 @@ __global__ __launch_bounds__(256) void unpack_kernel(double2* __restrict__ dst, 
     }
 #pragma unroll
     for (int k = 0; k < NK; ++k) {
-        const int e = (int)threadIdx.x + k * 256, q = e & (TP_SITES - 1), g = e / TP_SITES;
-        if (g < NG) *reinterpret_cast<u32x4*>(t + q * ST + P * g) = v[k];
+        const int e = (int)threadIdx.x + k * 256, q = tp_site<NG>(e), g = (e >> 4) % NG;
+        if (e < NG * TP_SITES) *reinterpret_cast<u32x4*>(t + q * ST + P * g) = v[k];
     }
     __syncthreads();
 #pragma unroll
@@ -178,19 +188,19 @@ __global__ __launch_bounds__(256) void links_kernel(double2* __restrict__ l64, f
         for (int e = 9; e < 12; ++e) u[e] = make_double2(0.0, 0.0);   // unused elements of the last group
         const long r64 = link_elems_parity(Vhp, 16), r32 = link_elems_parity(Vhp, 8), r16 = link_elems_parity(Vhp, 4);
 #pragma unroll
-        for (int e = 0; e < link_ng(16) * link_lp(16); ++e) l64[p * r64 + lidx(d, e, i, Vhp, 16)] = u[e];
+        for (int e = 0; e < link_ng(16) * link_lp(16); ++e) l64[p * r64 + lidx(d, e, i, 16)] = u[e];
 #pragma unroll
         for (int e = 0; e < link_ng(8) * link_lp(8); ++e)
-            l32[p * r32 + lidx(d, e, i, Vhp, 8)] = make_float2((float)u[e].x, (float)u[e].y);
+            l32[p * r32 + lidx(d, e, i, 8)] = make_float2((float)u[e].x, (float)u[e].y);
 #pragma unroll
         for (int e = 0; e < link_ng(4) * link_lp(4); ++e)
-            l16[p * r16 + lidx(d, e, i, Vhp, 4)] = pack_bf16((float)u[e].x, (float)u[e].y);
+            l16[p * r16 + lidx(d, e, i, 4)] = pack_bf16((float)u[e].x, (float)u[e].y);
     }
 }
 
 // 4D canonical -> two-slice half field of one parity: slice 0 = P+ b4, slice 1 = P- b4
 template <class S>
-__global__ void pack_chiral_pair_kernel(void* dst, const double2* b4, const int* lex_of_site, long Vh, long Vhp) {
+__global__ void pack_chiral_pair_kernel(void* dst, const double2* b4, const int* lex_of_site, long Vh) {
     const long eo = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (eo >= Vh) return;
     const long lex = lex_of_site[eo];
@@ -198,8 +208,8 @@ __global__ void pack_chiral_pair_kernel(void* dst, const double2* b4, const int*
     for (int cp = 0; cp < 12; ++cp) {
         double2 v = b4[lex * 12 + cp];
         const bool up = cp < 6;
-        cstore<S>(dst, fidx(cp, eo, Vhp, fpack<S>()), up ? v.x : 0.0, up ? v.y : 0.0);
-        cstore<S>(dst, fidx(12 + cp, eo, Vhp, fpack<S>()), up ? 0.0 : v.x, up ? 0.0 : v.y);
+        cstore<S>(dst, fidx(cp, eo, 24, fpack<S>()), up ? v.x : 0.0, up ? v.y : 0.0);
+        cstore<S>(dst, fidx(12 + cp, eo, 24, fpack<S>()), up ? 0.0 : v.x, up ? 0.0 : v.y);
     }
 }
 
@@ -242,37 +252,34 @@ __global__ void convert_kernel(void* dst, const void* src, long n) {
 }
 
 // The same copy between layouts with different component grouping (FP64
-// single components, FP32 pairs, BF16 quads): thread t handles rows 4g..4g+3
-// of site t % Vhp, g = t / Vhp.
+// single components, FP32 pairs, BF16 quads), a quad per thread.
 template <class SD, class SS>
-__global__ void convert_remap_kernel(void* dst, const void* src, long nquads, long Vhp) {
+__global__ void convert_remap_kernel(void* dst, const void* src, long nquads) {
     for (long t = (long)blockIdx.x * blockDim.x + threadIdx.x; t < nquads; t += (long)gridDim.x * blockDim.x) {
-        const long g = t / Vhp, site = t - g * Vhp;
         typename Traits<SS>::R a[8];
         typename Traits<SD>::R c[8];
-        load4<SS>(src, g, site, Vhp, a);
+        load4<SS>(src, t, a);
 #pragma unroll
         for (int k = 0; k < 8; ++k) c[k] = (typename Traits<SD>::R)a[k];
-        store4<SD>(dst, g, site, Vhp, c);
+        store4<SD>(dst, t, c);
     }
 }
 
 // y = a x + b y between layouts with different grouping (no reduction)
 template <class SY, class SX>
-__global__ void axpby_remap_kernel(void* y, const void* x, long nquads, long Vhp, const double* sa, double ha,
+__global__ void axpby_remap_kernel(void* y, const void* x, long nquads, const double* sa, double ha,
                                    const double* sb, double hb) {
     const double a = sa ? *sa : ha;
     const double bb = sb ? *sb : hb;
     using RY = typename Traits<SY>::R;
     for (long t = (long)blockIdx.x * blockDim.x + threadIdx.x; t < nquads; t += (long)gridDim.x * blockDim.x) {
-        const long g = t / Vhp, site = t - g * Vhp;
         typename Traits<SX>::R xv[8];
         RY yv[8];
-        load4<SX>(x, g, site, Vhp, xv);
-        load4<SY>(y, g, site, Vhp, yv);
+        load4<SX>(x, t, xv);
+        load4<SY>(y, t, yv);
 #pragma unroll
         for (int k = 0; k < 8; ++k) yv[k] = RY(a) * RY(xv[k]) + RY(bb) * yv[k];
-        store4<SY>(y, g, site, Vhp, yv);
+        store4<SY>(y, t, yv);
     }
 }
 
@@ -280,46 +287,44 @@ __global__ void axpby_remap_kernel(void* y, const void* x, long nquads, long Vhp
 // same arithmetic as cg_xr_kernel / cg_p_kernel, each operand read in its own
 // layout with whole-group accesses, four components of one site per thread.
 template <class SX, class SP>
-__global__ void cg_xr_remap_kernel(void* x, void* r, const void* p, const void* w, long nquads, long Vhp,
+__global__ void cg_xr_remap_kernel(void* x, void* r, const void* p, const void* w, long nquads,
                                    const double* alpha, double* partial) {
     __shared__ double red[BLAS_THREADS / 64];
     using RX = typename Traits<SX>::R;
     const RX a = RX(*alpha);
     double acc = 0.0;
     for (long t = (long)blockIdx.x * blockDim.x + threadIdx.x; t < nquads; t += (long)gridDim.x * blockDim.x) {
-        const long g = t / Vhp, site = t - g * Vhp;
         typename Traits<SP>::R pv[8], wv[8];
         RX xv[8], rv[8];
-        load4<SP>(p, g, site, Vhp, pv);
-        load4<SP>(w, g, site, Vhp, wv);
-        load4<SX>(x, g, site, Vhp, xv);
-        load4<SX>(r, g, site, Vhp, rv);
+        load4<SP>(p, t, pv);
+        load4<SP>(w, t, wv);
+        load4<SX>(x, t, xv);
+        load4<SX>(r, t, rv);
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
             xv[k] += a * RX(pv[k]);
             rv[k] -= a * RX(wv[k]);
             acc += double(rv[k]) * double(rv[k]);
         }
-        store4<SX>(x, g, site, Vhp, xv);
-        store4<SX>(r, g, site, Vhp, rv);
+        store4<SX>(x, t, xv);
+        store4<SX>(r, t, rv);
     }
     double tt = block_sum(acc, red);
     if (threadIdx.x == 0) partial[blockIdx.x] = tt;
 }
 
 template <class SR, class SP>
-__global__ void cg_p_remap_kernel(void* p, const void* r, long nquads, long Vhp, const double* beta) {
+__global__ void cg_p_remap_kernel(void* p, const void* r, long nquads, const double* beta) {
     using RP = typename Traits<SP>::R;
     const RP b = RP(*beta);
     for (long t = (long)blockIdx.x * blockDim.x + threadIdx.x; t < nquads; t += (long)gridDim.x * blockDim.x) {
-        const long g = t / Vhp, site = t - g * Vhp;
         typename Traits<SR>::R rv[8];
         RP pv[8];
-        load4<SR>(r, g, site, Vhp, rv);
-        load4<SP>(p, g, site, Vhp, pv);
+        load4<SR>(r, t, rv);
+        load4<SP>(p, t, pv);
 #pragma unroll
         for (int k = 0; k < 8; ++k) pv[k] = RP(rv[k]) + b * pv[k];
-        store4<SP>(p, g, site, Vhp, pv);
+        store4<SP>(p, t, pv);
     }
 }
 
@@ -337,19 +342,18 @@ __global__ void cg_p2_kernel(void* pd, const void* ps, const void* r, long n, co
     }
 }
 template <class SR, class SP>
-__global__ void cg_p2_remap_kernel(void* pd, const void* ps, const void* r, long nquads, long Vhp,
+__global__ void cg_p2_remap_kernel(void* pd, const void* ps, const void* r, long nquads,
                                    const double* beta) {
     using RP = typename Traits<SP>::R;
     const RP b = RP(*beta);
     for (long t = (long)blockIdx.x * blockDim.x + threadIdx.x; t < nquads; t += (long)gridDim.x * blockDim.x) {
-        const long g = t / Vhp, site = t - g * Vhp;
         typename Traits<SR>::R rv[8];
         RP pv[8];
-        load4<SR>(r, g, site, Vhp, rv);
-        load4<SP>(ps, g, site, Vhp, pv);
+        load4<SR>(r, t, rv);
+        load4<SP>(ps, t, pv);
 #pragma unroll
         for (int k = 0; k < 8; ++k) pv[k] = RP(rv[k]) + b * pv[k];
-        store4<SP>(pd, g, site, Vhp, pv);
+        store4<SP>(pd, t, pv);
     }
 }
 
@@ -422,47 +426,44 @@ __global__ __launch_bounds__(256) void cg_p2_f32_kernel(float4* __restrict__ pd,
 }
 
 template <class SX, class SP>
-__global__ void cg_accx_remap_kernel(void* x, const void* ring, const double* alpha, int cnt, long n, long nquads,
-                                     long Vhp) {
+__global__ void cg_accx_remap_kernel(void* x, const void* ring, const double* alpha, int cnt, long n, long nquads) {
     using RX = typename Traits<SX>::R;
     for (long t = (long)blockIdx.x * blockDim.x + threadIdx.x; t < nquads; t += (long)gridDim.x * blockDim.x) {
-        const long g = t / Vhp, site = t - g * Vhp;
         RX xv[8];
-        load4<SX>(x, g, site, Vhp, xv);
+        load4<SX>(x, t, xv);
         for (int q = 0; q < cnt; ++q) {
             typename Traits<SP>::R pv[8];
-            load4<SP>(static_cast<const char*>(ring) + (size_t)q * n * cbytes<SP>(), g, site, Vhp, pv);
+            load4<SP>(static_cast<const char*>(ring) + (size_t)q * n * cbytes<SP>(), t, pv);
             const RX a = RX(alpha[q]);
 #pragma unroll
             for (int k = 0; k < 8; ++k) xv[k] = xv[k] + a * RX(pv[k]);
         }
-        store4<SX>(x, g, site, Vhp, xv);
+        store4<SX>(x, t, xv);
     }
 }
 
 // x += alpha p; p = r + beta p (the x update of a CG step deferred to the
 // kernel that reads p anyway), operands in different layouts
 template <class SX, class SP>
-__global__ void cg_px_remap_kernel(void* x, void* p, const void* r, long nquads, long Vhp, const double* alpha,
+__global__ void cg_px_remap_kernel(void* x, void* p, const void* r, long nquads, const double* alpha,
                                    const double* beta) {
     using RX = typename Traits<SX>::R;
     using RP = typename Traits<SP>::R;
     const RX a = RX(*alpha);
     const RP b = RP(*beta);
     for (long t = (long)blockIdx.x * blockDim.x + threadIdx.x; t < nquads; t += (long)gridDim.x * blockDim.x) {
-        const long g = t / Vhp, site = t - g * Vhp;
         RX xv[8], rv[8];
         RP pv[8];
-        load4<SP>(p, g, site, Vhp, pv);
-        load4<SX>(x, g, site, Vhp, xv);
-        load4<SX>(r, g, site, Vhp, rv);
+        load4<SP>(p, t, pv);
+        load4<SX>(x, t, xv);
+        load4<SX>(r, t, rv);
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
             xv[k] += a * RX(pv[k]);
             pv[k] = RP(rv[k]) + b * pv[k];
         }
-        store4<SX>(x, g, site, Vhp, xv);
-        store4<SP>(p, g, site, Vhp, pv);
+        store4<SX>(x, t, xv);
+        store4<SP>(p, t, pv);
     }
 }
 
@@ -535,7 +536,7 @@ __global__ void caxpy_kernel(void* y, const void* x, long n, double ar, double a
 
 // Deterministic pseudo-random fill in [-1, 1) (SplitMix64 of seed and index)
 // on the valid sites of each row; padding stays zero.
-__global__ void random_fill_kernel(double2* v, long rows, long Vh, long Vhp, unsigned long long seed) {
+__global__ void random_fill_kernel(double2* v, long rows, long Vh, unsigned long long seed) {
     const long n = rows * Vh;
     for (long k = (long)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (long)gridDim.x * blockDim.x) {
         const long row = k / Vh, site = k % Vh;
@@ -547,7 +548,7 @@ __global__ void random_fill_kernel(double2* v, long rows, long Vh, long Vhp, uns
             z ^= z >> 31;
             out[h] = (double)(z >> 11) * (2.0 / 9007199254740992.0) - 1.0;
         }
-        v[fidx(row, site, Vhp, 1)] = make_double2(out[0], out[1]);
+        v[fidx(row, site, rows, 1)] = make_double2(out[0], out[1]);
     }
 }
 
@@ -699,79 +700,80 @@ static unsigned tp_grid(long Vh, int np, long ns, unsigned* tiles) {
 }
 template <class S>
 static void pack_t(int np, void* d0, void* d1, const void* src, const int* lex, long Vh, long Vhp, long vstride,
-                   long ns, hipStream_t st) {
+                     int Ls, long nrhs, hipStream_t st) {
     unsigned tiles;
-    const unsigned blocks = tp_grid(Vh, np, ns, &tiles);
+    const unsigned blocks = tp_grid(Vh, np, Ls * nrhs, &tiles);
     if (np == 2)
         hipLaunchKernelGGL((pack_kernel<S, 2>), dim3(blocks), dim3(256), 0, st, d0, d1, (const double2*)src, lex, Vh,
-                           Vhp, vstride, tiles);
+                           Vhp, vstride, tiles, Ls);
     else
         hipLaunchKernelGGL((pack_kernel<S, 1>), dim3(blocks), dim3(256), 0, st, d0, d1, (const double2*)src, lex, Vh,
-                           Vhp, vstride, tiles);
+                           Vhp, vstride, tiles, Ls);
 }
 template <class S>
 static void unpack_t(int np, void* dst, const void* s0, const void* s1, const int* lex, long Vh, long Vhp,
-                     long vstride, long ns, hipStream_t st) {
+                     long vstride,
+                     int Ls, long nrhs, hipStream_t st) {
     unsigned tiles;
-    const unsigned blocks = tp_grid(Vh, np, ns, &tiles);
+    const unsigned blocks = tp_grid(Vh, np, Ls * nrhs, &tiles);
     if (np == 2)
         hipLaunchKernelGGL((unpack_kernel<S, 2>), dim3(blocks), dim3(256), 0, st, (double2*)dst, s0, s1, lex, Vh, Vhp,
-                           vstride, tiles);
+                           vstride, tiles, Ls);
     else
         hipLaunchKernelGGL((unpack_kernel<S, 1>), dim3(blocks), dim3(256), 0, st, (double2*)dst, s0, s1, lex, Vh, Vhp,
-                           vstride, tiles);
+                           vstride, tiles, Ls);
 }
 
 template <class S>
-static void pack_eo5_t(void* d0, void* d1, const void* src, const int* lex, long Vh, long V, long ns, hipStream_t st) {
+static void pack_eo5_t(void* d0, void* d1, const void* src, const int* lex, long Vh, long Vhp, long V, int Ls, hipStream_t st) {
     unsigned tiles;
-    const unsigned blocks = tp_grid(Vh, 2, ns, &tiles);
+    const unsigned blocks = tp_grid(Vh, 2, Ls, &tiles);
     hipLaunchKernelGGL((pack_kernel<S, 2, true>), dim3(blocks), dim3(256), 0, st, d0, d1, (const double2*)src, lex, Vh,
-                       Vh, V, tiles);
+                       Vhp, V, tiles, Ls);
 }
 template <class S>
-static void unpack_eo5_t(void* dst, const void* s0, const void* s1, const int* lex, long Vh, long V, long ns,
+static void unpack_eo5_t(void* dst, const void* s0, const void* s1, const int* lex, long Vh, long Vhp, long V, int Ls,
                          hipStream_t st) {
     unsigned tiles;
-    const unsigned blocks = tp_grid(Vh, 2, ns, &tiles);
-    hipLaunchKernelGGL((unpack_kernel<S, 2, true>), dim3(blocks), dim3(256), 0, st, (double2*)dst, s0, s1, lex, Vh, Vh,
-                       V, tiles);
+    const unsigned blocks = tp_grid(Vh, 2, Ls, &tiles);
+    hipLaunchKernelGGL((unpack_kernel<S, 2, true>), dim3(blocks), dim3(256), 0, st, (double2*)dst, s0, s1, lex, Vh, Vhp,
+                       V, tiles, Ls);
 }
-void pack_eo5(int kind, void* dst_e, void* dst_o, const void* src, const int* lex, long Vh, long V, int Ls,
+void pack_eo5(int kind, void* dst_e, void* dst_o, const void* src, const int* lex, long Vh, long Vhp, long V, int Ls,
               hipStream_t st) {
-    if (kind == ST_F64) pack_eo5_t<double>(dst_e, dst_o, src, lex, Vh, V, Ls, st);
-    else if (kind == ST_F32) pack_eo5_t<float>(dst_e, dst_o, src, lex, Vh, V, Ls, st);
+    if (kind == ST_F64) pack_eo5_t<double>(dst_e, dst_o, src, lex, Vh, Vhp, V, Ls, st);
+    else if (kind == ST_F32) pack_eo5_t<float>(dst_e, dst_o, src, lex, Vh, Vhp, V, Ls, st);
     else throw Error{DWF_EINVAL, "5D even-odd fields are FP64 or FP32"};
     DWF_HIP(hipGetLastError());
 }
-void unpack_eo5(int kind, void* dst, const void* src_e, const void* src_o, const int* lex, long Vh, long V, int Ls,
-                hipStream_t st) {
-    if (kind == ST_F64) unpack_eo5_t<double>(dst, src_e, src_o, lex, Vh, V, Ls, st);
-    else if (kind == ST_F32) unpack_eo5_t<float>(dst, src_e, src_o, lex, Vh, V, Ls, st);
+void unpack_eo5(int kind, void* dst, const void* src_e, const void* src_o, const int* lex, long Vh, long Vhp, long V, int Ls,
+              hipStream_t st) {
+    if (kind == ST_F64) unpack_eo5_t<double>(dst, src_e, src_o, lex, Vh, Vhp, V, Ls, st);
+    else if (kind == ST_F32) unpack_eo5_t<float>(dst, src_e, src_o, lex, Vh, Vhp, V, Ls, st);
     else throw Error{DWF_EINVAL, "5D even-odd fields are FP64 or FP32"};
     DWF_HIP(hipGetLastError());
 }
 
 void pack_full(int kind, void* dst_e, void* dst_o, const void* src, const int* lex, long Vh, long Vhp, long V,
-               long ns, hipStream_t st) {
-    if (ns <= 0) return;
-    DISPATCH1(kind, pack_t, 2, dst_e, dst_o, src, lex, Vh, Vhp, V, ns, st);
+               int Ls, hipStream_t st, long nrhs) {
+    if (Ls <= 0 || nrhs <= 0) return;
+    DISPATCH1(kind, pack_t, 2, dst_e, dst_o, src, lex, Vh, Vhp, V, Ls, nrhs, st);
     DWF_HIP(hipGetLastError());
 }
 void unpack_full(int kind, void* dst, const void* src_e, const void* src_o, const int* lex, long Vh, long Vhp,
-                 long V, long ns, hipStream_t st) {
-    if (ns <= 0) return;
-    DISPATCH1(kind, unpack_t, 2, dst, src_e, src_o, lex, Vh, Vhp, V, ns, st);
+                 long V, int Ls, hipStream_t st, long nrhs) {
+    if (Ls <= 0 || nrhs <= 0) return;
+    DISPATCH1(kind, unpack_t, 2, dst, src_e, src_o, lex, Vh, Vhp, V, Ls, nrhs, st);
     DWF_HIP(hipGetLastError());
 }
-void pack_half(int kind, void* dst, const void* src, const int* lex, long Vh, long Vhp, long ns, hipStream_t st) {
-    if (ns <= 0) return;
-    DISPATCH1(kind, pack_t, 1, dst, nullptr, src, lex, Vh, Vhp, Vh, ns, st);
+void pack_half(int kind, void* dst, const void* src, const int* lex, long Vh, long Vhp, int Ls, hipStream_t st) {
+    if (Ls <= 0) return;
+    DISPATCH1(kind, pack_t, 1, dst, nullptr, src, lex, Vh, Vhp, Vh, Ls, 1, st);
     DWF_HIP(hipGetLastError());
 }
-void unpack_half(int kind, void* dst, const void* src, const int* lex, long Vh, long Vhp, long ns, hipStream_t st) {
-    if (ns <= 0) return;
-    DISPATCH1(kind, unpack_t, 1, dst, src, nullptr, lex, Vh, Vhp, Vh, ns, st);
+void unpack_half(int kind, void* dst, const void* src, const int* lex, long Vh, long Vhp, int Ls, hipStream_t st) {
+    if (Ls <= 0) return;
+    DISPATCH1(kind, unpack_t, 1, dst, src, nullptr, lex, Vh, Vhp, Vh, Ls, 1, st);
     DWF_HIP(hipGetLastError());
 }
 
@@ -782,9 +784,9 @@ void pack_links(void* l64, void* l32, void* l16, const void* U, const int* lex, 
     DWF_HIP(hipGetLastError());
 }
 
-void pack_chiral_pair_f64(void* dst, const void* b4, const int* lex, long Vh, long Vhp, hipStream_t st) {
+void pack_chiral_pair_f64(void* dst, const void* b4, const int* lex, long Vh, hipStream_t st) {
     hipLaunchKernelGGL(pack_chiral_pair_kernel<double>, dim3(blocks_for(Vh, 256)), dim3(256), 0, st, dst,
-                       (const double2*)b4, lex, Vh, Vhp);
+                       (const double2*)b4, lex, Vh);
     DWF_HIP(hipGetLastError());
 }
 
@@ -801,26 +803,26 @@ void embed_4d(void* e5, const void* y, long V, int Ls, hipStream_t st) {
 }
 
 template <class SD, class SS>
-static void convert_t2(void* dst, const void* src, long n, long Vhp, hipStream_t st) {
+static void convert_t2(void* dst, const void* src, long n, hipStream_t st) {
     if (fpack<SD>() == fpack<SS>())
         hipLaunchKernelGGL((convert_kernel<SD, SS>), dim3(blas_grid(n)), dim3(BLAS_THREADS), 0, st, dst, src, n);
     else
         hipLaunchKernelGGL((convert_remap_kernel<SD, SS>), dim3(blas_grid(n / 4)), dim3(BLAS_THREADS), 0, st, dst,
-                           src, n / 4, Vhp);
+                           src, n / 4);
 }
 template <class SD>
-static void convert_t1(int ks, void* dst, const void* src, long n, long Vhp, hipStream_t st) {
+static void convert_t1(int ks, void* dst, const void* src, long n, hipStream_t st) {
     switch (ks) {
-        case ST_F64: convert_t2<SD, double>(dst, src, n, Vhp, st); break;
-        case ST_F32: convert_t2<SD, float>(dst, src, n, Vhp, st); break;
-        case ST_BF16: convert_t2<SD, bf16s>(dst, src, n, Vhp, st); break;
+        case ST_F64: convert_t2<SD, double>(dst, src, n, st); break;
+        case ST_F32: convert_t2<SD, float>(dst, src, n, st); break;
+        case ST_BF16: convert_t2<SD, bf16s>(dst, src, n, st); break;
         default: throw Error{DWF_EINVAL, "bad storage kind"};
     }
 }
-void convert(int kd, int ks, void* dst, const void* src, long n, hipStream_t st, long Vhp) {
+void convert(int kd, int ks, void* dst, const void* src, long n, hipStream_t st) {
     if (fpack_of(kd) != fpack_of(ks))
-        DWF_REQUIRE(Vhp > 0 && n % (4 * Vhp) == 0, DWF_EINVAL, "layout change needs the row stride");
-    DISPATCH1(kd, convert_t1, ks, dst, src, n, Vhp, st);
+        DWF_REQUIRE(n % 64 == 0, DWF_EINVAL, "layout change needs whole tiles");
+    DISPATCH1(kd, convert_t1, ks, dst, src, n, st);
     DWF_HIP(hipGetLastError());
 }
 
@@ -849,10 +851,10 @@ static void axpby_t2(void* y, const void* x, long n, const double* sa, double ha
                        sb, hb, partial);
 }
 template <class SY, class SX>
-static void axpby_remap_t(void* y, const void* x, long n, long Vhp, const double* sa, double ha, const double* sb,
+static void axpby_remap_t(void* y, const void* x, long n, const double* sa, double ha, const double* sb,
                           double hb, hipStream_t st) {
     hipLaunchKernelGGL((axpby_remap_kernel<SY, SX>), dim3(blas_grid(n / 4)), dim3(BLAS_THREADS), 0, st, y, x, n / 4,
-                       Vhp, sa, ha, sb, hb);
+                       sa, ha, sb, hb);
 }
 template <class SY>
 static void axpby_t1(int kx, void* y, const void* x, long n, const double* sa, double ha, const double* sb,
@@ -865,16 +867,16 @@ static void axpby_t1(int kx, void* y, const void* x, long n, const double* sa, d
     }
 }
 void axpby(int ky, int kx, void* y, const void* x, long n, const double* sa, double ha, const double* sb,
-           double hb, double* partial, hipStream_t st, long Vhp) {
+           double hb, double* partial, hipStream_t st) {
     if (fpack_of(ky) != fpack_of(kx)) {
-        DWF_REQUIRE(Vhp > 0 && n % (4 * Vhp) == 0 && !partial, DWF_EINVAL, "layout change needs the row stride");
+        DWF_REQUIRE(n % 64 == 0 && !partial, DWF_EINVAL, "layout change needs whole tiles");
         switch (ky * 3 + kx) {
-            case ST_F64 * 3 + ST_F32: axpby_remap_t<double, float>(y, x, n, Vhp, sa, ha, sb, hb, st); break;
-            case ST_F64 * 3 + ST_BF16: axpby_remap_t<double, bf16s>(y, x, n, Vhp, sa, ha, sb, hb, st); break;
-            case ST_F32 * 3 + ST_F64: axpby_remap_t<float, double>(y, x, n, Vhp, sa, ha, sb, hb, st); break;
-            case ST_F32 * 3 + ST_BF16: axpby_remap_t<float, bf16s>(y, x, n, Vhp, sa, ha, sb, hb, st); break;
-            case ST_BF16 * 3 + ST_F64: axpby_remap_t<bf16s, double>(y, x, n, Vhp, sa, ha, sb, hb, st); break;
-            default: axpby_remap_t<bf16s, float>(y, x, n, Vhp, sa, ha, sb, hb, st); break;
+            case ST_F64 * 3 + ST_F32: axpby_remap_t<double, float>(y, x, n, sa, ha, sb, hb, st); break;
+            case ST_F64 * 3 + ST_BF16: axpby_remap_t<double, bf16s>(y, x, n, sa, ha, sb, hb, st); break;
+            case ST_F32 * 3 + ST_F64: axpby_remap_t<float, double>(y, x, n, sa, ha, sb, hb, st); break;
+            case ST_F32 * 3 + ST_BF16: axpby_remap_t<float, bf16s>(y, x, n, sa, ha, sb, hb, st); break;
+            case ST_BF16 * 3 + ST_F64: axpby_remap_t<bf16s, double>(y, x, n, sa, ha, sb, hb, st); break;
+            default: axpby_remap_t<bf16s, float>(y, x, n, sa, ha, sb, hb, st); break;
         }
         DWF_HIP(hipGetLastError());
         return;
@@ -884,7 +886,7 @@ void axpby(int ky, int kx, void* y, const void* x, long n, const double* sa, dou
 }
 
 template <class SX, class SP>
-static void cg_xr_t2(void* x, void* r, const void* p, const void* w, long n, long Vhp, const double* alpha,
+static void cg_xr_t2(void* x, void* r, const void* p, const void* w, long n, const double* alpha,
                      double* partial, hipStream_t st) {
     // same block count in both forms: callers reduce blas_grid(n) partials
     if (fpack<SX>() == fpack<SP>())
@@ -892,80 +894,80 @@ static void cg_xr_t2(void* x, void* r, const void* p, const void* w, long n, lon
                            alpha, partial);
     else
         hipLaunchKernelGGL((cg_xr_remap_kernel<SX, SP>), dim3(blas_grid(n)), dim3(BLAS_THREADS), 0, st, x, r, p, w,
-                           n / 4, Vhp, alpha, partial);
+                           n / 4, alpha, partial);
 }
 template <class SX>
-static void cg_xr_t1(int kp, void* x, void* r, const void* p, const void* w, long n, long Vhp, const double* alpha,
+static void cg_xr_t1(int kp, void* x, void* r, const void* p, const void* w, long n, const double* alpha,
                      double* partial, hipStream_t st) {
     switch (kp) {
-        case ST_F64: cg_xr_t2<SX, double>(x, r, p, w, n, Vhp, alpha, partial, st); break;
-        case ST_F32: cg_xr_t2<SX, float>(x, r, p, w, n, Vhp, alpha, partial, st); break;
-        case ST_BF16: cg_xr_t2<SX, bf16s>(x, r, p, w, n, Vhp, alpha, partial, st); break;
+        case ST_F64: cg_xr_t2<SX, double>(x, r, p, w, n, alpha, partial, st); break;
+        case ST_F32: cg_xr_t2<SX, float>(x, r, p, w, n, alpha, partial, st); break;
+        case ST_BF16: cg_xr_t2<SX, bf16s>(x, r, p, w, n, alpha, partial, st); break;
         default: throw Error{DWF_EINVAL, "bad storage kind"};
     }
 }
 void cg_update_xr(int kx, int kp, void* x, void* r, const void* p, const void* w, long n,
-                  const double* alpha, double* partial, hipStream_t st, long Vhp) {
+                  const double* alpha, double* partial, hipStream_t st) {
     if (fpack_of(kx) != fpack_of(kp))
-        DWF_REQUIRE(Vhp > 0 && n % (4 * Vhp) == 0, DWF_EINVAL, "layout change needs the row stride");
-    DISPATCH1(kx, cg_xr_t1, kp, x, r, p, w, n, Vhp, alpha, partial, st);
+        DWF_REQUIRE(n % 64 == 0, DWF_EINVAL, "layout change needs whole tiles");
+    DISPATCH1(kx, cg_xr_t1, kp, x, r, p, w, n, alpha, partial, st);
     DWF_HIP(hipGetLastError());
 }
 
 template <class SR, class SP>
-static void cg_p_t2(void* p, const void* r, long n, long Vhp, const double* beta, hipStream_t st) {
+static void cg_p_t2(void* p, const void* r, long n, const double* beta, hipStream_t st) {
     if (fpack<SR>() == fpack<SP>())
         hipLaunchKernelGGL((cg_p_kernel<SR, SP>), dim3(blas_grid(n)), dim3(BLAS_THREADS), 0, st, p, r, n, beta);
     else
         hipLaunchKernelGGL((cg_p_remap_kernel<SR, SP>), dim3(blas_grid(n)), dim3(BLAS_THREADS), 0, st, p, r, n / 4,
-                           Vhp, beta);
+                           beta);
 }
 template <class SR>
-static void cg_p_t1(int kp, void* p, const void* r, long n, long Vhp, const double* beta, hipStream_t st) {
+static void cg_p_t1(int kp, void* p, const void* r, long n, const double* beta, hipStream_t st) {
     switch (kp) {
-        case ST_F64: cg_p_t2<SR, double>(p, r, n, Vhp, beta, st); break;
-        case ST_F32: cg_p_t2<SR, float>(p, r, n, Vhp, beta, st); break;
-        case ST_BF16: cg_p_t2<SR, bf16s>(p, r, n, Vhp, beta, st); break;
+        case ST_F64: cg_p_t2<SR, double>(p, r, n, beta, st); break;
+        case ST_F32: cg_p_t2<SR, float>(p, r, n, beta, st); break;
+        case ST_BF16: cg_p_t2<SR, bf16s>(p, r, n, beta, st); break;
         default: throw Error{DWF_EINVAL, "bad storage kind"};
     }
 }
-void cg_update_p(int kr, int kp, void* p, const void* r, long n, const double* beta, hipStream_t st, long Vhp) {
+void cg_update_p(int kr, int kp, void* p, const void* r, long n, const double* beta, hipStream_t st) {
     if (fpack_of(kr) != fpack_of(kp))
-        DWF_REQUIRE(Vhp > 0 && n % (4 * Vhp) == 0, DWF_EINVAL, "layout change needs the row stride");
-    DISPATCH1(kr, cg_p_t1, kp, p, r, n, Vhp, beta, st);
+        DWF_REQUIRE(n % 64 == 0, DWF_EINVAL, "layout change needs whole tiles");
+    DISPATCH1(kr, cg_p_t1, kp, p, r, n, beta, st);
     DWF_HIP(hipGetLastError());
 }
 
 template <class SX, class SP>
-static void cg_px_t2(void* x, void* p, const void* r, long n, long Vhp, const double* alpha, const double* beta,
+static void cg_px_t2(void* x, void* p, const void* r, long n, const double* alpha, const double* beta,
                      hipStream_t st) {
     if (fpack<SX>() == fpack<SP>())
         hipLaunchKernelGGL((cg_px_kernel<SX, SP>), dim3(blas_grid(n)), dim3(BLAS_THREADS), 0, st, x, p, r, n, alpha,
                            beta);
     else
         hipLaunchKernelGGL((cg_px_remap_kernel<SX, SP>), dim3(blas_grid(n)), dim3(BLAS_THREADS), 0, st, x, p, r,
-                           n / 4, Vhp, alpha, beta);
+                           n / 4, alpha, beta);
 }
 template <class SX>
-static void cg_px_t1(int kp, void* x, void* p, const void* r, long n, long Vhp, const double* alpha,
+static void cg_px_t1(int kp, void* x, void* p, const void* r, long n, const double* alpha,
                      const double* beta, hipStream_t st) {
     switch (kp) {
-        case ST_F64: cg_px_t2<SX, double>(x, p, r, n, Vhp, alpha, beta, st); break;
-        case ST_F32: cg_px_t2<SX, float>(x, p, r, n, Vhp, alpha, beta, st); break;
-        case ST_BF16: cg_px_t2<SX, bf16s>(x, p, r, n, Vhp, alpha, beta, st); break;
+        case ST_F64: cg_px_t2<SX, double>(x, p, r, n, alpha, beta, st); break;
+        case ST_F32: cg_px_t2<SX, float>(x, p, r, n, alpha, beta, st); break;
+        case ST_BF16: cg_px_t2<SX, bf16s>(x, p, r, n, alpha, beta, st); break;
         default: throw Error{DWF_EINVAL, "bad storage kind"};
     }
 }
 void cg_update_px(int kx, int kp, void* x, void* p, const void* r, long n, const double* alpha, const double* beta,
-                  hipStream_t st, long Vhp) {
+                  hipStream_t st) {
     if (fpack_of(kx) != fpack_of(kp))
-        DWF_REQUIRE(Vhp > 0 && n % (4 * Vhp) == 0, DWF_EINVAL, "layout change needs the row stride");
-    DISPATCH1(kx, cg_px_t1, kp, x, p, r, n, Vhp, alpha, beta, st);
+        DWF_REQUIRE(n % 64 == 0, DWF_EINVAL, "layout change needs whole tiles");
+    DISPATCH1(kx, cg_px_t1, kp, x, p, r, n, alpha, beta, st);
     DWF_HIP(hipGetLastError());
 }
 
 template <class SR, class SP>
-static void cg_p2_t2(void* pd, const void* ps, const void* r, long n, long Vhp, const double* beta, hipStream_t st) {
+static void cg_p2_t2(void* pd, const void* ps, const void* r, long n, const double* beta, hipStream_t st) {
     if constexpr (std::is_same<SR, float>::value && std::is_same<SP, float>::value) {
         if (n % 2 == 0) {
             const long n2 = n / 2;
@@ -979,28 +981,28 @@ static void cg_p2_t2(void* pd, const void* ps, const void* r, long n, long Vhp, 
         hipLaunchKernelGGL((cg_p2_kernel<SR, SP>), dim3(blas_grid(n)), dim3(BLAS_THREADS), 0, st, pd, ps, r, n, beta);
     else
         hipLaunchKernelGGL((cg_p2_remap_kernel<SR, SP>), dim3(blas_grid(n)), dim3(BLAS_THREADS), 0, st, pd, ps, r,
-                           n / 4, Vhp, beta);
+                           n / 4, beta);
 }
 template <class SR>
-static void cg_p2_t1(int kp, void* pd, const void* ps, const void* r, long n, long Vhp, const double* beta,
+static void cg_p2_t1(int kp, void* pd, const void* ps, const void* r, long n, const double* beta,
                      hipStream_t st) {
     switch (kp) {
-        case ST_F64: cg_p2_t2<SR, double>(pd, ps, r, n, Vhp, beta, st); break;
-        case ST_F32: cg_p2_t2<SR, float>(pd, ps, r, n, Vhp, beta, st); break;
-        case ST_BF16: cg_p2_t2<SR, bf16s>(pd, ps, r, n, Vhp, beta, st); break;
+        case ST_F64: cg_p2_t2<SR, double>(pd, ps, r, n, beta, st); break;
+        case ST_F32: cg_p2_t2<SR, float>(pd, ps, r, n, beta, st); break;
+        case ST_BF16: cg_p2_t2<SR, bf16s>(pd, ps, r, n, beta, st); break;
         default: throw Error{DWF_EINVAL, "bad storage kind"};
     }
 }
 void cg_update_p2(int kr, int kp, void* p_dst, const void* p_src, const void* r, long n, const double* beta,
-                  hipStream_t st, long Vhp) {
+                  hipStream_t st) {
     if (fpack_of(kr) != fpack_of(kp))
-        DWF_REQUIRE(Vhp > 0 && n % (4 * Vhp) == 0, DWF_EINVAL, "layout change needs the row stride");
-    DISPATCH1(kr, cg_p2_t1, kp, p_dst, p_src, r, n, Vhp, beta, st);
+        DWF_REQUIRE(n % 64 == 0, DWF_EINVAL, "layout change needs whole tiles");
+    DISPATCH1(kr, cg_p2_t1, kp, p_dst, p_src, r, n, beta, st);
     DWF_HIP(hipGetLastError());
 }
 
 template <class SX, class SP>
-static void cg_accx_t2(void* x, const void* ring, const double* alpha, int cnt, long n, long Vhp, hipStream_t st) {
+static void cg_accx_t2(void* x, const void* ring, const double* alpha, int cnt, long n, hipStream_t st) {
     if constexpr (std::is_same<SX, float>::value && std::is_same<SP, float>::value) {
         if (n % 2 == 0 && cnt <= 16) {
             const long n2 = n / 2;
@@ -1014,24 +1016,24 @@ static void cg_accx_t2(void* x, const void* ring, const double* alpha, int cnt, 
                            cnt, n);
     else
         hipLaunchKernelGGL((cg_accx_remap_kernel<SX, SP>), dim3(blas_grid(n)), dim3(BLAS_THREADS), 0, st, x, ring,
-                           alpha, cnt, n, n / 4, Vhp);
+                           alpha, cnt, n, n / 4);
 }
 template <class SX>
-static void cg_accx_t1(int kp, void* x, const void* ring, const double* alpha, int cnt, long n, long Vhp,
+static void cg_accx_t1(int kp, void* x, const void* ring, const double* alpha, int cnt, long n,
                        hipStream_t st) {
     switch (kp) {
-        case ST_F64: cg_accx_t2<SX, double>(x, ring, alpha, cnt, n, Vhp, st); break;
-        case ST_F32: cg_accx_t2<SX, float>(x, ring, alpha, cnt, n, Vhp, st); break;
-        case ST_BF16: cg_accx_t2<SX, bf16s>(x, ring, alpha, cnt, n, Vhp, st); break;
+        case ST_F64: cg_accx_t2<SX, double>(x, ring, alpha, cnt, n, st); break;
+        case ST_F32: cg_accx_t2<SX, float>(x, ring, alpha, cnt, n, st); break;
+        case ST_BF16: cg_accx_t2<SX, bf16s>(x, ring, alpha, cnt, n, st); break;
         default: throw Error{DWF_EINVAL, "bad storage kind"};
     }
 }
 void cg_accumulate_x(int kx, int kp, void* x, const void* p_ring, const double* alpha, int cnt, long n,
-                     hipStream_t st, long Vhp) {
+                     hipStream_t st) {
     if (cnt <= 0) return;
     if (fpack_of(kx) != fpack_of(kp))
-        DWF_REQUIRE(Vhp > 0 && n % (4 * Vhp) == 0, DWF_EINVAL, "layout change needs the row stride");
-    DISPATCH1(kx, cg_accx_t1, kp, x, p_ring, alpha, cnt, n, Vhp, st);
+        DWF_REQUIRE(n % 64 == 0, DWF_EINVAL, "layout change needs whole tiles");
+    DISPATCH1(kx, cg_accx_t1, kp, x, p_ring, alpha, cnt, n, st);
     DWF_HIP(hipGetLastError());
 }
 
@@ -1044,9 +1046,9 @@ void caxpy(int kind, void* y, const void* x, long n, double ar, double ai, hipSt
     DWF_HIP(hipGetLastError());
 }
 
-void random_fill_f64(void* v, long rows, long Vh, long Vhp, unsigned long long seed, hipStream_t st) {
+void random_fill_f64(void* v, long rows, long Vh, unsigned long long seed, hipStream_t st) {
     hipLaunchKernelGGL(random_fill_kernel, dim3(blas_grid(rows * Vh)), dim3(BLAS_THREADS), 0, st, (double2*)v, rows,
-                       Vh, Vhp, seed);
+                       Vh, seed);
     DWF_HIP(hipGetLastError());
 }
 

@@ -1,21 +1,16 @@
 // Internal declarations of libdwf (host and device).
 //
-// Internal field layout ("half field"): for one parity, one right-hand side,
-//   elem[(s*12 + comp)*Vhp + site], comp = spin*3 + colour, site = internal
-// site index of that parity (see build_geometry: spatial bricks of about
-// 8^3, swept in t; lex_of_site gives the lexicographic site),
-// complex stored as (re, im) pairs of the storage type.  Multi-RHS fields put
-// the RHS index outermost: elem[((r*Ls + s)*12 + comp)*Vhp + site].
-// Vhp >= Vh is the padded row stride (32 times an odd number): with a
-// power-of-two stride every row of a site falls into the same L2 set and
-// the hop thrashes the cache by conflict.  Padding entries stay zero.
+// Internal field ("half field"): one parity, one right-hand side, Ls slices of
+// 12 components (spin * 3 + colour) at the internal sites of that parity (see
+// build_geometry; lex_of_site gives the lexicographic site), complex stored as
+// (re, im) pairs of the storage type.  Multi-RHS fields put the RHS index
+// outermost.  Sites come in tiles of 16 whose data are contiguous (precision.h);
+// Vhp is Vh rounded up to whole tiles, and padding entries stay zero.
 //
-// Links per output parity p ("hop links"):
-//   link[((p*8 + d)*9 + row*3 + col)*Vhp + site],
-//   d = 0..3: U_mu(x) (forward hop to x+mu), d = 4..7: U_mu(x-mu)^dag,
-// with the antiperiodic time phase folded in.
-// Neighbours: nbr[(p*8 + d)*Vhp + site] = internal index (other parity) of x+mu
-// (d < 4) or x-mu (d >= 4).
+// Links per output parity p ("hop links"), directions d = 0..3: U_mu(x) (forward
+// hop to x+mu), d = 4..7: U_mu(x-mu)^dag, with the antiperiodic time phase folded
+// in.  Neighbours: internal index (other parity) of x+mu (d < 4) or x-mu (d >= 4).
+// Both are tables of the same tiles, parity 0 first.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -107,8 +102,8 @@ struct DevBuf {
 // allocation of the library finds no memory.  A call takes its own buffers, so
 // calls from several threads never share one.
 struct ScratchPool {
-    // half fields by StoreKind; two-slice FP64 fields; scalars; half fields of the 5D split (no padding)
-    enum Class { F64 = 0, F32 = 1, BF16 = 2, PAIR = 3, SMALL = 4, EO5 = 5, EO5_F32 = 6, NCLASS };
+    // half fields by StoreKind; two-slice FP64 fields; scalars
+    enum Class { F64 = 0, F32 = 1, BF16 = 2, PAIR = 3, SMALL = 4, NCLASS };
     static constexpr size_t MAX_IDLE = 6;
     std::mutex mu;
     std::vector<DevBuf> idle[NCLASS];
@@ -163,11 +158,11 @@ enum StoreKind { ST_F64 = 0, ST_F32 = 1, ST_BF16 = 2 };
 struct dwf_lattice {
     int dims[4];
     int antiperiodic_t;
-    long V, Vh, Vhp;   // sites, sites per parity, padded row stride
+    long V, Vh, Vhp;   // sites, sites per parity, those rounded up to whole tiles
     int brick[3] = {0, 0, 0};       // spatial brick extents of the internal site order
     int site_order = 0;             // 0 bricks swept in t, 1 t columns (build_geometry)
     std::vector<int> lex_of_site;   // host [2][Vh]: lexicographic index of internal site
-    std::vector<int> nbr_host;    // host [2][8][Vh]
+    std::vector<int> nbr_host;    // host copy of nbr
     dwf::DevBuf nbr;              // device [2][8][Vh]
     dwf::DevBuf lex_of_site_dev;    // device [2][Vh]
     dwf::DevBuf links[3];         // per storage kind: [2][8][9][Vh] complex
@@ -229,10 +224,5 @@ struct PairScratch : Scratch {
 };
 struct SmallScratch : Scratch {
     SmallScratch(const dwf_op* op, size_t bytes) : Scratch(op->scratch, ScratchPool::SMALL, bytes) {}
-};
-// half field of the 5D split, storage kind F64 or F32
-struct Eo5Scratch : Scratch {
-    Eo5Scratch(const dwf_op* op, int kind)
-        : Scratch(op->scratch, ScratchPool::EO5 + kind, (size_t)op->Ls * 12 * op->lat->Vh * (kind == 0 ? 16 : 8)) {}
 };
 }  // namespace dwf

@@ -12,9 +12,8 @@
 // eq. even-odd_linear_equation needs no dense fifth-dimension algebra.
 //
 // Half fields of 5D parity P: slice s holds the 4D sites of parity
-// (P + s) mod 2 in the lattice's internal site order, in the component groups
-// of the 4D half fields (precision.h) with row stride Vh (pack_eo5, unpack_eo5
-// in blas.h).  The 4D neighbours of such a site at
+// (P + s) mod 2 in the lattice's internal site order, in the layout of
+// the 4D half fields (pack_eo5, unpack_eo5 in blas.h).  The 4D neighbours of such a site at
 // slice s, and the same site at slices s -/+ 1, are then entries of the
 // opposite half field at the indices of the 4D tables.
 #pragma once
@@ -34,7 +33,7 @@ struct Eo5Params {
     const void* in;
     const void* loc;        // nullptr: no local term
     const void* links;      // the lattice's hop links of this storage kind (both output parities)
-    const int* nbr;         // [2][8][Vhp]
+    const int* nbr;         // the lattice's neighbour table (both output parities)
     const double* coef;     // EO5_NCOEF doubles
     long Vh, Vhp, lpar;     // lpar: complex link elements of one output parity
     int Ls, par;            // par: 5D parity of the output
@@ -47,7 +46,7 @@ struct Eo5Params {
 // out = a loc + sgn D_{P,P'} in with the scalings of Eo5Params (kind F64 or F32).
 void launch_eo5(int kind, const Eo5Params& P, hipStream_t st);
 // out = M_ss(chirality) in over one FP64 half field (the 5D-diagonal block)
-void eo5_diag(void* out, const void* in, const double* coef, long Vh, int Ls, hipStream_t st);
+void eo5_diag(void* out, const void* in, const double* coef, long Vhp, int Ls, hipStream_t st);
 
 // host side (eo5d_solve.cpp)
 // FP64 coefficients of op; throws DWF_EINVAL unless every c_s is 0 and Ls is even

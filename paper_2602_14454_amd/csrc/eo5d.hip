@@ -72,13 +72,13 @@ __device__ __forceinline__ void reconstruct(T sg, const T (&v)[12], T (&acc)[24]
 
 }  // namespace
 
-// the 12 components of slice s at site j (row stride Vh)
+// the 12 components of slice s at site j
 template <class T>
-__device__ __forceinline__ void load_site(const void* f, int s, long j, long Vh, T (&v)[24]) {
+__device__ __forceinline__ void load_site(const void* f, int s, long j, int Ls, T (&v)[24]) {
 #pragma unroll
     for (int g = 0; g < 3; ++g) {
         T q[8];
-        load4<T>(f, (long)s * 3 + g, j, Vh, q);
+        load4<T>(f, gidx(s * 3 + g, j, Ls * 3), q);
 #pragma unroll
         for (int k = 0; k < 8; ++k) v[8 * g + k] = q[k];
     }
@@ -88,13 +88,13 @@ template <int MU, class T>
 __device__ __forceinline__ void eo5_direction(const Eo5Params& P, const void* lk, int d, T sg, int s, int q, long i,
                                               const T (&cin)[2], T (&acc)[24]) {
     constexpr int CB = 2 * (int)sizeof(T), LP = link_lp(CB), NG = link_ng(CB);
-    const long j = P.nbr[((long)q * 8 + d) * P.Vhp + i];
+    const long j = P.nbr[(long)q * 8 * P.Vhp + gidx(d, i, 8)];
     T p[24], u[18], w[12], v[12];
-    load_site<T>(P.in, s, j, P.Vh, p);
+    load_site<T>(P.in, s, j, P.Ls, p);
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
         static_assert(LP * CB == 16, "16-byte link groups expected");
-        const u32x4 x = static_cast<const u32x4*>(lk)[((long)d * NG + g) * P.Vhp + i];
+        const u32x4 x = static_cast<const u32x4*>(lk)[gidx(d * NG + g, i, 8 * NG)];
         decode_link_group<T>(x, g, u);
     }
     project<MU, T>(sg, p, cin, w);
@@ -184,14 +184,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
             c[chi] = T(m) * (P.pre ? T(MINV[chi * 16 + sq]) : T(1));
         }
         T v[24];
-        load_site<T>(P.in, sq, i, Vh, v);
+        load_site<T>(P.in, sq, i, Ls, v);
 #pragma unroll
         for (int k = 0; k < 24; ++k) acc[k] = fma(k < 12 ? c[0] : c[1], v[k], acc[k]);
     }
     const T mo[2] = {T(MINV[0 * 16 + s]), T(MINV[1 * 16 + s])};
     const T sgn = T(P.sgn), a = T(P.a);
     T l[24];
-    if (P.loc) load_site<T>(P.loc, s, i, Vh, l);
+    if (P.loc) load_site<T>(P.loc, s, i, Ls, l);
 #pragma unroll
     for (int g = 0; g < 3; ++g) {
         T o[8];
@@ -206,16 +206,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
             }
             o[k8] = r;
         }
-        store4<T>(P.out, (long)s * 3 + g, i, Vh, o);
+        store4<T>(P.out, gidx(s * 3 + g, i, Ls * 3), o);
     }
 }
 
-__global__ __launch_bounds__(256) void eo5_diag_kernel(double2* out, const double2* in, const double* coef, long Vh,
+__global__ __launch_bounds__(256) void eo5_diag_kernel(double2* out, const double2* in, const double* coef, long n,
                                                        int Ls) {
     const long t = (long)blockIdx.x * 256 + threadIdx.x;
-    if (t >= (long)Ls * Vh * 12) return;
-    const long sk = t / Vh;
-    const int s = (int)(sk / 12), k = (int)(sk - (long)s * 12);
+    if (t >= n) return;
+    const int row = (int)((t >> 4) % (Ls * 12));
+    const int s = row / 12, k = row - s * 12;
     const int chi = k < 6 ? 0 : 1;
     const double m = coef[EO5_M + (chi * 16 + s) * 16 + s];
     out[t] = make_double2(m * in[t].x, m * in[t].y);
@@ -234,11 +234,11 @@ void launch_eo5(int kind, const Eo5Params& P, hipStream_t st) {
     DWF_HIP(hipGetLastError());
 }
 
-void eo5_diag(void* out, const void* in, const double* coef, long Vh, int Ls, hipStream_t st) {
-    const long n = (long)Ls * Vh * 12;
+void eo5_diag(void* out, const void* in, const double* coef, long Vhp, int Ls, hipStream_t st) {
+    const long n = (long)Ls * 12 * Vhp;
     if (n == 0) return;
     hipLaunchKernelGGL(eo5_diag_kernel, dim3(grid_of(n)), dim3(256), 0, st, static_cast<double2*>(out),
-                       static_cast<const double2*>(in), coef, Vh, Ls);
+                       static_cast<const double2*>(in), coef, n, Ls);
     DWF_HIP(hipGetLastError());
 }
 

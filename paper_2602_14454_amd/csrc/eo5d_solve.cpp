@@ -167,10 +167,10 @@ void apply_eo5_schur(const dwf_op* op, int kind, int dagger, void* out5, const v
     SmallScratch coef(op, sizeof hc);
     DWF_HIP(hipMemcpyAsync(coef.p, hc, sizeof hc, hipMemcpyHostToDevice, st));
     const int* lex = L->lex_of_site_dev.as<int>();
-    Eo5Scratch ek(op, kind), ok(op, kind), tk(op, kind);
-    pack_eo5(kind, ek.p, nullptr, in5, lex, L->Vh, L->V, op->Ls, st);
+    FieldScratch ek(op, kind), ok(op, kind), tk(op, kind);
+    pack_eo5(kind, ek.p, nullptr, in5, lex, L->Vh, L->Vhp, L->V, op->Ls, st);
     eo5_dhat(op, kind, dagger, ok.p, ek.p, tk.p, coef.as<double>(), st);
-    unpack_eo5(kind, out5, ok.p, nullptr, lex, L->Vh, L->V, op->Ls, st);
+    unpack_eo5(kind, out5, ok.p, nullptr, lex, L->Vh, L->Vhp, L->V, op->Ls, st);
     DWF_HIP(hipStreamSynchronize(st));
 }
 
@@ -178,9 +178,9 @@ int solve_eo5(const dwf_op* op, void* x5, const void* b5, const dwf_solve_params
               hipStream_t st) {
     const dwf_lattice* L = op->lat;
     DWF_REQUIRE(L->has_gauge, DWF_ESTATE, "gauge field not set");
-    const long Vh = L->Vh, V = L->V;
+    const long Vh = L->Vh, Vhp = L->Vhp, V = L->V;
     const int Ls = op->Ls;
-    const long n = (long)Ls * Vh * 12;
+    const long n = (long)Ls * 12 * Vhp;
     int kp = ST_F64;
     if (prm->algo == DWF_ALGO_DC || prm->paper_mode) kp = prm->inner_prec;
     DWF_REQUIRE(kp == ST_F64 || kp == ST_F32, DWF_EINVAL, "the 5D even-odd split runs its CG in FP64 or FP32");
@@ -209,7 +209,7 @@ int solve_eo5(const dwf_op* op, void* x5, const void* b5, const dwf_solve_params
     DWF_HIP(hipEventCreate(&e1));
     DWF_HIP(hipEventRecord(e0, st));
     const int* lex = L->lex_of_site_dev.as<int>();
-    pack_eo5(ST_F64, be.p, bo.p, b5, lex, Vh, V, Ls, st);
+    pack_eo5(ST_F64, be.p, bo.p, b5, lex, Vh, Vhp, V, Ls, st);
     const double b2 = norm2_of(ST_F64, be.p, n, pp, sc, hs, st) + norm2_of(ST_F64, bo.p, n, pp, sc, hs, st);
     // b~_e = D_ee^-1 b_e - D_ee^-1 D_eo D_oo^-1 b_o
     piece(op, ST_F64, 0, 0, 1, 1, 1, 1.0, -1.0, bt.p, bo.p, be.p, cf, st);
@@ -231,7 +231,7 @@ int solve_eo5(const dwf_op* op, void* x5, const void* b5, const dwf_solve_params
     }
     while (!converged && total < maxiter && outer < 100) {
         Eo5Cg& W = cg_of(kp);
-        convert(kp, ST_F64, W.rin.p, rh.p, n, st, Vh);
+        convert(kp, ST_F64, W.rin.p, rh.p, n, st);
         const bool plain = prm->paper_mode || (kp == ST_F64 && outer == 0);
         const double itol = plain ? inner_tol : dc_target(tol, rel5, kp, inner_tol, f_ratio);
         const int it = cgnr5(op, W, cf, itol, maxiter - total, prm->check_every, pp, sc, hs, st, &last_inner_rel,
@@ -239,13 +239,13 @@ int solve_eo5(const dwf_op* op, void* x5, const void* b5, const dwf_solve_params
         total += it;
         ++outer;
         if (nan_seen) break;
-        convert(ST_F64, kp, te.p, W.x.p, n, st, Vh);
+        convert(ST_F64, kp, te.p, W.x.p, n, st);
         axpby(ST_F64, ST_F64, xe.p, te.p, n, nullptr, 1.0, nullptr, 1.0, nullptr, st);
         // r^ = b~ - D^5 x_e (FP64); the 5D residual is (D_ee r^, 0) after reconstruction
         eo5_dhat(op, ST_F64, 0, te.p, xe.p, to.p, cf, st);
         axpby(ST_F64, ST_F64, te.p, bt.p, n, nullptr, 1.0, nullptr, -1.0, nullptr, st);
         std::swap(rh, te);
-        eo5_diag(te.p, rh.p, cf, Vh, Ls, st);
+        eo5_diag(te.p, rh.p, cf, Vhp, Ls, st);
         const double rel5_old = rel5;
         rel5 = b2 > 0 ? std::sqrt(norm2_of(ST_F64, te.p, n, pp, sc, hs, st) / b2) : 0.0;
         f_ratio = dc_ratio(rel5 / rel5_old, itol);
@@ -265,7 +265,7 @@ int solve_eo5(const dwf_op* op, void* x5, const void* b5, const dwf_solve_params
     }
     // x_o = D_oo^-1 b_o - D_oo^-1 D_oe x_e
     piece(op, ST_F64, 1, 0, 0, 1, 1, 1.0, -1.0, xo.p, xe.p, bo.p, cf, st);
-    unpack_eo5(ST_F64, x5, xe.p, xo.p, lex, Vh, V, Ls, st);
+    unpack_eo5(ST_F64, x5, xe.p, xo.p, lex, Vh, Vhp, V, Ls, st);
     DWF_HIP(hipEventRecord(e1, st));
     DWF_HIP(hipEventSynchronize(e1));
     float ms = 0;

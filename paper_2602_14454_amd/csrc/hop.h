@@ -27,7 +27,7 @@ struct HopParams {
     const void* locmix2;   // dense LOCMIX2 (required with out2 and loc)
     double* partial;       // per-block FP64 partial norms (nullptr: none)
     long Vh;               // sites of the output parity
-    long Vhp;              // padded row stride of fields, links and neighbour table
+    long Vhp;              // sites rounded up to whole tiles of 16
     int Ls;
     int pre_mode;          // 0 identity, 1 diagonal d, 2 d + e (K sparsity)
     int reduce;            // 1: |out|^2, 2: |out2|^2, 3: |upd|^2 after the update

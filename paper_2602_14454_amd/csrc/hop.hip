@@ -32,8 +32,7 @@ __global__ __launch_bounds__(256) void mix_mfma_kernel(MixParams P) {
     const long site = ((long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 16 + j;
     const bool valid = site < Vh;
     const long sx = valid ? site : Vh - 1;
-    const long Vhp = P.Vhp;
-    const long roff = (long)blockIdx.y * Ls * 12 * Vhp;
+    const long rows = (long)Ls * 12, roff = (long)blockIdx.y * rows * P.Vhp;
     const R* A = static_cast<const R*>(P.mat);
     R a[2][KK];
 #pragma unroll
@@ -49,7 +48,7 @@ __global__ __launch_bounds__(256) void mix_mfma_kernel(MixParams P) {
         for (int kk = 0; kk < KK; ++kk) {
             const int s = sc + 4 * kk;
             R xr = 0, xi = 0;
-            if (s < Ls) cload<S>(P.in, roff + fidx((long)s * 12 + cp, sx, Vhp, fpack<S>()), xr, xi);
+            if (s < Ls) cload<S>(P.in, roff + fidx((long)s * 12 + cp, sx, rows, fpack<S>()), xr, xi);
             cr = mfma4(a[chi][kk], xr, cr);
             ci = mfma4(a[chi][kk], xi, ci);
         }
@@ -57,7 +56,7 @@ __global__ __launch_bounds__(256) void mix_mfma_kernel(MixParams P) {
         for (int i = 0; i < 4; ++i) {
             const int s = out_row<R>(sc, i);
             if (valid && s < Ls) {
-                cstore<S>(P.out, roff + fidx((long)s * 12 + cp, site, Vhp, fpack<S>()), cr[i], ci[i]);
+                cstore<S>(P.out, roff + fidx((long)s * 12 + cp, site, rows, fpack<S>()), cr[i], ci[i]);
                 nrm += double(cr[i]) * double(cr[i]) + double(ci[i]) * double(ci[i]);
             }
         }

@@ -42,14 +42,16 @@ namespace dwf {
 
 // Tuning knobs (compile time): occupancy target per precision, 4-slice
 // groups per wave in the hop phase (KPW > 1: each link load serves KPW
-// groups), unrolling of the direction loop, and whether the 8 neighbour
-// indices are loaded up front.  Defaults are the best of sweeps on MI355X:
-// one slice group per wave; the single-lattice kernels run the pipelined
+// groups), and unrolling of the direction loop.  Defaults are the best of
+// sweeps on MI355X: one slice group per wave; the single-lattice kernels run the pipelined
 // direction loop (below) in FP32 at 4 waves per SIMD (<= 127 VGPRs) and in
 // BF16 at 5 (<= 95), FP64 runs the rolled loop at 3 (<= 168); without the
 // pipelining, unrolling only lets the compiler hoist the loads of several
 // directions and spill.  The work-list kernels, whose pre-mix mode is a
-// runtime value, keep 4 waves (FP64: 2).
+// runtime value, keep 4 waves (FP64: 2).  The hop on 24^3x48, Ls = 16, takes
+// FP32 368, BF16 252 and FP64 812 us; the figures at the single switches below
+// were measured one by one, most of them while fields lay in rows over all sites
+// (410, 265 and 869 us; precision.h).
 #ifndef DWF_HOP_WAVES_PER_EU
 #define DWF_HOP_WAVES_PER_EU 4
 #endif
@@ -75,9 +77,6 @@ namespace dwf {
 #ifndef DWF_HOP_KPW64
 #define DWF_HOP_KPW64 1
 #endif
-#ifndef DWF_HOP_NBR_PRELOAD
-#define DWF_HOP_NBR_PRELOAD 1
-#endif
 // Software pipelining of the direction loop: the neighbour spinors of
 // direction d+1 are loaded (raw 16-byte groups, decoded at use) while
 // direction d is computed, so every wave keeps one direction's loads in
@@ -94,13 +93,6 @@ namespace dwf {
 #endif
 #ifndef DWF_HOP_PREFETCH64
 #define DWF_HOP_PREFETCH64 0
-#endif
-// Pipelined loop: request the first two directions' neighbour spinors in the
-// block prologue, together with the link staging loads, instead of after the
-// block barrier that publishes the staged tables.  Measured slower (FP32 hop
-// 409 -> 419 us on 24^3x48, Ls = 16): off.
-#ifndef DWF_HOP_EARLY
-#define DWF_HOP_EARLY 0
 #endif
 // Staging of the tile's links and neighbour indices with every load issued
 // before the first LDS write (1), or as a loop over the block's threads (0:
@@ -163,12 +155,6 @@ namespace dwf {
 #ifndef DWF_HOP_COEF_HOIST
 #define DWF_HOP_COEF_HOIST 2
 #endif
-// Stage the block's links and neighbour indices in LDS once (all lanes of a
-// block need the same 16 sites' links; loaded per lane they would be fetched
-// by every slice group of every wave).
-#ifndef DWF_HOP_LDS_LINKS
-#define DWF_HOP_LDS_LINKS 1
-#endif
 // FP32/BF16: stage the local-term field of the tile in LDS with 16-byte loads
 // at block start, and write the outputs through an LDS tile so that every
 // global store is a whole 16-byte group (the MFMA leaves one complex number
@@ -190,6 +176,8 @@ namespace dwf {
 #ifndef DWF_HOP_LOC_LDS32
 #define DWF_HOP_LOC_LDS32 0
 #endif
+// one 16-byte group of the 16 sites of a tile
+constexpr unsigned GRB = 256;
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef double v4d __attribute__((ext_vector_type(4)));
 
@@ -363,8 +351,7 @@ struct HopRes {
 };
 
 template <class S, int G, int PM>
-__device__ __forceinline__ void hop_direction(const HopParams& P, const HopRes& R_, unsigned gb, unsigned sx,
-                                              int D, unsigned ynb, const int (&s)[G],
+__device__ __forceinline__ void hop_direction(const HopParams& P, const HopRes& R_, int D, const int (&s)[G],
                                               const typename Traits<S>::R (&pd)[G][2],
                                               const typename Traits<S>::R (&pe)[G][2],
                                               const typename Traits<S>::R (&kr)[G],
@@ -374,21 +361,12 @@ __device__ __forceinline__ void hop_direction(const HopParams& P, const HopRes& 
     constexpr unsigned CB = cbytes<S>();
     constexpr unsigned NG = link_ng(CB);
     const int Ls = P.Ls;
-    const unsigned Vhp = (unsigned)P.Vhp;
     R U[18];
-    unsigned y;
-    if constexpr (DWF_HOP_LDS_LINKS) {
-        y = lnbr[D * 16 + j];
+    const unsigned yg = lnbr[D * 16 + j];      // byte offset of the neighbour's groups
 #pragma unroll
-        for (unsigned g = 0; g < NG; ++g) decode_link_group<S>(lnk[(D * NG + g) * 16 + j], (int)g, U);
-    } else {
-        y = DWF_HOP_NBR_PRELOAD ? ynb : __builtin_amdgcn_raw_buffer_load_b32(R_.nbr, sx * 4u, (unsigned)D * Vhp * 4u, 0);
-        constexpr unsigned LGB = link_lp(CB) * CB;   // bytes of one link group per site
-        bload_link<S>(R_.links, sx * LGB, (unsigned)D * NG * Vhp * LGB, Vhp * LGB, U);
-    }
+    for (unsigned g = 0; g < NG; ++g) decode_link_group<S>(lnk[(D * NG + g) * 16 + j], (int)g, U);
     constexpr int PK = fpack<S>();             // components per group
     constexpr int NGR = 12 / PK;               // groups per slice
-    const unsigned yg = y * (unsigned)PK * CB; // byte offset of the neighbour in a group row
 #pragma unroll
     for (int g = 0; g < G; ++g) {
         // Slices beyond Ls (Ls not a multiple of 4) read slice 0 (finite
@@ -397,12 +375,12 @@ __device__ __forceinline__ void hop_direction(const HopParams& P, const HopRes& 
         const int sg_ = s[g] < Ls ? s[g] : 0;
         R p[24];
         // lane-dependent offsets (site, slice) go to the vector operand, the
-        // wave-uniform group offset to the scalar one
-        const unsigned vb = yg + (unsigned)sg_ * NGR * gb;
+        // group's to the immediate one
+        const unsigned vb = yg + (unsigned)sg_ * NGR * GRB;
 #pragma unroll
         for (int q = 0; q < NGR; ++q) {
             R v[8];
-            bload_group<S>(R_.in, vb, (unsigned)q * gb, v);
+            bload_group<S>(R_.in, vb + (unsigned)q * GRB, 0u, v);
 #pragma unroll
             for (int k = 0; k < 2 * PK; ++k) p[2 * PK * q + k] = v[k];
         }
@@ -416,13 +394,13 @@ __device__ __forceinline__ void hop_direction(const HopParams& P, const HopRes& 
             // K pattern: upper chirality (components 0-5) couples s-1, lower
             // (6-11) s+1 (cyclic); groups that straddle the boundary are read
             // from both slices
-            const unsigned sm = (unsigned)(sg_ == 0 ? Ls - 1 : sg_ - 1) * NGR * gb;
-            const unsigned sp = (unsigned)(sg_ == Ls - 1 ? 0 : sg_ + 1) * NGR * gb;
+            const unsigned sm = (unsigned)(sg_ == 0 ? Ls - 1 : sg_ - 1) * NGR * GRB;
+            const unsigned sp = (unsigned)(sg_ == Ls - 1 ? 0 : sg_ + 1) * NGR * GRB;
 #pragma unroll
             for (int q = 0; q < NGR; ++q) {
                 if (PK * q < 6) {
                     R v[8];
-                    bload_group<S>(R_.in, yg + sm, (unsigned)q * gb, v);
+                    bload_group<S>(R_.in, yg + sm + (unsigned)q * GRB, 0u, v);
 #pragma unroll
                     for (int k = 0; k < PK; ++k)
                         if (PK * q + k < 6) {
@@ -432,7 +410,7 @@ __device__ __forceinline__ void hop_direction(const HopParams& P, const HopRes& 
                 }
                 if (PK * q + PK > 6) {
                     R v[8];
-                    bload_group<S>(R_.in, yg + sp, (unsigned)q * gb, v);
+                    bload_group<S>(R_.in, yg + sp + (unsigned)q * GRB, 0u, v);
 #pragma unroll
                     for (int k = 0; k < PK; ++k)
                         if (PK * q + k >= 6) {
@@ -470,35 +448,28 @@ __device__ __forceinline__ void decode_group(u32x4 w, typename Traits<S>::R (&v)
     }
 }
 
-// neighbour site index y given (hop_fetch_at) or read from the staged table
 template <class S, int G>
-__device__ __forceinline__ void hop_fetch_at(const HopParams& P, const HopRes& R_, unsigned gb, unsigned y,
-                                             const int (&s)[G], u32x4 (&raw)[G][12 / fpack<S>()], unsigned& yg) {
+__device__ __forceinline__ void hop_fetch(const HopParams& P, const HopRes& R_, int D, const int (&s)[G],
+                                          const unsigned* lnbr, int j, u32x4 (&raw)[G][12 / fpack<S>()],
+                                          unsigned& yg) {
     constexpr unsigned CB = cbytes<S>();
     constexpr int PK = fpack<S>();
     constexpr int NGR = 12 / PK;
     static_assert(PK * CB == 16, "16-byte field groups expected");
-    yg = y * (unsigned)PK * CB;
+    yg = lnbr[D * 16 + j];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
         const int sg_ = s[g] < P.Ls ? s[g] : 0;   // slices past Ls read slice 0 (zeroed later)
-        const unsigned vb = yg + (unsigned)sg_ * NGR * gb;
+        const unsigned vb = yg + (unsigned)sg_ * NGR * GRB;
 #pragma unroll
-        for (int q = 0; q < NGR; ++q) raw[g][q] = __builtin_amdgcn_raw_buffer_load_b128(R_.in, vb, (unsigned)q * gb, 0);
+        for (int q = 0; q < NGR; ++q) raw[g][q] = __builtin_amdgcn_raw_buffer_load_b128(R_.in, vb + (unsigned)q * GRB, 0, 0);
     }
-}
-
-template <class S, int G>
-__device__ __forceinline__ void hop_fetch(const HopParams& P, const HopRes& R_, unsigned gb, int D, const int (&s)[G],
-                                          const unsigned* lnbr, int j, u32x4 (&raw)[G][12 / fpack<S>()],
-                                          unsigned& yg) {
-    hop_fetch_at<S, G>(P, R_, gb, lnbr[D * 16 + j], s, raw, yg);
 }
 
 // Mode 2's extra reads of the same direction: slice s-1 for the upper
 // chirality's groups, s+1 for the lower one's.
 template <class S, int G>
-__device__ __forceinline__ void hop_fetch2(const HopParams& P, const HopRes& R_, unsigned gb, const int (&s)[G],
+__device__ __forceinline__ void hop_fetch2(const HopParams& P, const HopRes& R_, const int (&s)[G],
                                            unsigned yg, u32x4 (&rm)[G][12 / fpack<S>()],
                                            u32x4 (&rp)[G][12 / fpack<S>()]) {
     constexpr int PK = fpack<S>();
@@ -506,19 +477,19 @@ __device__ __forceinline__ void hop_fetch2(const HopParams& P, const HopRes& R_,
 #pragma unroll
     for (int g = 0; g < G; ++g) {
         const int sg_ = s[g] < P.Ls ? s[g] : 0;
-        const unsigned sm = (unsigned)(sg_ == 0 ? P.Ls - 1 : sg_ - 1) * NGR * gb;
-        const unsigned sp = (unsigned)(sg_ == P.Ls - 1 ? 0 : sg_ + 1) * NGR * gb;
+        const unsigned sm = (unsigned)(sg_ == 0 ? P.Ls - 1 : sg_ - 1) * NGR * GRB;
+        const unsigned sp = (unsigned)(sg_ == P.Ls - 1 ? 0 : sg_ + 1) * NGR * GRB;
 #pragma unroll
         for (int q = 0; q < NGR; ++q) {
-            if (PK * q < 6) rm[g][q] = __builtin_amdgcn_raw_buffer_load_b128(R_.in, yg + sm, (unsigned)q * gb, 0);
-            if (PK * q + PK > 6) rp[g][q] = __builtin_amdgcn_raw_buffer_load_b128(R_.in, yg + sp, (unsigned)q * gb, 0);
+            if (PK * q < 6) rm[g][q] = __builtin_amdgcn_raw_buffer_load_b128(R_.in, yg + sm + (unsigned)q * GRB, 0, 0);
+            if (PK * q + PK > 6) rp[g][q] = __builtin_amdgcn_raw_buffer_load_b128(R_.in, yg + sp + (unsigned)q * GRB, 0, 0);
         }
     }
 }
 
 // PRE2: the rows s-1 and s+1 of mode 2 were fetched ahead too (rm, rp; hop_fetch2).
 template <class S, int G, int PM, bool PRE2 = false>
-__device__ __forceinline__ void hop_apply(const HopParams& P, const HopRes& R_, unsigned gb, int D, const int (&s)[G],
+__device__ __forceinline__ void hop_apply(const HopParams& P, const HopRes& R_, int D, const int (&s)[G],
                                           const typename Traits<S>::R (&pd)[G][2],
                                           const typename Traits<S>::R (&pe)[G][2],
                                           const typename Traits<S>::R (&kr)[G],
@@ -551,14 +522,14 @@ __device__ __forceinline__ void hop_apply(const HopParams& P, const HopRes& R_, 
             for (int k = 0; k < 12; ++k) p[k] *= pd[g][0];
 #pragma unroll
             for (int k = 12; k < 24; ++k) p[k] *= pd[g][1];
-            const unsigned sm = (unsigned)(sg_ == 0 ? Ls - 1 : sg_ - 1) * NGR * gb;
-            const unsigned sp = (unsigned)(sg_ == Ls - 1 ? 0 : sg_ + 1) * NGR * gb;
+            const unsigned sm = (unsigned)(sg_ == 0 ? Ls - 1 : sg_ - 1) * NGR * GRB;
+            const unsigned sp = (unsigned)(sg_ == Ls - 1 ? 0 : sg_ + 1) * NGR * GRB;
 #pragma unroll
             for (int q = 0; q < NGR; ++q) {
                 if (PK * q < 6) {
                     R v[8];
                     if constexpr (PRE2) decode_group<S>(rm[g][q], v);
-                    else bload_group<S>(R_.in, yg + sm, (unsigned)q * gb, v);
+                    else bload_group<S>(R_.in, yg + sm + (unsigned)q * GRB, 0u, v);
 #pragma unroll
                     for (int k = 0; k < PK; ++k)
                         if (PK * q + k < 6) {
@@ -569,7 +540,7 @@ __device__ __forceinline__ void hop_apply(const HopParams& P, const HopRes& R_, 
                 if (PK * q + PK > 6) {
                     R v[8];
                     if constexpr (PRE2) decode_group<S>(rp[g][q], v);
-                    else bload_group<S>(R_.in, yg + sp, (unsigned)q * gb, v);
+                    else bload_group<S>(R_.in, yg + sp + (unsigned)q * GRB, 0u, v);
 #pragma unroll
                     for (int k = 0; k < PK; ++k)
                         if (PK * q + k >= 6) {
@@ -664,7 +635,7 @@ template <class S, int KK> struct HopSmem {
     static constexpr unsigned red_off = r0;
     // FP32: the dense s-mixes (POST, LOCMIX, POST2, LOCMIX2; [2][16][16]
     // each) staged with the links, read back in the second phase
-    static constexpr bool CST = sizeof(S) == 4 && DWF_HOP_COEF_LDS32 && DWF_HOP_STAGE_BATCH && DWF_HOP_LDS_LINKS;
+    static constexpr bool CST = sizeof(S) == 4 && DWF_HOP_COEF_LDS32 && DWF_HOP_STAGE_BATCH;
     static constexpr unsigned cst_off = r0 + 32;
     static constexpr unsigned cst_b = CST ? 4u * MAT_ELEMS * 4u : 0u;
     static constexpr unsigned loc_off = cst_off + cst_b;
@@ -724,14 +695,14 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
     const int Ls = P.Ls;
     const long site = tile * 16 + j;
     const bool valid = site < Vh;
-    const long sx = valid ? site : Vh - 1;
     constexpr unsigned CB = cbytes<S>();
     constexpr unsigned PK = fpack<S>();
-    const unsigned gb = (unsigned)P.Vhp * PK * CB;             // bytes of one group row (PK components of a slice)
-    const unsigned fieldb = (unsigned)Ls * (12u / PK) * gb;    // bytes of one right-hand side
-    const unsigned fieldb_a = active ? fieldb : 0u;             // zero-size descriptors when inactive
-    const size_t rhsb = (size_t)rhs * fieldb;                  // bytes of the preceding RHS
-    const unsigned sxb = (unsigned)sx * PK * CB;               // this site's offset in a group row
+    const unsigned tileb = (unsigned)Ls * (12u / PK) * GRB;             // bytes of a tile of a field
+    const unsigned fieldb = tileb * ((unsigned)P.Vhp >> 4);             // bytes of one right-hand side
+    const unsigned fieldb_a = active ? fieldb : 0u;                     // zero-size descriptors when inactive
+    const size_t rhsb = (size_t)rhs * fieldb;                           // bytes of the preceding RHS
+    const unsigned t0 = (unsigned)tile * tileb;                         // this tile
+    const unsigned sxb = t0 + (unsigned)j * 16u;                        // this site's groups
     HopRes R_;
     R_.in = make_rsrc(static_cast<const char*>(P.in) + rhsb, fieldb_a);
     R_.loc = make_rsrc(P.loc ? static_cast<const char*>(P.loc) + rhsb : nullptr, P.loc ? fieldb_a : 0u);
@@ -739,19 +710,17 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
     R_.out2 = make_rsrc(P.out2 ? static_cast<const char*>(P.out2) + rhsb : nullptr, P.out2 ? fieldb_a : 0u);
     // fused CG update target: compute type in its own layout
     constexpr unsigned PKU = fpack<typename std::conditional<sizeof(R) == 8, double, float>::type>();
-    const unsigned fieldu = (unsigned)Ls * 12u * (unsigned)P.Vhp * 2u * (unsigned)sizeof(R);
+    const unsigned tileu = (unsigned)Ls * (12u / PKU) * GRB;
+    const unsigned fieldu = tileu * ((unsigned)P.Vhp >> 4);
+    const unsigned tu0 = (unsigned)tile * tileu;
     R_.upd = make_rsrc(P.upd ? static_cast<char*>(P.upd) + (size_t)rhs * fieldu : nullptr,
                        (P.upd && active) ? fieldu : 0u);
     R_.links = make_rsrc(P.links, 8u * link_ng(CB) * (unsigned)P.Vhp * link_lp(CB) * CB);
     R_.nbr = make_rsrc(P.nbr, 8u * (unsigned)P.Vhp * 4u);
 
-    // Slice groups of this wave, and the pipelined loop's first two
-    // directions (EARLY: their neighbour spinors are requested before the
-    // block barrier, with the neighbour indices read per lane).
+    // Slice groups of this wave, and the pipelined loop's buffers
     constexpr int G = hop_kpw(KK, sizeof(S) == 8);
     constexpr int PF = LAT ? 3 : (PM < 0 ? 0 : (sizeof(S) == 8 ? DWF_HOP_PREFETCH64 : DWF_HOP_PREFETCH));
-    constexpr bool EARLY = DWF_HOP_EARLY && PF == 2 && DWF_HOP_LDS_LINKS &&
-                           (sizeof(S) == 8 ? DWF_HOP_STAGE_BATCH64 : DWF_HOP_STAGE_BATCH);
     constexpr int NGR_ = 12 / fpack<S>();
     int sg[G];
 #pragma unroll
@@ -777,40 +746,32 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
     }
 
     constexpr bool SBATCH = LAT || (sizeof(S) == 8 ? DWF_HOP_STAGE_BATCH64 : DWF_HOP_STAGE_BATCH);
-    if constexpr (DWF_HOP_LDS_LINKS && SBATCH) {
+    // the tile's links and neighbours: contiguous, entries past the last site are
+    // zero (site 0); a neighbour is staged as the byte offset of its groups.  (The
+    // tile's offset is a scalar operand here only: a descriptor of size zero bounds
+    // the vector operand.)
+    const unsigned l0 = (unsigned)tile * (8u * link_ng(CB) * GRB), n0 = (unsigned)tile * 512u;
+    auto offset_of = [&](unsigned y) -> unsigned { return (y >> 4) * tileb + (y & 15u) * 16u; };
+    if constexpr (SBATCH) {
         // the tile's links (16-byte groups) and neighbour indices, once per
         // block; every lane-dependent offset is in the vector operand.  All
         // loads are issued before the first LDS write (a loop with a runtime
         // trip count would wait for each load in turn).  Threads past the
         // table's end read and rewrite its last entry.
-        const unsigned Vhp = (unsigned)P.Vhp;
         constexpr int NE = lnk_entries<S>();
         constexpr int IT = (NE + NTHR - 1) / NTHR;    // blockDim.x >= NTHR
         constexpr int IB = (128 + NTHR - 1) / NTHR;
-        unsigned y0 = 0, y1 = 0;
-        if constexpr (EARLY) {
-            y0 = __builtin_amdgcn_raw_buffer_load_b32(R_.nbr, (unsigned)sx * 4u, 0u, DWF_HOP_NT_LINK);
-            y1 = __builtin_amdgcn_raw_buffer_load_b32(R_.nbr, (unsigned)sx * 4u, Vhp * 4u, DWF_HOP_NT_LINK);
-        }
         u32x4 lv[IT];
         unsigned nv[IB];
 #pragma unroll
         for (int i = 0; i < IT; ++i) {
             const int e = min((int)threadIdx.x + i * (int)blockDim.x, NE - 1);
-            const int dg = e >> 4, jj = e & 15;
-            const long se = tile * 16 + jj;
-            const unsigned sxe = (unsigned)(se < Vh ? se : Vh - 1);
-            lv[i] = __builtin_amdgcn_raw_buffer_load_b128(R_.links, sxe * 16u + (unsigned)dg * Vhp * 16u, 0u,
-                                                          DWF_HOP_NT_LINK);
+            lv[i] = __builtin_amdgcn_raw_buffer_load_b128(R_.links, (unsigned)e * 16u, l0, DWF_HOP_NT_LINK);
         }
 #pragma unroll
         for (int i = 0; i < IB; ++i) {
             const int e = min((int)threadIdx.x + i * (int)blockDim.x, 127);
-            const int d = e >> 4, jj = e & 15;
-            const long se = tile * 16 + jj;
-            const unsigned sxe = (unsigned)(se < Vh ? se : Vh - 1);
-            nv[i] = __builtin_amdgcn_raw_buffer_load_b32(R_.nbr, sxe * 4u + (unsigned)d * Vhp * 4u, 0u,
-                                                         DWF_HOP_NT_LINK);
+            nv[i] = __builtin_amdgcn_raw_buffer_load_b32(R_.nbr, (unsigned)e * 4u, n0, DWF_HOP_NT_LINK);
         }
         // dense s-mixes (FP32): 4 x 128 groups of 16 bytes; a missing matrix
         // reads POST instead (never used)
@@ -829,39 +790,24 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
                 cv[i] = src[e & 127];
             }
         }
-        if constexpr (EARLY) {
-            hop_fetch_at<S, G>(P, R_, gb, y0, sg, ra, ya);
-            hop_fetch_at<S, G>(P, R_, gb, y1, sg, rb, yb);
-        }
         // unconditional stores (a guarded store lets the compiler sink its
         // load behind the guard and wait for it there)
 #pragma unroll
         for (int i = 0; i < IT; ++i) lnk[min((int)threadIdx.x + i * (int)blockDim.x, NE - 1)] = lv[i];
 #pragma unroll
-        for (int i = 0; i < IB; ++i) lnbr[min((int)threadIdx.x + i * (int)blockDim.x, 127)] = nv[i];
+        for (int i = 0; i < IB; ++i) lnbr[min((int)threadIdx.x + i * (int)blockDim.x, 127)] = offset_of(nv[i]);
         if constexpr (L::CST) {
             u32x4* cdst = reinterpret_cast<u32x4*>(smem + L::cst_off);
 #pragma unroll
             for (int i = 0; i < IC; ++i) cdst[min((int)threadIdx.x + i * (int)blockDim.x, 4 * MAT_ELEMS / 4 - 1)] = cv[i];
         }
     }
-    if constexpr (DWF_HOP_LDS_LINKS && !SBATCH) {
+    if constexpr (!SBATCH) {
         // the same tables, one entry per thread and step
-        const unsigned Vhp = (unsigned)P.Vhp;
-        for (int e = threadIdx.x; e < lnk_entries<S>(); e += blockDim.x) {
-            const int dg = e >> 4, jj = e & 15;
-            const long se = tile * 16 + jj;
-            const unsigned sxe = (unsigned)(se < Vh ? se : Vh - 1);
-            lnk[e] = __builtin_amdgcn_raw_buffer_load_b128(R_.links, sxe * 16u + (unsigned)dg * Vhp * 16u, 0u,
-                                                           DWF_HOP_NT_LINK);
-        }
-        for (int e = threadIdx.x; e < 128; e += blockDim.x) {
-            const int d = e >> 4, jj = e & 15;
-            const long se = tile * 16 + jj;
-            const unsigned sxe = (unsigned)(se < Vh ? se : Vh - 1);
-            lnbr[e] = __builtin_amdgcn_raw_buffer_load_b32(R_.nbr, sxe * 4u + (unsigned)d * Vhp * 4u, 0u,
-                                                           DWF_HOP_NT_LINK);
-        }
+        for (int e = threadIdx.x; e < lnk_entries<S>(); e += blockDim.x)
+            lnk[e] = __builtin_amdgcn_raw_buffer_load_b128(R_.links, (unsigned)e * 16u, l0, DWF_HOP_NT_LINK);
+        for (int e = threadIdx.x; e < 128; e += blockDim.x)
+            lnbr[e] = offset_of(__builtin_amdgcn_raw_buffer_load_b32(R_.nbr, (unsigned)e * 4u, n0, DWF_HOP_NT_LINK));
     }
     if constexpr (L::LOC) {
         // local-term tile: group (s, q) of site jj at locT[(s * NGR + q) * 16 + jj];
@@ -873,11 +819,8 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
 #pragma unroll
             for (int i = 0; i < IL; ++i) {
                 const int e = min(tid + i * NTHR, NL - 1);
-                const int jj = e & 15, g = e >> 4;
-                const long se = tile * 16 + jj;
-                const unsigned sxe = (unsigned)(se < Vh ? se : Vh - 1);
-                const int gc = g < Ls * L::NGR ? g : 0;
-                lt[i] = __builtin_amdgcn_raw_buffer_load_b128(R_.loc, sxe * 16u + (unsigned)gc * gb, 0u, DWF_HOP_NT_LOAD);
+                const int gc = (e >> 4) < Ls * L::NGR ? e : (e & 15);
+                lt[i] = __builtin_amdgcn_raw_buffer_load_b128(R_.loc, t0 + (unsigned)gc * 16u, 0u, DWF_HOP_NT_LOAD);
             }
 #pragma unroll
             for (int i = 0; i < IL; ++i) {
@@ -887,7 +830,7 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
             }
         }
     }
-    if constexpr (DWF_HOP_LDS_LINKS || L::LOC) __syncthreads();
+    __syncthreads();
     if constexpr (LAT) {
 #pragma unroll
         for (int g = 0; g < G; ++g)
@@ -954,81 +897,72 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
         // Loop over the 8 hop directions.  Its unrolling (DWF_HOP_UNROLL)
         // trades registers for loads in flight: with 1, nothing of direction
         // d+1 (its links in particular) is hoisted above direction d.
-        unsigned ynb[8];
-#pragma unroll
-        for (int d = 0; d < 8; ++d)
-            ynb[d] = (DWF_HOP_NBR_PRELOAD && !DWF_HOP_LDS_LINKS)
-                         ? __builtin_amdgcn_raw_buffer_load_b32(R_.nbr, (unsigned)sx * 4u, (unsigned)d * (unsigned)P.Vhp * 4u, 0)
-                         : 0u;
-        if constexpr (PF == 2 && DWF_HOP_LDS_LINKS) {
+        if constexpr (PF == 2) {
             // fully unrolled, double-buffered: direction d is a compile-time
             // constant in each step (its spin structure folds), and the loads
             // of d+1 are issued before the arithmetic of d
-            if constexpr (!EARLY) {
-                hop_fetch<S, G>(P, R_, gb, 0, sg, lnbr, j, ra, ya);
-                hop_fetch<S, G>(P, R_, gb, 1, sg, lnbr, j, rb, yb);
-            }
+            hop_fetch<S, G>(P, R_, 0, sg, lnbr, j, ra, ya);
+            hop_fetch<S, G>(P, R_, 1, sg, lnbr, j, rb, yb);
             __builtin_amdgcn_sched_barrier(0);
-            hop_apply<S, G, PM>(P, R_, gb, 0, sg, pd, pe, kr, h, lnk, ra, ya, j);
-            hop_fetch<S, G>(P, R_, gb, 2, sg, lnbr, j, ra, ya);
+            hop_apply<S, G, PM>(P, R_, 0, sg, pd, pe, kr, h, lnk, ra, ya, j);
+            hop_fetch<S, G>(P, R_, 2, sg, lnbr, j, ra, ya);
             __builtin_amdgcn_sched_barrier(0);
-            hop_apply<S, G, PM>(P, R_, gb, 1, sg, pd, pe, kr, h, lnk, rb, yb, j);
-            hop_fetch<S, G>(P, R_, gb, 3, sg, lnbr, j, rb, yb);
+            hop_apply<S, G, PM>(P, R_, 1, sg, pd, pe, kr, h, lnk, rb, yb, j);
+            hop_fetch<S, G>(P, R_, 3, sg, lnbr, j, rb, yb);
             __builtin_amdgcn_sched_barrier(0);
-            hop_apply<S, G, PM>(P, R_, gb, 2, sg, pd, pe, kr, h, lnk, ra, ya, j);
-            hop_fetch<S, G>(P, R_, gb, 4, sg, lnbr, j, ra, ya);
+            hop_apply<S, G, PM>(P, R_, 2, sg, pd, pe, kr, h, lnk, ra, ya, j);
+            hop_fetch<S, G>(P, R_, 4, sg, lnbr, j, ra, ya);
             __builtin_amdgcn_sched_barrier(0);
-            hop_apply<S, G, PM>(P, R_, gb, 3, sg, pd, pe, kr, h, lnk, rb, yb, j);
-            hop_fetch<S, G>(P, R_, gb, 5, sg, lnbr, j, rb, yb);
+            hop_apply<S, G, PM>(P, R_, 3, sg, pd, pe, kr, h, lnk, rb, yb, j);
+            hop_fetch<S, G>(P, R_, 5, sg, lnbr, j, rb, yb);
             __builtin_amdgcn_sched_barrier(0);
-            hop_apply<S, G, PM>(P, R_, gb, 4, sg, pd, pe, kr, h, lnk, ra, ya, j);
-            hop_fetch<S, G>(P, R_, gb, 6, sg, lnbr, j, ra, ya);
+            hop_apply<S, G, PM>(P, R_, 4, sg, pd, pe, kr, h, lnk, ra, ya, j);
+            hop_fetch<S, G>(P, R_, 6, sg, lnbr, j, ra, ya);
             __builtin_amdgcn_sched_barrier(0);
-            hop_apply<S, G, PM>(P, R_, gb, 5, sg, pd, pe, kr, h, lnk, rb, yb, j);
-            hop_fetch<S, G>(P, R_, gb, 7, sg, lnbr, j, rb, yb);
+            hop_apply<S, G, PM>(P, R_, 5, sg, pd, pe, kr, h, lnk, rb, yb, j);
+            hop_fetch<S, G>(P, R_, 7, sg, lnbr, j, rb, yb);
             __builtin_amdgcn_sched_barrier(0);
-            hop_apply<S, G, PM>(P, R_, gb, 6, sg, pd, pe, kr, h, lnk, ra, ya, j);
+            hop_apply<S, G, PM>(P, R_, 6, sg, pd, pe, kr, h, lnk, ra, ya, j);
             __builtin_amdgcn_sched_barrier(0);
-            hop_apply<S, G, PM>(P, R_, gb, 7, sg, pd, pe, kr, h, lnk, rb, yb, j);
+            hop_apply<S, G, PM>(P, R_, 7, sg, pd, pe, kr, h, lnk, rb, yb, j);
         } else if constexpr (PF == 3) {
             // the next ND directions' loads in flight
-            static_assert(!LAT || DWF_HOP_LDS_LINKS, "the deep pipeline reads the staged tables");
             constexpr int ND = PM == 2 ? 2 : 4, ND2 = PM == 2 ? ND : 1;
             u32x4 rd[ND][G][NGR_], rm[ND2][G][NGR_], rp[ND2][G][NGR_];
             unsigned yd[ND];
 #pragma unroll
             for (int d = 0; d < ND; ++d) {
-                hop_fetch<S, G>(P, R_, gb, d, sg, lnbr, j, rd[d], yd[d]);
-                if constexpr (PM == 2) hop_fetch2<S, G>(P, R_, gb, sg, yd[d], rm[d], rp[d]);
+                hop_fetch<S, G>(P, R_, d, sg, lnbr, j, rd[d], yd[d]);
+                if constexpr (PM == 2) hop_fetch2<S, G>(P, R_, sg, yd[d], rm[d], rp[d]);
             }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int d = 0; d < 8; ++d) {
-                hop_apply<S, G, PM, PM == 2>(P, R_, gb, d, sg, pd, pe, kr, h, lnk, rd[d % ND], yd[d % ND], j,
+                hop_apply<S, G, PM, PM == 2>(P, R_, d, sg, pd, pe, kr, h, lnk, rd[d % ND], yd[d % ND], j,
                                              rm[d % ND2], rp[d % ND2]);
                 if (d + ND < 8) {
-                    hop_fetch<S, G>(P, R_, gb, d + ND, sg, lnbr, j, rd[d % ND], yd[d % ND]);
-                    if constexpr (PM == 2) hop_fetch2<S, G>(P, R_, gb, sg, yd[d % ND], rm[d % ND2], rp[d % ND2]);
+                    hop_fetch<S, G>(P, R_, d + ND, sg, lnbr, j, rd[d % ND], yd[d % ND]);
+                    if constexpr (PM == 2) hop_fetch2<S, G>(P, R_, sg, yd[d % ND], rm[d % ND2], rp[d % ND2]);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
-        } else if constexpr (PF == 1 && DWF_HOP_LDS_LINKS) {
+        } else if constexpr (PF == 1) {
             // ping-pong over two raw buffers: the loads of the next direction
             // are in flight while the current one is computed
-            hop_fetch<S, G>(P, R_, gb, 0, sg, lnbr, j, ra, ya);
+            hop_fetch<S, G>(P, R_, 0, sg, lnbr, j, ra, ya);
 #pragma unroll 1
             for (int d = 0; d < 8; d += 2) {
-                hop_fetch<S, G>(P, R_, gb, d + 1, sg, lnbr, j, rb, yb);
+                hop_fetch<S, G>(P, R_, d + 1, sg, lnbr, j, rb, yb);
                 __builtin_amdgcn_sched_barrier(0);
-                hop_apply<S, G, PM>(P, R_, gb, d, sg, pd, pe, kr, h, lnk, ra, ya, j);
-                if (d + 2 < 8) hop_fetch<S, G>(P, R_, gb, d + 2, sg, lnbr, j, ra, ya);
+                hop_apply<S, G, PM>(P, R_, d, sg, pd, pe, kr, h, lnk, ra, ya, j);
+                if (d + 2 < 8) hop_fetch<S, G>(P, R_, d + 2, sg, lnbr, j, ra, ya);
                 __builtin_amdgcn_sched_barrier(0);
-                hop_apply<S, G, PM>(P, R_, gb, d + 1, sg, pd, pe, kr, h, lnk, rb, yb, j);
+                hop_apply<S, G, PM>(P, R_, d + 1, sg, pd, pe, kr, h, lnk, rb, yb, j);
             }
         } else {
 #pragma unroll DWF_HOP_UNROLL
             for (int d = 0; d < 8; ++d) {
-                hop_direction<S, G, PM>(P, R_, gb, (unsigned)sx, d, ynb[d], sg, pd, pe, kr, h, lnk, lnbr, j);
+                hop_direction<S, G, PM>(P, R_, d, sg, pd, pe, kr, h, lnk, lnbr, j);
                 // unrolled: keep each direction's loads after the previous one's
                 // arithmetic (hoisting them all raises the register count past
                 // the occupancy target)
@@ -1058,8 +992,8 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
 #pragma unroll
             for (int kk = 0; kk < KK; ++kk) {
                 const int cp = w * CPW_ + q, s_ = sc + 4 * kk;
-                const unsigned off = sxb + (unsigned)(s_ < Ls ? s_ : 0) * (12u / PK) * gb +
-                                     (unsigned)(cp / PK) * gb + (unsigned)(cp % PK) * CB;
+                const unsigned off = sxb + ((unsigned)(s_ < Ls ? s_ : 0) * (12u / PK) + (unsigned)(cp / PK)) * GRB +
+                                     (unsigned)(cp % PK) * CB;
                 R vr, vi;
                 bload<S>(R_.loc, off, 0u, vr, vi);
                 lre[q][kk] = s_ < Ls ? vr : R(0);
@@ -1072,19 +1006,15 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
                 for (int i = 0; i < 4; ++i) {
                     const int cp = w * CPW_ + q, s_ = out_row<R>(sc, i);
                     uvl[q][i] = __builtin_amdgcn_raw_buffer_load_b128(
-                        R_.upd, sxb + ((unsigned)(s_ < Ls ? s_ : 0) * 12u + (unsigned)cp) * gb, 0u, 0);
+                        R_.upd, sxb + ((unsigned)(s_ < Ls ? s_ : 0) * 12u + (unsigned)cp) * GRB, 0u, 0);
                 }
         }
         if constexpr (UPDE) {
-            const unsigned gbu = (unsigned)P.Vhp * 16u;
             const int nU = Ls * 6 * 16;
 #pragma unroll
             for (int i = 0; i < IUE; ++i) {
                 const int e = min(tid + i * NTHR, nU - 1);
-                const int jj = e & 15, g = e >> 4;
-                const long se = tile * 16 + jj;
-                const unsigned sxe = (unsigned)(se < Vh ? se : Vh - 1);
-                uve[i] = __builtin_amdgcn_raw_buffer_load_b128(R_.upd, sxe * 16u + (unsigned)g * gbu, 0u, DWF_HOP_NT_LOAD);
+                uve[i] = __builtin_amdgcn_raw_buffer_load_b128(R_.upd, tu0 + (unsigned)e * 16u, 0u, DWF_HOP_NT_LOAD);
             }
         }
     }
@@ -1115,7 +1045,7 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
     // the compiler does not treat as uniform: a scalar operand would be
     // split into a loop over lanes)
     auto coff = [&](int s, int cp) -> unsigned {
-        return sxb + (unsigned)s * (12u / PK) * gb + (unsigned)(cp / PK) * gb + (unsigned)(cp % PK) * CB;
+        return sxb + ((unsigned)s * (12u / PK) + (unsigned)(cp / PK)) * GRB + (unsigned)(cp % PK) * CB;
     };
     double nrm = 0.0;
     // A operands of one chirality, loaded once per wave before the component
@@ -1319,7 +1249,6 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
             // upd -= alpha * result over upd's own groups (FP32 pairs)
             static_assert(PKU == 2, "fused update expects FP32 fields in component pairs");
             __syncthreads();
-            const unsigned gbu = (unsigned)P.Vhp * 16u;
             // every LDS and global read of the thread first, then the
             // updates (a loop with a runtime trip count would wait for each
             // iteration's reads in turn); threads past the end read the last
@@ -1333,31 +1262,25 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
                 const int e = min(tid + i * NTHR, nU - 1);
                 const int jj = e & 15, g = e >> 4;
                 const int sl = g / 6, q2 = g - sl * 6;
-                const long se = tile * 16 + jj;
                 const float* run0 = hs + (sl >> 2) * HSK + 2 * ((sl & 3) * 16 + jj);
                 av[i] = *reinterpret_cast<const float2*>(run0 + (2 * (2 * q2)) * 64);
                 bv[i] = *reinterpret_cast<const float2*>(run0 + (2 * (2 * q2 + 1)) * 64);
-                const unsigned sxe = (unsigned)(se < Vh ? se : Vh - 1);
                 if constexpr (UPDE)
                     uv[i] = uve[i];
                 else
-                    uv[i] = __builtin_amdgcn_raw_buffer_load_b128(R_.upd, sxe * 16u + (unsigned)g * gbu, 0u,
-                                                                  DWF_HOP_NT_LOAD);
+                    uv[i] = __builtin_amdgcn_raw_buffer_load_b128(R_.upd, tu0 + (unsigned)e * 16u, 0u, DWF_HOP_NT_LOAD);
             }
 #pragma unroll
             for (int i = 0; i < IU; ++i) {
                 const int e = tid + i * NTHR;
-                const int jj = e & 15, g = e >> 4;
-                const long se = tile * 16 + jj;
-                if (e < nU && se < Vh) {
-                    const unsigned off = (unsigned)se * 16u + (unsigned)g * gbu;
+                if (e < nU && tile * 16 + (e & 15) < Vh) {
                     const u32x4 u = uv[i];
                     const float2 a = av[i], b = bv[i];
                     float v0 = __uint_as_float(u.x) - ua * a.x, v1 = __uint_as_float(u.y) - ua * a.y;
                     float v2 = __uint_as_float(u.z) - ua * b.x, v3 = __uint_as_float(u.w) - ua * b.y;
                     u32x4 o;
                     o.x = __float_as_uint(v0); o.y = __float_as_uint(v1); o.z = __float_as_uint(v2); o.w = __float_as_uint(v3);
-                    __builtin_amdgcn_raw_buffer_store_b128(o, R_.upd, off, 0u, DWF_HOP_NT_STORE);
+                    __builtin_amdgcn_raw_buffer_store_b128(o, R_.upd, tu0 + (unsigned)e * 16u, 0u, DWF_HOP_NT_STORE);
                     if (f_reduce == 3)
                         nrm += double(v0) * double(v0) + double(v1) * double(v1) + double(v2) * double(v2) +
                                double(v3) * double(v3);
@@ -1392,11 +1315,8 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
 #pragma unroll
             for (int i = 0; i < IO; ++i) {
                 const int e = tid + i * NTHR;
-                const int jj = e & 15, g = e >> 4;
-                const long se = tile * 16 + jj;
-                if (e < nO && se < Vh)
-                    __builtin_amdgcn_raw_buffer_store_b128(vv[i], dst, (unsigned)se * 16u + (unsigned)g * gb, 0u,
-                                                           DWF_HOP_NT_STORE);
+                if (e < nO && tile * 16 + (e & 15) < Vh)
+                    __builtin_amdgcn_raw_buffer_store_b128(vv[i], dst, t0 + (unsigned)e * 16u, 0u, DWF_HOP_NT_STORE);
             }
         }
     }

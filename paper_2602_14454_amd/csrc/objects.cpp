@@ -197,9 +197,7 @@ void build_geometry(dwf_lattice* L) {
     const long V = L->V, Vh = L->Vh;
     choose_brick(L->dims, L->brick);
     L->site_order = site_order_kind();
-    // row stride: 32 x odd, so consecutive rows of a field land in different cache sets
-    L->Vhp = ((Vh + 31) / 32) * 32;
-    if ((L->Vhp / 32) % 2 == 0) L->Vhp += 32;
+    L->Vhp = (Vh + 15) / 16 * 16;   // whole tiles of 16 sites
     const long Vhp = L->Vhp;
     const int bx = L->brick[0], by = L->brick[1], bz = L->brick[2];
     L->lex_of_site.assign(2 * Vh, -1);
@@ -240,7 +238,7 @@ void build_geometry(dwf_lattice* L) {
                 int cc[4] = {c[0], c[1], c[2], c[3]};
                 cc[mu] = (cc[mu] + dir + ext[mu]) % ext[mu];
                 const long y = cc[0] + (long)Lx * (cc[1] + (long)Ly * (cc[2] + (long)Lz * cc[3]));
-                L->nbr_host[(p * 8 + d) * Vhp + i] = site_of_lex[y];
+                L->nbr_host[p * 8 * Vhp + ((i >> 4) * 8 + d) * 16 + (i & 15)] = site_of_lex[y];
             }
         }
     L->nbr.alloc(sizeof(int) * 2 * 8 * Vhp);

@@ -183,19 +183,26 @@ template <class S> constexpr unsigned cbytes() { return sizeof(S) == 8 ? 16u : s
 // ---------------------------------------------------------------------
 // Internal layouts.
 //
-// Fields: element (row, site), row = s * 12 + comp (further right-hand sides
-// and channels continue the row count), at complex index
-//   ((row / P) * Vhp + site) * P + row % P
-// with P = 1 for FP64, 2 for FP32 and 4 for BF16: P consecutive spin-colour
-// components of a site are contiguous (16 bytes) and consecutive sites follow
-// each other, so a wave's load of one group for 16 consecutive sites reads one
-// contiguous 256-byte run with a single 128-bit load per lane.  Kernels that
-// mix storage kinds element by element (conversions, CG updates with FP32 x, r
-// and BF16 p, w) index each operand in its own layout (blas.hip).
+// Sites come in tiles of 16; a tile's data are contiguous, in 16-byte groups of
+// one site each: with ng groups per site, group g of a site is group
+//   ((site / 16) * ng + g) * 16 + site % 16
+// of the array, so a load of one group by 16 lanes on consecutive sites reads a
+// 256-byte run, and everything that a tile's block reads of its own sites is one
+// run of memory.  (Rows of one group over all sites had the same runs, but put
+// the 12 to 192 groups of a site as many row strides apart: a block of the hop
+// then touched some 250 pages, and its loads waited for address translations.
+// Hop on 24^3x48, Ls = 16: FP32 410 -> 368 us, BF16 265 -> 252 us.)
 //
-// Links: LP = 16 / (complex bytes) elements of one site's 3x3 matrix share
-// a 16-byte group; direction d has NG = ceil(9 / LP) groups:
-//   element (d, e, site) at ((d * NG + e / LP) * Vhp + site) * LP + e % LP.
+// Fields: P consecutive spin-colour components (P = 1 for FP64, 2 for FP32, 4
+// for BF16) of row = s * 12 + comp share a group; rows = Ls * 12, ng = rows / P.
+// Further right-hand sides and channels follow as whole fields.  Kernels that
+// mix storage kinds element by element (conversions, CG updates with FP32 x, r
+// and BF16 p, w) take quads: 4 components of a site, which lie in 4, 2 or 1
+// groups of the same tile.
+//
+// Links: LP = 16 / (complex bytes) elements of one site's 3x3 matrix share a
+// group; direction d has NG = ceil(9 / LP) groups, ng = 8 NG per output parity.
+// Neighbour table: element d of 8 of a site at ((site / 16) * 8 + d) * 16 + site % 16.
 // ---------------------------------------------------------------------
 // Compile-time layout switches (measured on MI355X, see the hop kernel):
 // DWF_FIELD_PAIRS groups FP32/BF16 components in pairs, DWF_LINK_PACK packs
@@ -206,9 +213,14 @@ template <class S> constexpr unsigned cbytes() { return sizeof(S) == 8 ? 16u : s
 #ifndef DWF_LINK_PACK
 #define DWF_LINK_PACK 1
 #endif
-__host__ __device__ __forceinline__ long fidx(long row, long site, long Vhp, int P) {
-    return P == 1 ? row * Vhp + site : (P == 2 ? ((row >> 1) * Vhp + site) * 2 + (row & 1)
-                                               : ((row >> 2) * Vhp + site) * 4 + (row & 3));
+// group g of a site with ng groups
+__host__ __device__ __forceinline__ long gidx(long g, long site, long ng) {
+    return ((site >> 4) * ng + g) * 16 + (site & 15);
+}
+// complex index of a field's element
+__host__ __device__ __forceinline__ long fidx(long row, long site, long rows, int P) {
+    return P == 1 ? gidx(row, site, rows) : (P == 2 ? gidx(row >> 1, site, rows >> 1) * 2 + (row & 1)
+                                                    : gidx(row >> 2, site, rows >> 2) * 4 + (row & 3));
 }
 // components per group: FP64 1, FP32 2, BF16 4 (16 bytes per site and group)
 template <class S> constexpr int fpack() {
@@ -217,20 +229,20 @@ template <class S> constexpr int fpack() {
 inline int fpack_of(int kind) { return (kind == 0 || !DWF_FIELD_PAIRS) ? 1 : (kind == 1 ? 2 : 4); }
 __host__ __device__ constexpr int link_lp(int cb) { return DWF_LINK_PACK ? 16 / cb : 1; }
 __host__ __device__ constexpr int link_ng(int cb) { return (9 + link_lp(cb) - 1) / link_lp(cb); }
-__host__ __device__ __forceinline__ long lidx(int d, int e, long site, long Vhp, int cb) {
-    return (((long)d * link_ng(cb) + e / link_lp(cb)) * Vhp + site) * link_lp(cb) + e % link_lp(cb);
+__host__ __device__ __forceinline__ long lidx(int d, int e, long site, int cb) {
+    return gidx(d * link_ng(cb) + e / link_lp(cb), site, 8 * link_ng(cb)) * link_lp(cb) + e % link_lp(cb);
 }
 // complex elements of the link table of one parity
 __host__ __device__ inline long link_elems_parity(long Vhp, int cb) { return 8L * link_ng(cb) * link_lp(cb) * Vhp; }
 
-// Components 4g .. 4g+3 of one site with whole-group accesses (16 bytes per
-// access when the layout packs 16 bytes per group): v = re0, im0, ..., re3, im3.
+// Quad t of a field, whole groups: components 4g .. 4g+3 of a site for
+// t = gidx(g, site, rows / 4).  v = re0, im0, ..., re3, im3.
 template <class S>
-__device__ __forceinline__ void load4(const void* base, long g, long site, long Vhp,
+__device__ __forceinline__ void load4(const void* base, long t,
                                       typename Traits<S>::R (&v)[8]) {
     constexpr int P = fpack<S>();
     if constexpr (P == 4) {   // BF16 quads
-        const uint4 w = reinterpret_cast<const uint4*>(base)[g * Vhp + site];
+        const uint4 w = reinterpret_cast<const uint4*>(base)[t];
         const unsigned u[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -240,7 +252,7 @@ __device__ __forceinline__ void load4(const void* base, long g, long site, long 
     } else if constexpr (P == 2 && sizeof(S) == 4) {   // FP32 pairs
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            const float4 w = reinterpret_cast<const float4*>(base)[(2 * g + j) * Vhp + site];
+            const float4 w = reinterpret_cast<const float4*>(base)[((t >> 4) * 2 + j) * 16 + (t & 15)];
             v[4 * j] = w.x;
             v[4 * j + 1] = w.y;
             v[4 * j + 2] = w.z;
@@ -248,12 +260,12 @@ __device__ __forceinline__ void load4(const void* base, long g, long site, long 
         }
     } else {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) cload<S>(base, fidx(4 * g + k, site, Vhp, P), v[2 * k], v[2 * k + 1]);
+        for (int k = 0; k < 4; ++k) cload<S>(base, ((t >> 4) * 4 + k) * 16 + (t & 15), v[2 * k], v[2 * k + 1]);
     }
 }
 
 template <class S>
-__device__ __forceinline__ void store4(void* base, long g, long site, long Vhp,
+__device__ __forceinline__ void store4(void* base, long t,
                                        const typename Traits<S>::R (&v)[8]) {
     constexpr int P = fpack<S>();
     if constexpr (P == 4) {
@@ -262,15 +274,15 @@ __device__ __forceinline__ void store4(void* base, long g, long site, long Vhp,
         w.y = pack_bf16(v[2], v[3]);
         w.z = pack_bf16(v[4], v[5]);
         w.w = pack_bf16(v[6], v[7]);
-        reinterpret_cast<uint4*>(base)[g * Vhp + site] = w;
+        reinterpret_cast<uint4*>(base)[t] = w;
     } else if constexpr (P == 2 && sizeof(S) == 4) {
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-            reinterpret_cast<float4*>(base)[(2 * g + j) * Vhp + site] =
+            reinterpret_cast<float4*>(base)[((t >> 4) * 2 + j) * 16 + (t & 15)] =
                 make_float4(v[4 * j], v[4 * j + 1], v[4 * j + 2], v[4 * j + 3]);
     } else {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) cstore<S>(base, fidx(4 * g + k, site, Vhp, P), v[2 * k], v[2 * k + 1]);
+        for (int k = 0; k < 4; ++k) cstore<S>(base, ((t >> 4) * 4 + k) * 16 + (t & 15), v[2 * k], v[2 * k + 1]);
     }
 }
 
@@ -327,42 +339,6 @@ __device__ __forceinline__ void decode_link_group(u32x4 w, int g, typename Trait
                 U[2 * (LP * g + k)] = bf16_to_f32(u[k] & 0xffffu);
                 U[2 * (LP * g + k) + 1] = bf16_to_f32(u[k] >> 16);
             }
-    }
-}
-
-// The 3x3 link of direction d at one site: voff = site * group bytes,
-// soff = d * NG * group row bytes, gstride = group row bytes.  U = re, im of
-// elements 0..8.
-template <class S>
-__device__ __forceinline__ void bload_link(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff, unsigned gstride,
-                                           typename Traits<S>::R (&U)[18]) {
-    constexpr int CB = cbytes<S>(), LP = link_lp(CB), NG = link_ng(CB);
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-        if constexpr (LP == 1) {
-            bload<S>(r, voff, soff + (unsigned)g * gstride, U[2 * g], U[2 * g + 1]);
-        } else {
-            u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff + (unsigned)g * gstride, 0);
-            if constexpr (sizeof(S) == 8) {
-                U[2 * g] = __hiloint2double(w.y, w.x);
-                U[2 * g + 1] = __hiloint2double(w.w, w.z);
-            } else if constexpr (sizeof(S) == 4) {
-                U[4 * g] = __uint_as_float(w.x);
-                U[4 * g + 1] = __uint_as_float(w.y);
-                if (2 * g + 1 < 9) {
-                    U[4 * g + 2] = __uint_as_float(w.z);
-                    U[4 * g + 3] = __uint_as_float(w.w);
-                }
-            } else {
-                const unsigned u[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    if (LP * g + k < 9) {
-                        U[2 * (LP * g + k)] = bf16_to_f32(u[k] & 0xffffu);
-                        U[2 * (LP * g + k) + 1] = bf16_to_f32(u[k] >> 16);
-                    }
-            }
-        }
     }
 }
 

@@ -103,12 +103,12 @@ void dwf_ptc::reserve(const dwf_op* op, hipStream_t st) {
         to.alloc(n * sizeof(float2));
         tv.alloc(n * sizeof(float2));
         cap_n = n;
-    } else if (lay_n != n || lay_vhp != op->lat->Vhp) {
-        // another lattice: the loss sums run over whole rows, padding included
+    } else if (lay_n != n || lay_vh != op->lat->Vh) {
+        // another lattice: the loss sums run over whole tiles, padding included
         for (DevBuf* b : {&y, &d, &u}) DWF_HIP(hipMemsetAsync(b->p, 0, b->bytes, st));
     }
     lay_n = n;
-    lay_vhp = op->lat->Vhp;
+    lay_vh = op->lat->Vh;
 }
 
 void dwf_ptc::forward(const dwf_op* op, const float2* r, float2* out, hipStream_t st) {
@@ -215,7 +215,7 @@ dwf_ptc_pairs* ptc_pairs_create(const dwf_op* op, const void* b5, unsigned long 
         convert(ST_F64, ST_F64, xs.p, W.x.p, n, st);
     } else {
         // a system with known solution: x* = seeded random field, b~ = D^ x*
-        random_fill_f64(xs.p, (long)op->Ls * 12, L->Vh, L->Vhp, seed, st);
+        random_fill_f64(xs.p, (long)op->Ls * 12, L->Vh, seed, st);
         apply_dhat(op, ST_F64, 0, bt.p, xs.p, to.p, nullptr, 1, st);
     }
     std::unique_ptr<dwf_ptc_pairs> P(new dwf_ptc_pairs);
@@ -236,7 +236,7 @@ dwf_ptc_pairs* ptc_pairs_create(const dwf_op* op, const void* b5, unsigned long 
             float2* r = P->r.as<float2>() + (size_t)i * n;
             convert(ST_F64, ST_F64, tmp.p, xs.p, n, st);
             axpby(ST_F64, ST_F64, tmp.p, xk, n, nullptr, -1.0, nullptr, 1.0, nullptr, st);
-            convert(ST_F32, ST_F64, e, tmp.p, n, st, L->Vhp);
+            convert(ST_F32, ST_F64, e, tmp.p, n, st);
             apply_normal(op, ST_F32, r, e, t1.p, t2.p, nullptr, 1, st);
         }
     };

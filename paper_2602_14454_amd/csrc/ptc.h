@@ -11,8 +11,8 @@ struct PtcLayerParams {
     const float2* in_hop;   // field on the other parity (the 8 link paths), or nullptr
     float2* out;            // field on the output parity
     const float2* W;        // [11][4][4] complex
-    const float2* links;    // FP32 hop links of the output parity [8][9][Vhp]
-    const int* nbr;         // neighbour table of the output parity [8][Vhp]
+    const float2* links;    // FP32 hop links of the output parity
+    const int* nbr;         // neighbour table of the output parity
     long Vh, Vhp;
     int Ls;
 };

@@ -1,7 +1,7 @@
 // Kernels of the learned preconditioner: a linear, gauge-equivariant
 // parallel-transport convolution (PTC) network (layers, weight gradients,
-// loss, Adam).  Fields are FP32 internal half fields, channel-major:
-// element (ch, s, comp, site) at ((ch * Ls + s) * 12 + comp) * Vhp + site.
+// loss, Adam).  Fields are FP32 internal half fields (precision.h), one per
+// channel, channel after channel.
 //
 // One layer, for the sites x of one parity p:
 //   out^a(x, s) = sum_b [ sum_{q in 0, +s, -s} W_q^{ab} in_loc^b(x, s + shift_q)
@@ -35,49 +35,33 @@ __device__ __forceinline__ void cfma(float2& acc, float2 a, float2 b) {
     acc.y += a.x * b.y + a.y * b.x;
 }
 
-// v (12 complex, spin-major) of the slice whose first row is row0, at internal
-// site i (FP32 field layout: pairs of components, or single components)
-__device__ __forceinline__ void load12(const float2* f, long row0, long i, long Vhp, float2 (&v)[12]) {
-    if constexpr (fpack<float>() == 2) {
+// v (12 complex, spin-major) of slice s at internal site i
+__device__ __forceinline__ void load12(const float2* f, int s, long i, int Ls, float2 (&v)[12]) {
 #pragma unroll
-        for (int q = 0; q < 6; ++q) {
-            const float4 a = *reinterpret_cast<const float4*>(f + fidx(row0 + 2 * q, i, Vhp, 2));
-            v[2 * q] = make_float2(a.x, a.y);
-            v[2 * q + 1] = make_float2(a.z, a.w);
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < 12; ++k) v[k] = f[fidx(row0 + k, i, Vhp, 1)];
+    for (int q = 0; q < 6; ++q) {
+        const float4 a = reinterpret_cast<const float4*>(f)[gidx(s * 6 + q, i, Ls * 6)];
+        v[2 * q] = make_float2(a.x, a.y);
+        v[2 * q + 1] = make_float2(a.z, a.w);
     }
 }
 
-__device__ __forceinline__ void store12(float2* f, long row0, long i, long Vhp, const float2 (&v)[12]) {
-    if constexpr (fpack<float>() == 2) {
+__device__ __forceinline__ void store12(float2* f, int s, long i, int Ls, const float2 (&v)[12]) {
 #pragma unroll
-        for (int q = 0; q < 6; ++q)
-            *reinterpret_cast<float4*>(f + fidx(row0 + 2 * q, i, Vhp, 2)) =
-                make_float4(v[2 * q].x, v[2 * q].y, v[2 * q + 1].x, v[2 * q + 1].y);
-    } else {
-#pragma unroll
-        for (int k = 0; k < 12; ++k) f[fidx(row0 + k, i, Vhp, 1)] = v[k];
-    }
+    for (int q = 0; q < 6; ++q)
+        reinterpret_cast<float4*>(f)[gidx(s * 6 + q, i, Ls * 6)] =
+            make_float4(v[2 * q].x, v[2 * q].y, v[2 * q + 1].x, v[2 * q + 1].y);
 }
 
 // t = L v on every spin (L: 9 complex of direction d at site i; FP32 links
 // in pairs, one 16-byte load per pair)
-__device__ __forceinline__ void transport(const float2* links, int d, long i, long Vhp, const float2 (&v)[12],
+__device__ __forceinline__ void transport(const float2* links, int d, long i, const float2 (&v)[12],
                                           float2 (&t)[12]) {
     float2 L[10];
-    if constexpr (link_lp(8) == 2) {
 #pragma unroll
-        for (int g = 0; g < 5; ++g) {
-            const float4 a = *reinterpret_cast<const float4*>(links + lidx(d, 2 * g, i, Vhp, 8));
-            L[2 * g] = make_float2(a.x, a.y);
-            L[2 * g + 1] = make_float2(a.z, a.w);
-        }
-    } else {
-#pragma unroll
-        for (int e = 0; e < 9; ++e) L[e] = links[lidx(d, e, i, Vhp, 8)];
+    for (int g = 0; g < 5; ++g) {
+        const float4 a = reinterpret_cast<const float4*>(links)[gidx(d * 5 + g, i, 40)];
+        L[2 * g] = make_float2(a.x, a.y);
+        L[2 * g + 1] = make_float2(a.z, a.w);
     }
 #pragma unroll
     for (int sp = 0; sp < 4; ++sp)
@@ -107,7 +91,7 @@ __global__ __launch_bounds__(PT) void ptc_layer_kernel(PtcLayerParams P) {
     const long i = (long)blockIdx.x * PT + threadIdx.x;
     if (i >= P.Vh) return;
     const int s = blockIdx.y;
-    const long Vhp = P.Vhp;
+    const int Ls = P.Ls;
     float2 acc[12];
 #pragma unroll
     for (int k = 0; k < 12; ++k) acc[k] = make_float2(0.f, 0.f);
@@ -118,21 +102,21 @@ __global__ __launch_bounds__(PT) void ptc_layer_kernel(PtcLayerParams P) {
             const int ss = qi == 0 ? s : (qi == 1 ? s + 1 : s - 1);
             if (ss < 0 || ss >= P.Ls) continue;
             float2 t[12];
-            load12(P.in_loc, (long)ss * 12, i, Vhp, t);
+            load12(P.in_loc, ss, i, Ls, t);
             spin_apply(P.W + q * 16, t, acc);
         }
     }
     // link paths 1..8
     if (P.in_hop) {
         for (int d = 0; d < 8; ++d) {
-            const long y = P.nbr[(long)d * Vhp + i];
+            const long y = P.nbr[gidx(d, i, 8)];
             float2 v[12], t[12];
-            load12(P.in_hop, (long)s * 12, y, Vhp, v);
-            transport(P.links, d, i, Vhp, v, t);
+            load12(P.in_hop, s, y, Ls, v);
+            transport(P.links, d, i, v, t);
             spin_apply(P.W + (1 + d) * 16, t, acc);
         }
     }
-    store12(P.out, (long)s * 12, i, P.Vhp, acc);
+    store12(P.out, s, i, Ls, acc);
 }
 
 // ---------------------------------------------------------------------
@@ -212,11 +196,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
     const int nthr = blockDim.x;
     for (int e = threadIdx.x; e < 8 * 5 * 32; e += nthr) {
         const long site = tile * 32 + (e & 31);
-        lnk[e] = reinterpret_cast<const u32x4*>(links)[(long)(e >> 5) * Vhp + (site < Vh ? site : Vh - 1)];
+        lnk[e] = reinterpret_cast<const u32x4*>(links)[gidx(e >> 5, site < Vh ? site : Vh - 1, 40)];
     }
     for (int e = threadIdx.x; e < 8 * 32; e += nthr) {
         const long site = tile * 32 + (e & 31);
-        lnb[e] = nbr[(long)(e >> 5) * Vhp + (site < Vh ? site : Vh - 1)];
+        lnb[e] = (int)gidx(0, nbr[gidx(e >> 5, site < Vh ? site : Vh - 1, 8)], Ls * 6);   // of a field's 16-byte groups
     }
     for (int e = threadIdx.x; e < 1024; e += nthr) ew4[e] = reinterpret_cast<const u32x4*>(el)[e];
     __syncthreads();
@@ -233,7 +217,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
             for (int k = 0; k < 16; ++k) { acc[c][0][k] = 0.f; acc[c][1][k] = 0.f; }
         float4 nx[6];
 #pragma unroll
-        for (int q = 0; q < 6; ++q) nx[q] = r4[(long)(s * 6 + q) * Vhp + lnb[j]];
+        for (int q = 0; q < 6; ++q) nx[q] = r4[lnb[j] + (s * 6 + q) * 16];
 #pragma unroll 1
         for (int d = 0; d < 8; ++d) {
             // real lanes use (re, -im) of the spinor, imaginary lanes (im, re)
@@ -247,7 +231,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
             }
             const int y = lnb[(d < 7 ? d + 1 : 7) * 32 + j];   // the next direction's spinor, in flight meanwhile
 #pragma unroll
-            for (int q = 0; q < 6; ++q) nx[q] = r4[(long)(s * 6 + q) * Vhp + y];
+            for (int q = 0; q < 6; ++q) nx[q] = r4[y + (s * 6 + q) * 16];
             float U[20];
 #pragma unroll
             for (int k = 0; k < 5; ++k) {
@@ -282,7 +266,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
 #pragma unroll
                 for (int q = 0; q < 6; ++q) {
                     const int c0 = (2 * q) % 3, s0 = (2 * q) / 3, c1 = (2 * q + 1) % 3, s1 = (2 * q + 1) / 3;
-                    reinterpret_cast<float4*>(gd)[(long)(s * 6 + q) * Vhp + site] =
+                    reinterpret_cast<float4*>(gd)[gidx(s * 6 + q, site, Ls * 6)] =
                         make_float4(acc[c0][0][4 * k + s0], acc[c0][1][4 * k + s0], acc[c1][0][4 * k + s1],
                                     acc[c1][1][4 * k + s1]);
                 }
@@ -308,10 +292,10 @@ __global__ __launch_bounds__(256) void ptc_out_kernel(const float2* __restrict__
     for (int k = 0; k < 12; ++k) acc[k] = make_float2(0.f, 0.f);
 #pragma unroll 2
     for (int d = 0; d < 8; ++d) {
-        const long y = nbr[(long)d * Vhp + i];
+        const long y = nbr[gidx(d, i, 8)];
         float2 m[12], t[12];
-        load12(g + d * n, (long)s * 12, y, Vhp, m);
-        transport(links, d, i, Vhp, m, t);
+        load12(g + d * n, s, y, Ls, m);
+        transport(links, d, i, m, t);
 #pragma unroll
         for (int k = 0; k < 12; ++k) {
             acc[k].x += t[k].x;
@@ -322,7 +306,7 @@ __global__ __launch_bounds__(256) void ptc_out_kernel(const float2* __restrict__
         const int ss = s + k - 2;
         if (ss < 0 || ss >= Ls) continue;
         float2 v[12];
-        load12(r, (long)ss * 12, i, Vhp, v);
+        load12(r, ss, i, Ls, v);
 #pragma unroll
         for (int lo = 112; lo >= 0; lo -= 112) {
             spin_apply(al + lo + k * 16, v, acc);
@@ -330,7 +314,7 @@ __global__ __launch_bounds__(256) void ptc_out_kernel(const float2* __restrict__
             if (k == 2 && s > 0) spin_apply(al + lo + 6 * 16, v, acc);
         }
     }
-    store12(out, (long)s * 12, i, Vhp, acc);
+    store12(out, s, i, Ls, acc);
 }
 
 // Correlations C[a][b] = sum_{site, s, colour} u_a conj(t_b), a, b = 0..31 = 4 x
@@ -348,7 +332,7 @@ __global__ __launch_bounds__(256) void ptc_out_kernel(const float2* __restrict__
 template <int LOCAL>
 __global__ __launch_bounds__(256) void ptc_corr_kernel(const float2* __restrict__ r, const float2* __restrict__ g,
                                                        const float2* __restrict__ links, const int* __restrict__ nbr,
-                                                       long Vh, long Vhp, int Ls, long ntiles,
+                                                       long Vh, int Ls, long ntiles,
                                                        double* __restrict__ partial) {
     constexpr int NK = 96, ST = 33;
     __shared__ double smem[4 * NK * ST / 2];
@@ -371,15 +355,15 @@ __global__ __launch_bounds__(256) void ptc_corr_kernel(const float2* __restrict_
         if (site < Vh) {
             if constexpr (LOCAL) {
                 const int ss = s + slot - 2;
-                if (slot < 5 && ss >= 0 && ss < Ls) load12(r, (long)ss * 12, site, Vhp, t);
-                if (slot == 0 || (slot == 1 && s + 1 < Ls) || (slot == 2 && s > 0)) load12(g, (long)s * 12, site, Vhp, u);
+                if (slot < 5 && ss >= 0 && ss < Ls) load12(r, ss, site, Ls, t);
+                if (slot == 0 || (slot == 1 && s + 1 < Ls) || (slot == 2 && s > 0)) load12(g, s, site, Ls, u);
             } else {
-                const long y = nbr[(long)slot * Vhp + site];
+                const long y = nbr[gidx(slot, site, 8)];
                 float2 v[12], v2[12];
-                load12(r, (long)s * 12, y, Vhp, v);
-                load12(g, (long)s * 12, y, Vhp, v2);
-                transport(links, slot, site, Vhp, v, t);
-                transport(links, slot, site, Vhp, v2, u);
+                load12(r, s, y, Ls, v);
+                load12(g, s, y, Ls, v2);
+                transport(links, slot, site, v, t);
+                transport(links, slot, site, v2, u);
             }
         }
         __syncthreads();   // the previous tile's reads
@@ -625,9 +609,9 @@ void ptc_pairs_gradient(const PtcPairParams& P, const float2* r, const float2* g
                         float2* G2, hipStream_t st) {
     const int nb = corr_blocks(P);
     double* c = corr + (size_t)2 * nb * 2048;
-    hipLaunchKernelGGL(ptc_corr_kernel<0>, dim3(nb), dim3(256), 0, st, r, g, P.links[1], P.nbr[1], P.Vh, P.Vhp, P.Ls,
+    hipLaunchKernelGGL(ptc_corr_kernel<0>, dim3(nb), dim3(256), 0, st, r, g, P.links[1], P.nbr[1], P.Vh, P.Ls,
                        corr_tiles(P), corr);
-    hipLaunchKernelGGL(ptc_corr_kernel<1>, dim3(nb), dim3(256), 0, st, r, g, P.links[0], P.nbr[0], P.Vh, P.Vhp, P.Ls,
+    hipLaunchKernelGGL(ptc_corr_kernel<1>, dim3(nb), dim3(256), 0, st, r, g, P.links[0], P.nbr[0], P.Vh, P.Ls,
                        corr_tiles(P), corr + (size_t)nb * 2048);
     hipLaunchKernelGGL(ptc_corr_finalize, dim3(64, 2), dim3(256), 0, st, corr, nb, c);
     hipLaunchKernelGGL(ptc_weight_grad, dim3((2 * 11 * P.H * 16 + PT - 1) / PT), dim3(PT), 0, st, c, P.W1, P.W2, P.H, G1,

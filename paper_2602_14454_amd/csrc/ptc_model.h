@@ -13,7 +13,7 @@ struct dwf_ptc {
     int loss_kind = 1;       // 0: |M r - e|^2/|e|^2;  1: |A (M r - e)|^2/|r|^2 = |A M r - r|^2/|r|^2
     dwf::DevBuf W, G, m, v, stats, pair_w;
     long cap_n = 0;
-    long lay_n = 0, lay_vhp = 0;   // field layout of the workspace's last use (its zero padding)
+    long lay_n = 0, lay_vh = 0;   // field layout of the workspace's last use (its zero padding)
     // hid: the intermediate fields (8 pair sums, or the two parities of one hidden channel)
     dwf::DevBuf hid, y, g, lpartial, corr, d, u, w, to, tv;
 

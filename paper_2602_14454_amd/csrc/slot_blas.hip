@@ -90,19 +90,18 @@ __global__ __launch_bounds__(BT) void bcg_p2_kernel(void* pd, const void* ps, co
         }
     } else {
         // operands in different layouts: four components of one site per step
-        // (slot offsets are multiples of 4 * Vhp complex, whole groups)
+        // (slot offsets are multiples of 4 * Vhp complex, whole tiles)
         const char* rb = static_cast<const char*>(r) + d.off * cbytes<SR>();
         const char* sb = static_cast<const char*>(ps) + d.off * cbytes<SP>();
         char* db = static_cast<char*>(pd) + d.off * cbytes<SP>();
         for (long t = (long)b * BT + threadIdx.x; t < d.n / 4; t += (long)d.nb * BT) {
-            const long g = t / d.Vhp, site = t - g * d.Vhp;
             typename Traits<SR>::R rv[8];
             RP pv[8];
-            load4<SR>(rb, g, site, d.Vhp, rv);
-            load4<SP>(sb, g, site, d.Vhp, pv);
+            load4<SR>(rb, t, rv);
+            load4<SP>(sb, t, pv);
 #pragma unroll
             for (int q = 0; q < 8; ++q) pv[q] = RP(rv[q]) + be * pv[q];
-            store4<SP>(db, g, site, d.Vhp, pv);
+            store4<SP>(db, t, pv);
         }
     }
 }
@@ -165,18 +164,17 @@ __global__ __launch_bounds__(BT) void bcg_accx_kernel(void* x, const void* ring,
         char* xb = static_cast<char*>(x) + d.off * cbytes<SX>();
         const char* pb = static_cast<const char*>(ring) + d.off * cbytes<SP>();
         for (long t = (long)b * BT + threadIdx.x; t < d.n / 4; t += (long)d.nb * BT) {
-            const long g = t / d.Vhp, site = t - g * d.Vhp;
             RX xv[8];
-            load4<SX>(xb, g, site, d.Vhp, xv);
+            load4<SX>(xb, t, xv);
             for (int q = 0; q < cnt; ++q) {
                 if (al[q] == 0.0) continue;
                 RP pv[8];
-                load4<SP>(pb + q * qb, g, site, d.Vhp, pv);
+                load4<SP>(pb + q * qb, t, pv);
                 const RX a = RX(al[q]);
 #pragma unroll
                 for (int k = 0; k < 8; ++k) xv[k] = xv[k] + a * RX(pv[k]);
             }
-            store4<SX>(xb, g, site, d.Vhp, xv);
+            store4<SX>(xb, t, xv);
         }
     }
 }

@@ -82,7 +82,6 @@ int cgnr(const dwf_op* op, CgWork& W, const void* b_kp, double tol_rel, int maxi
     // p lives in a ring of W.ring_len slots unless the caller wants x after
     // every iteration (on_iter)
     const bool ring = !on_iter;
-    const long Vhp = op->lat->Vhp;
     const size_t pbytes = complex_bytes_of(W.kp) * (size_t)n;
     if (ring && !W.ring.p) {
         W.ring_len = ring_slots(pbytes);
@@ -93,8 +92,8 @@ int cgnr(const dwf_op* op, CgWork& W, const void* b_kp, double tol_rel, int maxi
     auto slot = [&](int i) -> void* { return static_cast<char*>(W.ring.p) + (size_t)i * pbytes; };
     // r = D^dag b, p = r, x = 0
     apply_dhat(op, W.kp, 1, W.w.p, b_kp, W.t.p, W.v.p, W.nrhs, st);
-    convert(W.kx, W.kp, W.r.p, W.w.p, n, st, Vhp);
-    convert(W.kp, W.kx, ring ? slot(0) : W.p.p, W.r.p, n, st, Vhp);
+    convert(W.kx, W.kp, W.r.p, W.w.p, n, st);
+    convert(W.kp, W.kx, ring ? slot(0) : W.p.p, W.r.p, n, st);
     DWF_HIP(hipMemsetAsync(W.x.p, 0, complex_bytes_of(W.kx) * n, st));
     norm2_partial(W.kx, W.r.p, n, partial, st);
     finalize(partial, blas_grid(n), 1, scal + CG_RR, 0, st);
@@ -124,15 +123,15 @@ int cgnr(const dwf_op* op, CgWork& W, const void* b_kp, double tol_rel, int maxi
             ++pend;
             int nxt = cur + 1;
             if (nxt == W.ring_len) {
-                cg_accumulate_x(W.kx, W.kp, W.x.p, W.ring.p, alphas, pend, n, st, Vhp);
+                cg_accumulate_x(W.kx, W.kp, W.x.p, W.ring.p, alphas, pend, n, st);
                 pend = 0;
                 nxt = 0;
             }
-            cg_update_p2(W.kx, W.kp, slot(nxt), pk, W.r.p, n, scal + CG_BETA, st, Vhp);
+            cg_update_p2(W.kx, W.kp, slot(nxt), pk, W.r.p, n, scal + CG_BETA, st);
             cur = nxt;
         } else {
             // the x update rides on the p update, which reads p anyway
-            cg_update_px(W.kx, W.kp, W.x.p, W.p.p, W.r.p, n, scal + CG_ALPHA, scal + CG_BETA, st, Vhp);
+            cg_update_px(W.kx, W.kp, W.x.p, W.p.p, W.r.p, n, scal + CG_ALPHA, scal + CG_BETA, st);
         }
         ++k;
         if (on_iter) on_iter(k, W.x.p);
@@ -149,7 +148,7 @@ int cgnr(const dwf_op* op, CgWork& W, const void* b_kp, double tol_rel, int maxi
             rr_prev = rr;
         }
     }
-    if (ring) cg_accumulate_x(W.kx, W.kp, W.x.p, W.ring.p, alphas, pend, n, st, Vhp);
+    if (ring) cg_accumulate_x(W.kx, W.kp, W.x.p, W.ring.p, alphas, pend, n, st);
     if (final_rel) *final_rel = std::sqrt(rr / rr0);
     return k;
 }
@@ -165,7 +164,6 @@ int cgnr(const dwf_op* op, CgWork& W, const void* b_kp, double tol_rel, int maxi
 static int cgnr_right(const dwf_op* op, CgWork& W, const void* b_kp, double tol_rel, int maxiter, int check_every,
                       hipStream_t st, double* final_rel, bool* nan_seen) {
     const long n = W.n;
-    const long Vhp = op->lat->Vhp;
     double* partial = W.partial.as<double>();
     double* scal = W.scal.as<double>();
     Pinned& hs = W.hs;
@@ -182,8 +180,8 @@ static int cgnr_right(const dwf_op* op, CgWork& W, const void* b_kp, double tol_
     };
     DWF_HIP(hipMemsetAsync(W.scal.p, 0, CG_NSLOTS * sizeof(double), st));
     apply_rdag(W.w.p, b_kp);
-    convert(W.kx, W.kp, W.r.p, W.w.p, n, st, Vhp);
-    convert(W.kp, W.kx, W.p.p, W.r.p, n, st, Vhp);
+    convert(W.kx, W.kp, W.r.p, W.w.p, n, st);
+    convert(W.kp, W.kx, W.p.p, W.r.p, n, st);
     DWF_HIP(hipMemsetAsync(W.x.p, 0, complex_bytes_of(W.kx) * n, st));
     norm2_partial(W.kx, W.r.p, n, partial, st);
     finalize(partial, blas_grid(n), 1, scal + CG_RR, 0, st);
@@ -207,9 +205,9 @@ static int cgnr_right(const dwf_op* op, CgWork& W, const void* b_kp, double tol_
         mix(op, W.kp, W.w.p, rb, MAT_MT, nullptr, 1, st);
         apply_dhat(op, W.kp, 1, ra, rb, W.t.p, W.v.p, 1, st);
         mix(op, W.kp, ra, W.w.p, MAT_MIT, nullptr, 1, st);
-        cg_update_xr(W.kx, W.kp, W.x.p, W.r.p, W.p.p, W.w.p, n, scal + CG_ALPHA, partial, st, Vhp);
+        cg_update_xr(W.kx, W.kp, W.x.p, W.r.p, W.p.p, W.w.p, n, scal + CG_ALPHA, partial, st);
         finalize(partial, blas_grid(n), 1, scal, 2, st);
-        cg_update_p(W.kx, W.kp, W.p.p, W.r.p, n, scal + CG_BETA, st, Vhp);
+        cg_update_p(W.kx, W.kp, W.p.p, W.r.p, n, scal + CG_BETA, st);
         ++k;
         if (k % check_every == 0 || k == maxiter) {
             read_scalars(scal, hs, st);
@@ -260,8 +258,8 @@ static int cgnr_reliable(const dwf_op* op, CgWork& W, void* xe, const void* bt, 
     // r^ = b~ (x_hi = 0), r = D^dag r^
     convert(ST_F64, ST_F64, rh, bt, n, st);
     apply_dhat(op, ST_F64, 1, te, rh, to, tmp_e, 1, st);
-    convert(W.kx, ST_F64, W.r.p, te, n, st, op->lat->Vhp);
-    convert(W.kp, W.kx, W.p.p, W.r.p, n, st, op->lat->Vhp);
+    convert(W.kx, ST_F64, W.r.p, te, n, st);
+    convert(W.kp, W.kx, W.p.p, W.r.p, n, st);
     DWF_HIP(hipMemsetAsync(W.x.p, 0, complex_bytes_of(W.kx) * n, st));
     norm2_partial(W.kx, W.r.p, n, partial, st);
     finalize(partial, blas_grid(n), 1, scal + CG_RR, 0, st);
@@ -276,7 +274,7 @@ static int cgnr_reliable(const dwf_op* op, CgWork& W, void* xe, const void* bt, 
     while (k < maxiter) {
         apply_normal(op, W.kp, W.w.p, W.p.p, W.t.p, W.v.p, partial, W.nrhs, st);
         finalize(partial, hop_partials(op, W.nrhs), 1, scal, 1, st);
-        cg_update_xr(W.kx, W.kp, W.x.p, W.r.p, W.p.p, W.w.p, n, scal + CG_ALPHA, partial, st, op->lat->Vhp);
+        cg_update_xr(W.kx, W.kp, W.x.p, W.r.p, W.p.p, W.w.p, n, scal + CG_ALPHA, partial, st);
         finalize(partial, blas_grid(n), 1, scal, 2, st);
         ++k;
         if (k % check_every == 0 || k == maxiter) {
@@ -285,7 +283,7 @@ static int cgnr_reliable(const dwf_op* op, CgWork& W, void* xe, const void* bt, 
             if (hs.h[CG_NANFLAG] != 0.0 || !std::isfinite(rr)) { *nan_seen = true; break; }
             if (rr < delta * delta * rmax2 || rr < target || k == maxiter) {
                 // reliable update: fold x_lo into x_hi and recompute the residual in FP64
-                axpby(ST_F64, W.kx, xe, W.x.p, n, nullptr, 1.0, nullptr, 1.0, nullptr, st, op->lat->Vhp);
+                axpby(ST_F64, W.kx, xe, W.x.p, n, nullptr, 1.0, nullptr, 1.0, nullptr, st);
                 DWF_HIP(hipMemsetAsync(W.x.p, 0, complex_bytes_of(W.kx) * n, st));
                 apply_dhat(op, ST_F64, 0, te, xe, to, tmp_e, 1, st);
                 convert(ST_F64, ST_F64, rh, bt, n, st);
@@ -295,7 +293,7 @@ static int cgnr_reliable(const dwf_op* op, CgWork& W, void* xe, const void* bt, 
                 ++*nupdates;
                 if (rel5 <= tol || k == maxiter) break;
                 apply_dhat(op, ST_F64, 1, te, rh, to, tmp_e, 1, st);
-                convert(W.kx, ST_F64, W.r.p, te, n, st, op->lat->Vhp);
+                convert(W.kx, ST_F64, W.r.p, te, n, st);
                 norm2_partial(W.kx, W.r.p, n, partial, st);
                 finalize(partial, blas_grid(n), 1, scal, 3, st);
                 read_scalars(scal, hs, st);
@@ -311,7 +309,7 @@ static int cgnr_reliable(const dwf_op* op, CgWork& W, void* xe, const void* bt, 
                 rmax2 = std::max(rmax2, rr);
             }
         }
-        cg_update_p(W.kx, W.kp, W.p.p, W.r.p, n, scal + CG_BETA, st, op->lat->Vhp);
+        cg_update_p(W.kx, W.kp, W.p.p, W.r.p, n, scal + CG_BETA, st);
     }
     if (*nan_seen) return k;
     *rel5_out = rel5;
@@ -460,7 +458,7 @@ int solve(const dwf_op* op, void* x5, const void* b5, const dwf_solve_params* pr
     while (prm->algo != DWF_ALGO_MIXED && !converged && total < maxiter && outer < 100) {
         const int kx = kp == ST_F64 ? ST_F64 : ST_F32;
         if (W->kp != kp) W = &solve_cg(ws, op, kp);
-        convert(kp, ST_F64, rin.p, rh.p, n, st, Vhp);
+        convert(kp, ST_F64, rin.p, rh.p, n, st);
         // FP64: the first step is the textbook CGNR stop; restarts are calibrated
         const bool plain = prm->paper_mode || (kp == ST_F64 && outer == 0);
         bool last_step = false;
@@ -483,10 +481,10 @@ int solve(const dwf_op* op, void* x5, const void* b5, const dwf_solve_params* pr
         } else if (right_schur) {
             // the right system for the current residual: D_R y = M r^, then x_e += M^-1 y
             mix(op, ST_F64, rh.p, te.p, MAT_M, nullptr, 1, st);
-            convert(kp, ST_F64, rin.p, te.p, n, st, Vhp);
+            convert(kp, ST_F64, rin.p, te.p, n, st);
             it = cgnr_right(op, *W, rin.p, itol, maxiter - total, prm->check_every, st, &last_inner_rel, &nan_seen);
             total += it;
-            convert(ST_F64, kx, te.p, W->x.p, n, st, Vhp);
+            convert(ST_F64, kx, te.p, W->x.p, n, st);
             mix(op, ST_F64, te.p, to.p, MAT_MINV, nullptr, 1, st);
             xin = to.p;
         } else {
@@ -505,7 +503,7 @@ int solve(const dwf_op* op, void* x5, const void* b5, const dwf_solve_params* pr
         }
         ++outer;
         if (nan_seen) break;
-        axpby(ST_F64, right_schur ? ST_F64 : kx, xe.p, xin, n, nullptr, 1.0, nullptr, 1.0, nullptr, st, Vhp);
+        axpby(ST_F64, right_schur ? ST_F64 : kx, xe.p, xin, n, nullptr, 1.0, nullptr, 1.0, nullptr, st);
         // r^ = b~ - D^ xe (FP64), formed where D^ xe was written; the buffers
         // then trade names so that rh holds r^.  r5_e = -M r^ with |M r^|^2
         // reduced by the mix itself; r5_o = 0 exactly after reconstruction.

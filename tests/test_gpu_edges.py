@@ -239,3 +239,33 @@ def test_eo5_tiles(dims, Ls, prec):
         op.apply_eo5(out, _dev(x), dagger, prec)
         got = out.cpu().numpy()
         assert _rel(got, eo5.dhat5(p, U, x, dagger=dagger)) < TOL[prec] and np.all(got[odd] == 0)
+
+
+# sites per parity 8 (half a tile of 16), 16, 24, 72 (remainder 8), 1008
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (2, 2, 2, 4), (2, 2, 6, 2), (6, 6, 2, 2), (6, 6, 4, 14)])
+def test_neighbour_table_tiles(dims):
+    """The device's neighbour table, read back through its tiles, names the sites next to each site."""
+    import paper_2602_14454_amd as dwf
+    lex, nbr = dwf.Lattice(dims).maps()
+    step = np.cumprod((1,) + dims[:3])
+    for d in range(8):
+        mu, n = d % 4, dims[d % 4]
+        c = lex // step[mu] % n
+        assert np.array_equal(nbr[:, d], lex + ((c + (1 if d < 4 else -1)) % n - c) * step[mu])
+
+
+def test_network_on_lattices_of_equal_tiles():
+    """One model on 80 and then 72 sites per parity (both five tiles): the second lattice's padding is clean."""
+    import paper_2602_14454_amd as dwf
+    from oracle import ptc as optc
+    first, second = _make((2, 2, 4, 10), 3)[:2], _make((6, 6, 2, 2), 3)[:2]
+    W = optc.random_weights(4, 5)
+    got = []
+    for ops in ((first, second), (second,)):
+        M = dwf.PtcModel(4)
+        M.set_weights(*W)
+        for lat, op in ops:
+            r, e = (_dev(np.ascontiguousarray(dwfgen.gaussian_source_5d(lat.dims, op.Ls, k)[:, : lat.Vh])) for k in (6, 7))
+            loss, (g1, g2) = M.gradient(op, r, e)
+        got.append((loss, g1, g2))
+    assert got[0][0] == got[1][0] and np.array_equal(got[0][1], got[1][1]) and np.array_equal(got[0][2], got[1][2])

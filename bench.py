@@ -65,7 +65,7 @@ def workload_name(c):
 
 def source_hash():
     h = hashlib.sha256()
-    for f in ("hop_tile.h", "hop.hip", "hop.h", "precision.h"):
+    for f in ("cg_scalars.h", "hop_tile.h", "hop.hip", "hop.h", "precision.h"):
         with open(os.path.join(ROOT, "paper_2602_14454_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

@@ -42,8 +42,17 @@ void axpby(int ky, int kx, void* y, const void* x, long n, const double* sa, dou
 void cg_update_xr(int kx, int kp, void* x, void* r, const void* p, const void* w, long n, const double* alpha,
                   double* partial, hipStream_t st);
 void cg_update_p(int kr, int kp, void* p, const void* r, long n, const double* beta, hipStream_t st);
+// beta of a step: read from `beta`, or (sum != nullptr) formed from the nsum partials of the new |r|^2, with
+// the step's scalars stored in scal and, if given, |r|^2 and the NaN flag in host (page-locked memory)
+struct CgBeta {
+    const double* beta;
+    const double* sum;
+    int nsum;
+    double* scal;
+    double* host;
+};
 // p_dst = r + beta p_src (r of kind kr; p_src, p_dst of kind kp, distinct buffers)
-void cg_update_p2(int kr, int kp, void* p_dst, const void* p_src, const void* r, long n, const double* beta,
+void cg_update_p2(int kr, int kp, void* p_dst, const void* p_src, const void* r, long n, const CgBeta& beta,
                   hipStream_t st);
 // x += sum_{i < cnt} alpha[i] p_i, p_i = p_ring + i * n elements of kind kp, added in order i = 0, 1, ...
 // with x (kind kx) rounded after each term, as cnt successive x += alpha p updates

@@ -8,6 +8,7 @@
 #include <type_traits>
 
 #include "blas.h"
+#include "cg_scalars.h"
 #include "dwf_internal.h"
 #include "precision.h"
 
@@ -330,9 +331,9 @@ __global__ void cg_p_remap_kernel(void* p, const void* r, long nquads, const dou
 
 // p_dst = r + beta p_src
 template <class SR, class SP>
-__global__ void cg_p2_kernel(void* pd, const void* ps, const void* r, long n, const double* beta) {
+__global__ void cg_p2_kernel(void* pd, const void* ps, const void* r, long n, CgBeta beta) {
     using RP = typename Traits<SP>::R;
-    const RP b = RP(*beta);
+    const RP b = RP(beta_of(beta));
     for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
         typename Traits<SR>::R rr, ri;
         RP pr, pi;
@@ -343,9 +344,9 @@ __global__ void cg_p2_kernel(void* pd, const void* ps, const void* r, long n, co
 }
 template <class SR, class SP>
 __global__ void cg_p2_remap_kernel(void* pd, const void* ps, const void* r, long nquads,
-                                   const double* beta) {
+                                   CgBeta beta) {
     using RP = typename Traits<SP>::R;
-    const RP b = RP(*beta);
+    const RP b = RP(beta_of(beta));
     for (long t = (long)blockIdx.x * blockDim.x + threadIdx.x; t < nquads; t += (long)gridDim.x * blockDim.x) {
         typename Traits<SR>::R rv[8];
         RP pv[8];
@@ -404,9 +405,9 @@ __global__ __launch_bounds__(256) void cg_accx_f32_kernel(float4* __restrict__ x
 
 // FP32 p_dst = r + beta p_src, 2 x 16 bytes per lane, all loads first
 __global__ __launch_bounds__(256) void cg_p2_f32_kernel(float4* __restrict__ pd, const float4* __restrict__ ps,
-                                                        const float4* __restrict__ r, long n2, const double* beta) {
+                                                        const float4* __restrict__ r, long n2, CgBeta beta) {
     const long i0 = (long)blockIdx.x * 512 + threadIdx.x;
-    const float b = (float)*beta;
+    const float b = (float)beta_of(beta);
     float4 rv[2], pv[2];
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
@@ -655,16 +656,16 @@ __global__ __launch_bounds__(FIN_THREADS) void finalize_kernel(const double* par
             out[0] = sum;
         } else if (mode == 1) {
             out[CG_QQ] = sum;
-            out[CG_ALPHA] = (sum > 0.0 && isfinite(sum)) ? out[CG_RR] / sum : 0.0;
+            out[CG_ALPHA] = cg_alpha(out[CG_RR], sum);
             if (alpha_copy) *alpha_copy = out[CG_ALPHA];
         } else if (mode == 2) {
             out[CG_RRNEW] = sum;
-            out[CG_BETA] = out[CG_RR] > 0.0 ? sum / out[CG_RR] : 0.0;
+            out[CG_BETA] = cg_beta(sum, out[CG_RR]);
             out[CG_RROLD] = out[CG_RR];
             out[CG_RR] = sum;
         } else if (mode == 3) {
             out[CG_RRNEW] = sum;
-            out[CG_BETA] = out[CG_RROLD] > 0.0 ? sum / out[CG_RROLD] : 0.0;
+            out[CG_BETA] = cg_beta(sum, out[CG_RROLD]);
             out[CG_RR] = sum;
         }
     }
@@ -967,7 +968,7 @@ void cg_update_px(int kx, int kp, void* x, void* p, const void* r, long n, const
 }
 
 template <class SR, class SP>
-static void cg_p2_t2(void* pd, const void* ps, const void* r, long n, const double* beta, hipStream_t st) {
+static void cg_p2_t2(void* pd, const void* ps, const void* r, long n, const CgBeta& beta, hipStream_t st) {
     if constexpr (std::is_same<SR, float>::value && std::is_same<SP, float>::value) {
         if (n % 2 == 0) {
             const long n2 = n / 2;
@@ -984,7 +985,7 @@ static void cg_p2_t2(void* pd, const void* ps, const void* r, long n, const doub
                            n / 4, beta);
 }
 template <class SR>
-static void cg_p2_t1(int kp, void* pd, const void* ps, const void* r, long n, const double* beta,
+static void cg_p2_t1(int kp, void* pd, const void* ps, const void* r, long n, const CgBeta& beta,
                      hipStream_t st) {
     switch (kp) {
         case ST_F64: cg_p2_t2<SR, double>(pd, ps, r, n, beta, st); break;
@@ -993,7 +994,7 @@ static void cg_p2_t1(int kp, void* pd, const void* ps, const void* r, long n, co
         default: throw Error{DWF_EINVAL, "bad storage kind"};
     }
 }
-void cg_update_p2(int kr, int kp, void* p_dst, const void* p_src, const void* r, long n, const double* beta,
+void cg_update_p2(int kr, int kp, void* p_dst, const void* p_src, const void* r, long n, const CgBeta& beta,
                   hipStream_t st) {
     if (fpack_of(kr) != fpack_of(kp))
         DWF_REQUIRE(n % 64 == 0, DWF_EINVAL, "layout change needs whole tiles");

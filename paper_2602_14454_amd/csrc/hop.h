@@ -40,6 +40,13 @@ struct HopParams {
     void* upd;
     const double* upd_alpha;   // alpha of right-hand side r at upd_alpha[r * upd_stride]
     long upd_stride;
+    // sum != nullptr: alpha is formed from the nsum partials of |D^ p|^2 instead,
+    // and stored with the step's other scalars (cg_scalars.h); `partial` must not
+    // overlap them
+    const double* sum;
+    int nsum;
+    double* scal;
+    double* alpha_copy;
     // work-list (batch) launches only
     const double* done;    // per-RHS done flags, done[r * done_stride] != 0: skip (nullptr: none)
     long done_stride;

@@ -96,6 +96,7 @@ static unsigned hop_min_lds() {
 template <class S, int TAG, int PM, int EK>
 static void launch_hop_ek(const HopParams& P, int nrhs, hipStream_t st) {
     const int KK = (P.Ls + 3) / 4;
+    DWF_REQUIRE(!P.sum || (EK == EK_UPDS && KK > 1), DWF_EINVAL, "this form of the hop reads alpha");
     dim3 grid(hop_grid_blocks(P.Vh), nrhs), block(64 * hop_waves(KK, sizeof(S) == 8));
     const unsigned smem_b = std::max(hop_smem_bytes<S>(KK, P.loc != nullptr), hop_min_lds());
     switch (KK) {
@@ -135,6 +136,7 @@ static void launch_hop_pm(const HopParams& P, int nrhs, hipStream_t st) {
             case EK_PLAIN: launch_hop_ek<S, TAG, PM, EK_PLAIN>(P, nrhs, st); break;
             case EK_CHAIN: launch_hop_ek<S, TAG, PM, EK_CHAIN>(P, nrhs, st); break;
             case EK_UPD: launch_hop_ek<S, TAG, PM, EK_UPD>(P, nrhs, st); break;
+            case EK_UPDS: launch_hop_ek<S, TAG, PM, EK_UPDS>(P, nrhs, st); break;
             case EK_LOCD: launch_hop_ek<S, TAG, PM, EK_LOCD>(P, nrhs, st); break;
             case EK_LOCI: launch_hop_ek<S, TAG, PM, EK_LOCI>(P, nrhs, st); break;
             case EK_CHAINN: launch_hop_ek<S, TAG, PM, EK_CHAINN>(P, nrhs, st); break;

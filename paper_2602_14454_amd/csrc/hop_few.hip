@@ -50,6 +50,7 @@ bool launch_hop_few(const HopParams& P, int nrhs, int ek, hipStream_t st) {
         case EK_PLAIN: return launch_few<0, EK_PLAIN>(P, nrhs, st);
         case EK_CHAIN: return launch_few<0, EK_CHAIN>(P, nrhs, st);
         case EK_UPD: return launch_few<0, EK_UPD>(P, nrhs, st);
+        case EK_UPDS: return launch_few<0, EK_UPDS>(P, nrhs, st);
         case EK_LOCD: return launch_few<0, EK_LOCD>(P, nrhs, st);
         case EK_LOCI: return launch_few<0, EK_LOCI>(P, nrhs, st);
         case EK_CHAINN: return launch_few<0, EK_CHAINN>(P, nrhs, st);

@@ -34,6 +34,7 @@
 
 #include <type_traits>
 
+#include "cg_scalars.h"
 #include "dwf_internal.h"
 #include "hop.h"
 #include "precision.h"
@@ -590,13 +591,15 @@ template <class S> constexpr int lnk_entries() { return 8 * link_ng(cbytes<S>())
 //     |first result|^2 reduced; EK_CHAINN: without the reduction.
 //   EK_UPD: the last CG stage, upd -= alpha (POST . H + LOCMIX . loc) with
 //     |upd|^2 reduced.
+//   EK_UPDS: EK_UPD with alpha formed here from few partials (HopParams::sum).
 //   EK_LOCD: out = POST . H + LOCMIX . loc; EK_LOCI: out = POST . H + loc_scale loc.
-constexpr int EK_PLAIN = 1, EK_CHAIN = 2, EK_UPD = 3, EK_LOCD = 4, EK_LOCI = 5, EK_CHAINN = 6;
+constexpr int EK_PLAIN = 1, EK_CHAIN = 2, EK_UPD = 3, EK_LOCD = 4, EK_LOCI = 5, EK_CHAINN = 6, EK_UPDS = 7;
+constexpr bool ek_upd(int ek) { return ek == EK_UPD || ek == EK_UPDS; }
 constexpr bool ek_chain(int ek) { return ek == EK_CHAIN || ek == EK_CHAINN; }
 inline int epilogue_kind(const HopParams& P) {
     if (P.partial && P.reduce == 0) return -1;
     const bool reduce = P.partial != nullptr;
-    if (P.upd) return !P.out && P.loc && P.locmix && !P.out2 && reduce && P.reduce == 3 ? EK_UPD : -1;
+    if (P.upd) return !P.out && P.loc && P.locmix && !P.out2 && reduce && P.reduce == 3 ? (P.sum ? EK_UPDS : EK_UPD) : -1;
     if (P.out2) {
         if (P.out || !P.loc || P.locmix || !P.chain2) return -1;
         return reduce ? (P.reduce == 1 ? EK_CHAIN : -1) : EK_CHAINN;
@@ -668,12 +671,12 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
     constexpr bool EKC = EK >= 0;
     const bool f_out = EKC ? (EK == EK_PLAIN || EK == EK_LOCD || EK == EK_LOCI) : P.out != nullptr;
     const bool f_loc = EKC ? EK != EK_PLAIN : P.loc != nullptr;
-    const bool f_dense = EKC ? (EK == EK_UPD || EK == EK_LOCD) : (P.loc != nullptr && P.locmix != nullptr);
+    const bool f_dense = EKC ? (ek_upd(EK) || EK == EK_LOCD) : (P.loc != nullptr && P.locmix != nullptr);
     const bool f_out2 = EKC ? ek_chain(EK) : P.out2 != nullptr;
     const bool f_chain = EKC ? ek_chain(EK) : (P.out2 != nullptr && P.chain2 != 0);
-    const bool f_upd = EKC ? EK == EK_UPD : P.upd != nullptr;
-    const int f_reduce = EKC ? (EK == EK_CHAIN ? 1 : (EK == EK_UPD ? 3 : 0)) : P.reduce;
-    const bool f_partial = EKC ? (EK == EK_CHAIN || EK == EK_UPD) : P.partial != nullptr;
+    const bool f_upd = EKC ? ek_upd(EK) : P.upd != nullptr;
+    const int f_reduce = EKC ? (EK == EK_CHAIN ? 1 : (ek_upd(EK) ? 3 : 0)) : P.reduce;
+    const bool f_partial = EKC ? (EK == EK_CHAIN || ek_upd(EK)) : P.partial != nullptr;
     constexpr int NW = hop_waves(KK, sizeof(S) == 8);
     constexpr int NTHR = 64 * NW;
     unsigned char* own = smem + (size_t)sub * region;
@@ -745,6 +748,9 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
         }
     }
 
+    R ua_sum = R(0);
+    double sv[CG_FEW / 64];
+    if constexpr (EK == EK_UPDS) load_few(P.sum, P.nsum, sv);
     constexpr bool SBATCH = LAT || (sizeof(S) == 8 ? DWF_HOP_STAGE_BATCH64 : DWF_HOP_STAGE_BATCH);
     // the tile's links and neighbours: contiguous, entries past the last site are
     // zero (site 0); a neighbour is staged as the byte offset of its groups.  (The
@@ -847,11 +853,11 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
     R lre[LOCE ? CPW_ : 1][LOCE ? KK : 1], lie[LOCE ? CPW_ : 1][LOCE ? KK : 1];
     // the update stage's old values (its 16-byte groups of this thread),
     // requested with the local term
-    constexpr bool UPDE = LOCE && DWF_HOP_UPD_EARLY32 && EK == EK_UPD;
+    constexpr bool UPDE = LOCE && DWF_HOP_UPD_EARLY32 && ek_upd(EK);
     constexpr int IUE = UPDE ? (4 * KK * 6 * 16 + NTHR - 1) / NTHR : 1;
     u32x4 uve[IUE];
     // LAT, FP64: the update stage's old values per component and row
-    constexpr bool UPDL = LAT && sizeof(S) == 8 && EK == EK_UPD;
+    constexpr bool UPDL = LAT && sizeof(S) == 8 && ek_upd(EK);
     u32x4 uvl[UPDL ? CPW_ : 1][4];
     R h[G][24];
     // A operands: A[m][k] = MAT[chi][row m = j][col 4*kk + sc].  A dense
@@ -894,6 +900,7 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
         for (int g = 0; g < G; ++g)
 #pragma unroll
             for (int k = 0; k < 24; ++k) h[g][k] = 0;
+        if constexpr (EK == EK_UPDS && PF != 3) ua_sum = R(alpha_of_partials(sv, P.scal, P.alpha_copy, blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0));
         // Loop over the 8 hop directions.  Its unrolling (DWF_HOP_UNROLL)
         // trades registers for loads in flight: with 1, nothing of direction
         // d+1 (its links in particular) is hoisted above direction d.
@@ -936,6 +943,7 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
                 if constexpr (PM == 2) hop_fetch2<S, G>(P, R_, sg, yd[d], rm[d], rp[d]);
             }
             __builtin_amdgcn_sched_barrier(0);
+            if constexpr (EK == EK_UPDS) ua_sum = R(alpha_of_partials(sv, P.scal, P.alpha_copy, blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0));
 #pragma unroll
             for (int d = 0; d < 8; ++d) {
                 hop_apply<S, G, PM, PM == 2>(P, R_, d, sg, pd, pe, kr, h, lnk, rd[d % ND], yd[d % ND], j,
@@ -1038,7 +1046,9 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
     // FP32/BF16: the primary output (out, else out2) goes through LDS; a
     // second output, if any, is stored directly
     const bool upd = f_upd;
-    const R ua = upd ? R(P.upd_alpha[(long)rhs * P.upd_stride]) : R(0);
+    R ua = R(0);
+    if constexpr (EK == EK_UPDS) ua = ua_sum;
+    else if (upd) ua = R(P.upd_alpha[(long)rhs * P.upd_stride]);
     const bool tile_out = L::TIO && (f_out || has_out2 || upd);
     // byte offset of component cp of slice s of this lane's site; the whole
     // offset goes to the vector operand (cp depends on the wave index, which

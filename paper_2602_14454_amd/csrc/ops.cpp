@@ -17,6 +17,7 @@
 
 #include "blas.h"
 #include "hop.h"
+#include "cg_scalars.h"
 #include "precision.h"
 
 namespace dwf {
@@ -117,7 +118,7 @@ void apply_normal(const dwf_op* op, int kind, void* out_e, const void* in_e, voi
 }
 
 void apply_normal_update_r(const dwf_op* op, int kind, void* r, const void* p, void* tmp_o, void* tmp_v,
-                           double* partial, double* scal, int nrhs, hipStream_t st, double* alpha_copy) {
+                           double* partial, double* scal, int nrhs, hipStream_t st, double* alpha_copy, bool few) {
     hop(op, kind, 1, p, nullptr, tmp_o, PRE_K, MAT_Q, -1, 0.0, nullptr, 0, 0, nullptr, 0, nrhs, st);
     {
         HopParams P = hop_params(op, kind, 0, tmp_o, p, nullptr, -1, MAT_MQMINV, -1, 1.0, tmp_v,
@@ -125,14 +126,31 @@ void apply_normal_update_r(const dwf_op* op, int kind, void* r, const void* p, v
         P.chain2 = DWF_CHAIN2;
         launch_hop(kind, P, nrhs, st);
     }
-    finalize(partial, hop_partials(op, nrhs), 1, scal, 1, st, alpha_copy);   // alpha
+    const int np = hop_partials(op, nrhs);
+    if (!few) finalize(partial, np, 1, scal, 1, st, alpha_copy);   // alpha
     hop(op, kind, 1, tmp_v, nullptr, tmp_o, -1, MAT_QT, -1, 0.0, nullptr, 0, 0, nullptr, 0, nrhs, st);
     HopParams P = hop_params(op, kind, 0, tmp_o, tmp_v, nullptr, -1, MAT_MQG5KT, MAT_G5MT, 0.0, nullptr, 0, 0,
                              partial, 3);
     P.upd = r;
     P.upd_alpha = scal + CG_ALPHA;
+    if (few) {
+        P.sum = partial;
+        P.nsum = np;
+        P.scal = scal;
+        P.alpha_copy = alpha_copy;
+        P.partial = partial + np;
+    }
     launch_hop(kind, P, nrhs, st);
 }
+
+// Whether a CG step's sums are formed where they are used: saves two launches a
+// step, but every wave of the consumers reads all partials.  Microseconds per
+// iteration, residual read every / every 8th iteration, FP64 and FP32 inside
+// defect correction, before -> after: 8^4, Ls = 8 (128 partials) 68 / 53 -> 61 / 50
+// and 59 / 45 -> 51 / 42; 8^3x16, Ls = 12 (256) 82 / 71 -> 78 / 70 and 61 / 48 ->
+// 54 / 45; with 512 partials (8^2x16^2, Ls = 16) 137 / 123 -> 133 / 122 and 84 / 73
+// -> 83 / 74, with 648 and 1024 up to 10 us more.
+bool cg_few(const dwf_op* op, int nrhs) { return hop_partials(op, nrhs) <= CG_FEW && op->Ls > 4; }
 
 void apply_full(const dwf_op* op, int kind, int dagger, void* out_e, void* out_o, const void* in_e,
                 const void* in_o, int nrhs, hipStream_t st) {

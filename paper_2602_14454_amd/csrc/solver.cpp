@@ -82,6 +82,9 @@ int cgnr(const dwf_op* op, CgWork& W, const void* b_kp, double tol_rel, int maxi
     // p lives in a ring of W.ring_len slots unless the caller wants x after
     // every iteration (on_iter)
     const bool ring = !on_iter;
+    // small lattices: alpha and beta are formed by the kernels that use them
+    const bool few = ring && cg_few(op, W.nrhs);
+    const int np = hop_partials(op, W.nrhs);
     const size_t pbytes = complex_bytes_of(W.kp) * (size_t)n;
     if (ring && !W.ring.p) {
         W.ring_len = ring_slots(pbytes);
@@ -115,8 +118,9 @@ int cgnr(const dwf_op* op, CgWork& W, const void* b_kp, double tol_rel, int maxi
         // alpha, then r -= alpha D^dag D^ p inside the last hop (|r|^2 partials)
         void* pk = ring ? slot(cur) : W.p.p;
         apply_normal_update_r(op, W.kp, W.r.p, pk, W.t.p, W.v.p, partial, scal, W.nrhs, st,
-                              ring ? alphas + cur : nullptr);
-        finalize(partial, hop_partials(op, W.nrhs), 1, scal, 2, st);
+                              ring ? alphas + cur : nullptr, few);
+        if (!few) finalize(partial, np, 1, scal, 2, st);
+        const bool check = k + 1 == next_check || k + 1 == maxiter;
         if (ring) {
             // p_{k+1} = r + beta p_k into the next slot; a full ring is folded
             // into x first (x += alpha_i p_i in order, as the per-iteration update)
@@ -127,7 +131,8 @@ int cgnr(const dwf_op* op, CgWork& W, const void* b_kp, double tol_rel, int maxi
                 pend = 0;
                 nxt = 0;
             }
-            cg_update_p2(W.kx, W.kp, slot(nxt), pk, W.r.p, n, scal + CG_BETA, st);
+            const CgBeta beta = {scal + CG_BETA, few ? partial + np : nullptr, np, scal, few && check ? hs.h : nullptr};
+            cg_update_p2(W.kx, W.kp, slot(nxt), pk, W.r.p, n, beta, st);
             cur = nxt;
         } else {
             // the x update rides on the p update, which reads p anyway
@@ -135,8 +140,9 @@ int cgnr(const dwf_op* op, CgWork& W, const void* b_kp, double tol_rel, int maxi
         }
         ++k;
         if (on_iter) on_iter(k, W.x.p);
-        if (k == next_check || k == maxiter) {
-            read_scalars(scal, hs, st);
+        if (check) {
+            if (few) DWF_HIP(hipStreamSynchronize(st));   // the p update wrote hs
+            else read_scalars(scal, hs, st);
             rr = hs.h[CG_RR];
             if (hs.h[CG_NANFLAG] != 0.0 || !std::isfinite(rr)) {
                 *nan_seen = true;

@@ -269,3 +269,24 @@ def test_network_on_lattices_of_equal_tiles():
             loss, (g1, g2) = M.gradient(op, r, e)
         got.append((loss, g1, g2))
     assert got[0][0] == got[1][0] and np.array_equal(got[0][1], got[1][1]) and np.array_equal(got[0][2], got[1][2])
+
+
+# 1, 9 and 256 partials (summed by the kernels that use them), 288 (by a kernel of its own); Ls = 4: always so
+@pytest.mark.parametrize("dims,Ls", [((2, 2, 2, 2), 5), ((2, 6, 6, 4), 8), ((8, 8, 8, 16), 5), ((8, 8, 8, 18), 5),
+                                     ((4, 4, 4, 4), 4)])
+@pytest.mark.parametrize("prec", [0, 1, 2])
+def test_cg_scalars_by_lattice_size(dims, Ls, prec):
+    """CG with its step lengths formed in the hop and in the p update: convergence to the oracle's residual
+    for any check period."""
+    import torch
+
+    import paper_2602_14454_amd as dwf
+    lat, op, p, U = _make(dims, Ls)
+    b = dwfgen.gaussian_source_5d(dims, Ls, 12)
+    x = torch.zeros(b.shape, dtype=torch.complex128, device="cuda")
+    for check in (1, 3):
+        prm = dwf.default_params(algo=dwf.ALGO_DC if prec else dwf.ALGO_CGNR, inner_prec=prec, check_every=check, tol=1e-10)
+        x.zero_()
+        st, info = op.solve(x, _dev(b), prm)
+        assert st == 0 and info.converged
+        assert oracle.true_residual(p, U, x.cpu().numpy(), b) <= 1.2e-10

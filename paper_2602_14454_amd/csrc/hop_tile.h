@@ -213,15 +213,6 @@ __device__ __forceinline__ int out_row(int sc, int i) {
     else return 4 * sc + i;
 }
 
-// Workgroups are dealt to the 8 XCDs round-robin (workgroup b runs on XCD
-// b % 8), and each XCD has its own L2.  Remap so that XCD x sweeps one
-// contiguous range of logical blocks: the y/z/t neighbours a block reads
-// were then mostly fetched by the same XCD a few blocks earlier.
-__device__ __forceinline__ int xcd_block(int b, int nb) {
-    const int x = b & 7, j = b >> 3, q = nb >> 3, r = nb & 7;
-    return x * q + min(x, r) + j;
-}
-
 // ---------------------------------------------------------------------
 // One hop direction: h += (1 + SG*gamma_MU) * U * p, spin-projected.
 // Chiral basis gamma_mu = [[0, B],[B^dag, 0]] on (upper spins 0,1 | lower 2,3)

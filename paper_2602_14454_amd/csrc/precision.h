@@ -342,6 +342,15 @@ __device__ __forceinline__ void decode_link_group(u32x4 w, int g, typename Trait
     }
 }
 
+// Workgroups are dealt to the 8 XCDs round-robin (workgroup b runs on XCD
+// b % 8), and each XCD has its own L2.  Remap so that XCD x sweeps one
+// contiguous range of logical blocks: the y/z/t neighbours a block reads
+// were then mostly fetched by the same XCD a few blocks earlier.
+__device__ __forceinline__ int xcd_block(int b, int nb) {
+    const int x = b & 7, j = b >> 3, q = nb >> 3, r = nb & 7;
+    return x * q + min(x, r) + j;
+}
+
 inline size_t complex_bytes(int kind) { return kind == 0 ? 16 : kind == 1 ? 8 : 4; }
 
 }  // namespace dwf

@@ -60,7 +60,7 @@ dwf_ptc::dwf_ptc(int hidden) : H(hidden) {
     m.alloc(2 * nw * sizeof(float));
     v.alloc(2 * nw * sizeof(float));
     stats.alloc(8 * sizeof(double));
-    pair_w.alloc(4096 * sizeof(float) + 2 * 7 * 16 * sizeof(float2));
+    pair_w.alloc(4096 * sizeof(float) + 2 * 8 * 16 * sizeof(float2));
 }
 
 const float2* dwf_ptc::W1() const { return W.as<float2>(); }
@@ -85,7 +85,7 @@ static PtcPairParams pair_params(const dwf_ptc* M, const dwf_op* op) {
 }
 
 // Pair sums for two and more hidden channels: their cost does not grow with the
-// channels (16^3x32, Ls = 16: 0.67 ms).  The layers take 0.48 ms with one
+// channels (16^3x32, Ls = 16: 0.59 ms).  The layers take 0.48 ms with one
 // channel, 0.71 ms with two, 2.5 ms with eight (8^4, Ls = 8: 36, 54 and 135 us
 // against 47).
 static bool by_pairs(int H) { return H >= 2; }

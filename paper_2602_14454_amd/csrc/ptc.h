@@ -28,7 +28,7 @@ struct PtcPairParams {
     int Ls, H;
     float2* mid;                 // 8 half fields
     float* el;                   // 4096 floats: pair weights of the links
-    float2* al;                  // 2 * 7 * 16: pair weights of the local paths and their rounding
+    float2* al;                  // 2 * 8 * 16: pair weights of the local paths and their rounding
 };
 void ptc_pairs_forward(const PtcPairParams& P, const float2* r, float2* out, hipStream_t st);
 // dL/dW of both layers from r and g = dL/d(out); corr: ptc_corr_bytes of scratch

@@ -52,17 +52,18 @@ __device__ __forceinline__ void store12(float2* f, int s, long i, int Ls, const 
             make_float4(v[2 * q].x, v[2 * q].y, v[2 * q + 1].x, v[2 * q + 1].y);
 }
 
-// t = L v on every spin (L: 9 complex of direction d at site i; FP32 links
-// in pairs, one 16-byte load per pair)
-__device__ __forceinline__ void transport(const float2* links, int d, long i, const float2 (&v)[12],
-                                          float2 (&t)[12]) {
-    float2 L[10];
+// the link of direction d at site i (9 complex; pairs, one 16-byte load each)
+__device__ __forceinline__ void load_link(const float2* links, int d, long i, float2 (&L)[10]) {
 #pragma unroll
     for (int g = 0; g < 5; ++g) {
         const float4 a = reinterpret_cast<const float4*>(links)[gidx(d * 5 + g, i, 40)];
         L[2 * g] = make_float2(a.x, a.y);
         L[2 * g + 1] = make_float2(a.z, a.w);
     }
+}
+
+// t = L v on every spin
+__device__ __forceinline__ void transport(const float2 (&L)[10], const float2 (&v)[12], float2 (&t)[12]) {
 #pragma unroll
     for (int sp = 0; sp < 4; ++sp)
 #pragma unroll
@@ -112,7 +113,9 @@ __global__ __launch_bounds__(PT) void ptc_layer_kernel(PtcLayerParams P) {
             const long y = P.nbr[gidx(d, i, 8)];
             float2 v[12], t[12];
             load12(P.in_hop, s, y, Ls, v);
-            transport(P.links, d, i, v, t);
+            float2 L[10];
+            load_link(P.links, d, i, L);
+            transport(L, v, t);
             spin_apply(P.W + (1 + d) * 16, t, acc);
         }
     }
@@ -123,20 +126,23 @@ __global__ __launch_bounds__(PT) void ptc_layer_kernel(PtcLayerParams P) {
 // the two layers as one (E_{qq'} above)
 // ---------------------------------------------------------------------
 typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 
 // Link part of E as the MFMA A operand of ptc_mid_kernel, then the local part:
 //   el[((d' * 4 + j) * 2 + tile) * 64 + lane], lane = 32 h + 4 d + i:
 //     the factor of (re, im)[h] of t_{d', j} in (re, im)[tile] of g_{d, i}
-//   al[k * 16 + i * 4 + j]: k = 0..4 the factor of r(s + k - 2); k = 5, 6 the
-//     terms through s + 1 and s - 1 and back, present where that slice is;
-//     al[112 + ..] what rounding these to FP32 left (they hold the identity that
+//   al[k * 16 + i * 4 + j]: k = 0..3 the factor of r(s - 2), r(s - 1), r(s + 1),
+//     r(s + 2); k = 4 + c that of r(s), with the term through s + 1 and back if
+//     c & 1 and the one through s - 1 if c & 2 (present where that slice is);
+//     al[AL + ..] what rounding these to FP32 left (they hold the identity that
 //     a trained network stays near: their rounding would be the same at every
 //     site, and the gradients' error against 64 bits 15 % larger with it).
+constexpr int AL = 8 * 16;
 __global__ __launch_bounds__(PT) void ptc_pair_weights(const float2* __restrict__ W1, const float2* __restrict__ W2,
                                                        int H, float* __restrict__ el, float2* __restrict__ al) {
     const int t = blockIdx.x * PT + threadIdx.x;
-    if (t >= 1024 + 7 * 16) return;
-    int q[2] = {0, 0}, p[2] = {0, 0}, n = 1, i, j;
+    if (t >= 1024 + AL) return;
+    int q[3] = {0, 0, 0}, p[3] = {0, 0, 0}, n = 1, i, j;
     if (t < 1024) {   // t = d' * 128 + j * 32 + d * 4 + i
         i = t & 3;
         q[0] = 1 + ((t >> 2) & 7);
@@ -148,10 +154,10 @@ __global__ __launch_bounds__(PT) void ptc_pair_weights(const float2* __restrict_
         j = t & 3;
         if (k == 0) { q[0] = 10; p[0] = 10; }
         if (k == 1) { q[0] = 0; p[0] = 10; q[1] = 10; p[1] = 0; n = 2; }
-        if (k == 3) { q[0] = 0; p[0] = 9; q[1] = 9; p[1] = 0; n = 2; }
-        if (k == 4) { q[0] = 9; p[0] = 9; }
-        if (k == 5) { q[0] = 9; p[0] = 10; }
-        if (k == 6) { q[0] = 10; p[0] = 9; }
+        if (k == 2) { q[0] = 0; p[0] = 9; q[1] = 9; p[1] = 0; n = 2; }
+        if (k == 3) { q[0] = 9; p[0] = 9; }
+        if (k == 5 || k == 7) { q[1] = 9; p[1] = 10; n = 2; }
+        if (k == 6 || k == 7) { q[n] = 10; p[n] = 9; ++n; }
     }
     double re = 0.0, im = 0.0;
     for (int m = 0; m < n; ++m)
@@ -171,7 +177,7 @@ __global__ __launch_bounds__(PT) void ptc_pair_weights(const float2* __restrict_
     } else {
         const float2 hi = make_float2((float)re, (float)im);
         al[t - 1024] = hi;
-        al[t - 1024 + 112] = make_float2((float)(re - hi.x), (float)(im - hi.y));
+        al[t - 1024 + AL] = make_float2((float)(re - hi.x), (float)(im - hi.y));
     }
 }
 
@@ -181,18 +187,24 @@ __global__ __launch_bounds__(PT) void ptc_pair_weights(const float2* __restrict_
 // of its lanes hold the real and the imaginary part of the same t, which is
 // the B operand (column = site, k = re/im).  A lane ends up with four of the
 // eight g_d of its site.  Links, neighbours and E are in LDS for the block's
-// 32 sites and all slices.  Bound by the matrix cores: 12288 multiply-adds per
-// site and slice against 3 KB read or written; 403 us on
-// 16^3x32, Ls = 16 (96 TFLOP/s of the 152 a large FP32 product reaches).  The
-// whole network there: 0.67 ms for any number of channels; two layers of 8
-// channels, one thread per site and slice, took 2.5 to 2.8 ms.
+// 32 sites and all slices.  Bound by the matrix cores (12288 multiply-adds per
+// site and slice), 56 % busy, and by a last round of blocks that fills two thirds
+// of the chip: 358 us on 16^3x32, Ls = 16 (72 TFLOP/s; a large FP32 product reaches
+// 152); 412 us with the next slice's first loads behind this slice's stores.
+// NT: non-temporal stores, for a g that the last-level cache (256 MB) does not
+// hold anyway; ptc_out then finds more of what it reads besides (16^3x32, 805 MB:
+// 226 us with, 264 without, and 371 against 357 here; 16^4, Ls = 8, 201 MB: 62
+// against 53, and 84 against 87 here).  The whole network on 16^3x32: 0.59 ms for any
+// number of channels; two layers of 8 channels, one thread per site and slice, took
+// 2.5 to 2.8 ms.
+template <bool NT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void ptc_mid_kernel(
     const float2* __restrict__ r, float2* __restrict__ g, const float2* __restrict__ links,
     const int* __restrict__ nbr, const float* __restrict__ el, long Vh, long Vhp, int Ls) {
     __shared__ u32x4 lnk[8 * 5 * 32];
     __shared__ u32x4 ew4[1024];
     __shared__ int lnb[8 * 32];
-    const long tile = blockIdx.x;
+    const long tile = xcd_block(blockIdx.x, gridDim.x);
     const int nthr = blockDim.x;
     for (int e = threadIdx.x; e < 8 * 5 * 32; e += nthr) {
         const long site = tile * 32 + (e & 31);
@@ -209,15 +221,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
     const long site = tile * 32 + j;
     const long n = (long)Ls * 12 * Vhp;
     const float4* r4 = reinterpret_cast<const float4*>(r);
+    float4 nx[6];
+#pragma unroll
+    for (int q = 0; q < 6; ++q) nx[q] = r4[lnb[j] + ((int)(threadIdx.x >> 6) * 6 + q) * 16];
     for (int s = threadIdx.x >> 6; s < Ls; s += nthr >> 6) {
         v16f acc[3][2];
 #pragma unroll
         for (int c = 0; c < 3; ++c)
 #pragma unroll
             for (int k = 0; k < 16; ++k) { acc[c][0][k] = 0.f; acc[c][1][k] = 0.f; }
-        float4 nx[6];
-#pragma unroll
-        for (int q = 0; q < 6; ++q) nx[q] = r4[lnb[j] + (s * 6 + q) * 16];
 #pragma unroll 1
         for (int d = 0; d < 8; ++d) {
             // real lanes use (re, -im) of the spinor, imaginary lanes (im, re)
@@ -229,9 +241,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
                 a[2 * q + 1] = h ? nx[q].w : nx[q].z;
                 b[2 * q + 1] = h ? nx[q].z : -nx[q].w;
             }
-            const int y = lnb[(d < 7 ? d + 1 : 7) * 32 + j];   // the next direction's spinor, in flight meanwhile
+            // the next direction's spinor, in flight meanwhile; after the last one the next
+            // slice's first, requested before this slice's stores (a load is waited for
+            // with every store that was issued before it)
+            const int y = lnb[((d + 1) & 7) * 32 + j], sn = d < 7 ? s : min(s + (nthr >> 6), Ls - 1);
 #pragma unroll
-            for (int q = 0; q < 6; ++q) nx[q] = r4[y + (s * 6 + q) * 16];
+            for (int q = 0; q < 6; ++q) nx[q] = r4[y + (sn * 6 + q) * 16];
+            __builtin_amdgcn_sched_barrier(0);
             float U[20];
 #pragma unroll
             for (int k = 0; k < 5; ++k) {
@@ -266,9 +282,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
 #pragma unroll
                 for (int q = 0; q < 6; ++q) {
                     const int c0 = (2 * q) % 3, s0 = (2 * q) / 3, c1 = (2 * q + 1) % 3, s1 = (2 * q + 1) / 3;
-                    reinterpret_cast<float4*>(gd)[gidx(s * 6 + q, site, Ls * 6)] =
-                        make_float4(acc[c0][0][4 * k + s0], acc[c0][1][4 * k + s0], acc[c1][0][4 * k + s1],
-                                    acc[c1][1][4 * k + s1]);
+                    const v4f o = {acc[c0][0][4 * k + s0], acc[c0][1][4 * k + s0], acc[c1][0][4 * k + s1],
+                                   acc[c1][1][4 * k + s1]};
+                    v4f* to = reinterpret_cast<v4f*>(gd) + gidx(s * 6 + q, site, Ls * 6);
+                    if constexpr (NT) __builtin_nontemporal_store(o, to);
+                    else *to = o;
                 }
             }
         }
@@ -276,15 +294,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
 }
 
 // out(x, s) = local pairs of r + sum_d L_d(x) g_d(nbr_d(x), s) at the even
-// sites; one thread per (site, slice), one slice per wave.  Bound by memory:
-// every g_d is read once (8 fields; 271 us on 16^3x32, Ls = 16, 3.7 TB/s), r and
-// the links from cache.
+// sites; one thread per (site, slice), one slice per wave.  Bound by memory (every
+// g_d is read once, 8 fields; r and the links come from cache) and by half as much
+// arithmetic.  The slices of 64 sites follow each other on one XCD: 226 us on
+// 16^3x32, Ls = 16 (4.4 TB/s); 288 us with the sites of four slices in sequence
+// over all XCDs and with the two terms through s + 1 and s - 1 and back as matrices
+// of their own.  Two slices per thread, with the links read once, were no faster.
 __global__ __launch_bounds__(256) void ptc_out_kernel(const float2* __restrict__ r, const float2* __restrict__ g,
                                                       float2* __restrict__ out, const float2* __restrict__ links,
                                                       const int* __restrict__ nbr, const float2* __restrict__ al,
-                                                      long Vh, long Vhp, int Ls) {
-    const long i = (long)blockIdx.x * 64 + (threadIdx.x & 63);
-    const int s = __builtin_amdgcn_readfirstlane((int)blockIdx.y * 4 + (int)(threadIdx.x >> 6));
+                                                      long Vh, long Vhp, int Ls, int groups) {
+    const int b = xcd_block(blockIdx.x, gridDim.x);
+    const long i = (long)(b / groups) * 64 + (threadIdx.x & 63);
+    const int s = __builtin_amdgcn_readfirstlane(b % groups * 4 + (int)(threadIdx.x >> 6));
     if (s >= Ls || i >= Vh) return;
     const long n = (long)Ls * 12 * Vhp;
     float2 acc[12];
@@ -293,26 +315,24 @@ __global__ __launch_bounds__(256) void ptc_out_kernel(const float2* __restrict__
 #pragma unroll 2
     for (int d = 0; d < 8; ++d) {
         const long y = nbr[gidx(d, i, 8)];
-        float2 m[12], t[12];
+        float2 L[10], m[12], t[12];
+        load_link(links, d, i, L);
         load12(g + d * n, s, y, Ls, m);
-        transport(links, d, i, m, t);
+        transport(L, m, t);
 #pragma unroll
         for (int k = 0; k < 12; ++k) {
             acc[k].x += t[k].x;
             acc[k].y += t[k].y;
         }
     }
-    for (int k = 0; k < 5; ++k) {
-        const int ss = s + k - 2;
-        if (ss < 0 || ss >= Ls) continue;
+#pragma unroll 1
+    for (int k = -2; k <= 2; ++k) {
+        if (s + k < 0 || s + k >= Ls) continue;
         float2 v[12];
-        load12(r, ss, i, Ls, v);
-#pragma unroll
-        for (int lo = 112; lo >= 0; lo -= 112) {
-            spin_apply(al + lo + k * 16, v, acc);
-            if (k == 2 && s + 1 < Ls) spin_apply(al + lo + 5 * 16, v, acc);
-            if (k == 2 && s > 0) spin_apply(al + lo + 6 * 16, v, acc);
-        }
+        load12(r, s + k, i, Ls, v);
+        const float2* a = al + 16 * (k < 0 ? k + 2 : (k > 0 ? k + 1 : 4 + (s + 1 < Ls ? 1 : 0) + (s > 0 ? 2 : 0)));
+        spin_apply(a + AL, v, acc);
+        spin_apply(a, v, acc);
     }
     store12(out, s, i, Ls, acc);
 }
@@ -362,8 +382,10 @@ __global__ __launch_bounds__(256) void ptc_corr_kernel(const float2* __restrict_
                 float2 v[12], v2[12];
                 load12(r, s, y, Ls, v);
                 load12(g, s, y, Ls, v2);
-                transport(links, slot, site, v, t);
-                transport(links, slot, site, v2, u);
+                float2 L[10];
+                load_link(links, slot, site, L);
+                transport(L, v, t);
+                transport(L, v2, u);
             }
         }
         __syncthreads();   // the previous tile's reads
@@ -592,12 +614,18 @@ void ptc_layer(const PtcLayerParams& P, hipStream_t st) {
 
 void ptc_pairs_forward(const PtcPairParams& P, const float2* r, float2* out, hipStream_t st) {
     DWF_REQUIRE(P.Ls >= 1 && P.Vh >= 1 && P.H >= 1, DWF_EINVAL, "bad PTC shape");
-    hipLaunchKernelGGL(ptc_pair_weights, dim3((1024 + 7 * 16 + PT - 1) / PT), dim3(PT), 0, st, P.W1, P.W2, P.H, P.el,
+    hipLaunchKernelGGL(ptc_pair_weights, dim3((1024 + AL + PT - 1) / PT), dim3(PT), 0, st, P.W1, P.W2, P.H, P.el,
                        P.al);
-    hipLaunchKernelGGL(ptc_mid_kernel, dim3((unsigned)((P.Vh + 31) / 32)), dim3(64 * (P.Ls < 4 ? P.Ls : 4)), 0, st, r,
-                       P.mid, P.links[1], P.nbr[1], P.el, P.Vh, P.Vhp, P.Ls);
-    hipLaunchKernelGGL(ptc_out_kernel, dim3((unsigned)((P.Vh + 63) / 64), (unsigned)((P.Ls + 3) / 4)), dim3(256), 0, st,
-                       r, P.mid, out, P.links[0], P.nbr[0], P.al, P.Vh, P.Vhp, P.Ls);
+    const dim3 mid_grid((unsigned)((P.Vh + 31) / 32)), mid_block(64 * (P.Ls < 4 ? P.Ls : 4));
+    if ((double)P.Ls * 12 * P.Vhp * 8 * sizeof(float2) > 256e6)
+        hipLaunchKernelGGL(ptc_mid_kernel<true>, mid_grid, mid_block, 0, st, r, P.mid, P.links[1], P.nbr[1], P.el, P.Vh,
+                           P.Vhp, P.Ls);
+    else
+        hipLaunchKernelGGL(ptc_mid_kernel<false>, mid_grid, mid_block, 0, st, r, P.mid, P.links[1], P.nbr[1], P.el, P.Vh,
+                           P.Vhp, P.Ls);
+    const int groups = (P.Ls + 3) / 4;
+    hipLaunchKernelGGL(ptc_out_kernel, dim3((unsigned)((P.Vh + 63) / 64 * groups)), dim3(256), 0, st, r, P.mid, out,
+                       P.links[0], P.nbr[0], P.al, P.Vh, P.Vhp, P.Ls, groups);
     DWF_HIP(hipGetLastError());
 }
 

@@ -290,3 +290,30 @@ def test_cg_scalars_by_lattice_size(dims, Ls, prec):
         st, info = op.solve(x, _dev(b), prm)
         assert st == 0 and info.converged
         assert oracle.true_residual(p, U, x.cpu().numpy(), b) <= 1.2e-10
+
+
+# intermediate fields of 201 and 245 MB (plain stores) and 264 MB (non-temporal ones); Ls = 2, 3: every combination
+# of missing neighbour slices
+@pytest.mark.parametrize("dims,Ls", [((16, 16, 16, 16), 8), ((16, 16, 16, 12), 13), ((16, 16, 16, 12), 14),
+                                     ((4, 4, 4, 4), 2), ((4, 4, 4, 4), 3)])
+def test_network_sizes_against_layers(dims, Ls):
+    """Two channels, of which the second is zero (pair sums), against the one channel (layer by layer): the same
+    sums in FP32, whose rounding is below 1e-6 of a field in either."""
+    import torch
+
+    import paper_2602_14454_amd as dwf
+    from oracle import ptc as optc
+    lat = dwf.Lattice(dims)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    u = torch.randn((lat.V, 4, 3, 3), dtype=torch.complex128, device="cuda", generator=g)
+    lat.set_gauge(torch.linalg.qr(u)[0].contiguous())
+    op = dwf.Op(lat, Ls, 1.6, 0.05, 1.0, 0.0, 1.0)
+    W1, W2 = optc.random_weights(1, 5)
+    one, two = dwf.PtcModel(1), dwf.PtcModel(2)
+    one.set_weights(W1, W2)
+    two.set_weights(np.concatenate([W1, 0 * W1], axis=1), np.concatenate([W2, 0 * W2], axis=2))
+    r = torch.randn((Ls, lat.Vh, 4, 3), dtype=torch.complex128, device="cuda", generator=g)
+    a, b = torch.empty_like(r), torch.empty_like(r)
+    one.apply(op, a, r)
+    two.apply(op, b, r)
+    assert float((a - b).abs().max() / a.abs().max()) < 2e-6

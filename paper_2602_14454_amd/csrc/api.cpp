@@ -392,7 +392,7 @@ int dwf_bench_hop(const dwf_op* op, int prec, int nrep, double* ms_per_launch, d
             for (int i = 0; i < nsets; ++i) {
                 ins[i].alloc(fb);
                 outs[i].alloc(fb);
-                random_fill_f64(tmp.p, (long)op->Ls * 12, Vh, 0x5eedULL + (unsigned long long)i, st);
+                random_fill_f64(tmp.p, (long)op->Ls * 12, Vh, nullptr, 0x5eedULL + (unsigned long long)i, st);
                 convert(k, ST_F64, ins[i].p, tmp.p, n, st);
             }
             DWF_HIP(hipStreamSynchronize(st));
@@ -545,7 +545,7 @@ int dwf_ptc_bench_apply(dwf_ptc* m, const dwf_op* op, int nrep, double* ms_per_a
         hipStream_t st = S(stream);
         const long n = ptc_field_elems(op);
         DevBuf a(8 * (size_t)n), b(8 * (size_t)n), t(16 * (size_t)n);
-        random_fill_f64(t.p, (long)op->Ls * 12, L->Vh, 0x7ee5ULL, st);
+        random_fill_f64(t.p, (long)op->Ls * 12, L->Vh, nullptr, 0x7ee5ULL, st);
         convert(ST_F32, ST_F64, a.p, t.p, n, st);
         m->forward(op, a.as<float2>(), b.as<float2>(), st);   // warm-up (workspace)
         hipEvent_t e0, e1;

@@ -64,7 +64,8 @@ void cg_update_px(int kx, int kp, void* x, void* p, const void* r, long n, const
 // y += (ar + i ai) x
 void caxpy(int kind, void* y, const void* x, long n, double ar, double ai, hipStream_t st);
 // FP64 half field(s) of `rows` rows: uniform [-1,1) real and imaginary parts on valid sites
-void random_fill_f64(void* v, long rows, long Vh, unsigned long long seed, hipStream_t st);
+// (site i takes the numbers of site place[i], or its own if place is nullptr)
+void random_fill_f64(void* v, long rows, long Vh, const int* place, unsigned long long seed, hipStream_t st);
 // mode 0: out[0] = sum; 1: alpha step; 2: beta step; 3: beta after a residual
 // replacement (RR = sum, BETA = sum / RROLD) (see CG slots)
 void finalize(const double* partial, int nparts, int stride, double* out, int mode, hipStream_t st,

@@ -537,13 +537,14 @@ __global__ void caxpy_kernel(void* y, const void* x, long n, double ar, double a
 
 // Deterministic pseudo-random fill in [-1, 1) (SplitMix64 of seed and index)
 // on the valid sites of each row; padding stays zero.
-__global__ void random_fill_kernel(double2* v, long rows, long Vh, unsigned long long seed) {
+__global__ void random_fill_kernel(double2* v, long rows, long Vh, const int* place,
+                                   unsigned long long seed) {
     const long n = rows * Vh;
     for (long k = (long)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (long)gridDim.x * blockDim.x) {
-        const long row = k / Vh, site = k % Vh;
+        const long row = k / Vh, site = k % Vh, at = row * Vh + (place ? place[site] : site);
         double out[2];
         for (int h = 0; h < 2; ++h) {
-            unsigned long long z = seed + 0x9E3779B97F4A7C15ull * (unsigned long long)(2 * k + h + 1);
+            unsigned long long z = seed + 0x9E3779B97F4A7C15ull * (unsigned long long)(2 * at + h + 1);
             z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
             z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
             z ^= z >> 31;
@@ -1047,9 +1048,9 @@ void caxpy(int kind, void* y, const void* x, long n, double ar, double ai, hipSt
     DWF_HIP(hipGetLastError());
 }
 
-void random_fill_f64(void* v, long rows, long Vh, unsigned long long seed, hipStream_t st) {
+void random_fill_f64(void* v, long rows, long Vh, const int* place, unsigned long long seed, hipStream_t st) {
     hipLaunchKernelGGL(random_fill_kernel, dim3(blas_grid(rows * Vh)), dim3(BLAS_THREADS), 0, st, (double2*)v, rows,
-                       Vh, seed);
+                       Vh, place, seed);
     DWF_HIP(hipGetLastError());
 }
 

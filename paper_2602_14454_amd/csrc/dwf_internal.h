@@ -161,6 +161,7 @@ struct dwf_lattice {
     long V, Vh, Vhp;   // sites, sites per parity, those rounded up to whole tiles
     int brick[3] = {0, 0, 0};       // spatial brick extents of the internal site order
     int site_order = 0;             // 0 bricks swept in t, 1 t columns (build_geometry)
+    dwf::DevBuf random_site;        // even sites: place in the random fields (empty: the site itself)
     std::vector<int> lex_of_site;   // host [2][Vh]: lexicographic index of internal site
     std::vector<int> nbr_host;    // host copy of nbr
     dwf::DevBuf nbr;              // device [2][8][Vh]

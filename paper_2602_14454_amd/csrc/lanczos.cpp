@@ -124,7 +124,7 @@ static double trlan(Ctx& C, int m, int keep, int max_restarts, double tol, bool 
     std::vector<double> H((size_t)(m + 1) * (m + 1), 0.0);
     auto Hs = [&](int i, int j) -> double& { return H[(size_t)i * (m + 1) + j]; };
     // random start vector, normalised
-    random_fill_f64(C.V[0].p, (long)C.op->Ls * 12, L->Vh, seed, C.st);
+    random_fill_f64(C.V[0].p, (long)C.op->Ls * 12, L->Vh, L->random_site.as<int>(), seed, C.st);
     {
         const double nv = C.norm(C.V[0].p);
         axpby(ST_F64, ST_F64, C.V[0].p, C.V[0].p, n, nullptr, 1.0 / nv, nullptr, 0.0, nullptr, C.st);

@@ -91,13 +91,7 @@ bool release_scratch() {
 // spatial volume this is the lexicographic order.  Smaller bricks keep the
 // t neighbours of the sites a GPU die has in flight inside its L2 (a t slice
 // of 24^3 sites is ~10 MB of FP32 input at Ls = 16, beyond an XCD's 4 MB L2)
-// at the cost of re-reading brick faces.  Measured on MI355X (fused hop,
-// Ls = 16): on 16^3x32 bricks of 1024 sites per slice beat whole slices
-// (FP64 193 -> 185 us, FP32 84 -> 78 us); on 24^3x48 bricks of 4096 sites
-// are best (FP32 479 us vs 519 us at 2048 and 546 us at 1024; larger bricks
-// are slower: 440 us vs 459 us at 8192 and 501 us for whole slices).
-// Brick limit: 1024 sites up to 16^3 spatial sites, 4096 above
-// ($DWF_BRICK_SITES overrides).
+// at the cost of re-reading brick faces (halve_brick, choose_brick).
 //
 // "tcol": t columns.  The sites of one parity at one spatial position (every
 // other t) are consecutive, so a block of 16 sites is (most of) one t
@@ -110,11 +104,14 @@ bool release_scratch() {
 // ($DWF_TCOL_TILE="tx,ty,tz", default 4,4,4) are shrunk to divide the
 // octant; $DWF_TCOL_CURVE=morton visits an octant's positions along the
 // Morton (bit-interleaved) curve instead of by tiles.
-static void choose_brick(const int dims[4], int b[3]) {
+
+// Extents halved, the largest first, down to at most fmax sites (both parities)
+// per brick slice.
+static void halve_brick(const int dims[4], int b[3]) {
     b[0] = dims[0];
     b[1] = dims[1];
     b[2] = dims[2];
-    long fmax = (long)dims[0] * dims[1] * dims[2] <= 4096 ? 1024L : 4096L;   // sites (both parities) per brick slice
+    long fmax = (long)dims[0] * dims[1] * dims[2] <= 4096 ? 1024L : 4096L;
     if (const char* e = std::getenv("DWF_BRICK_SITES")) {
         const long v = std::atol(e);
         if (v >= 8) fmax = v;
@@ -125,6 +122,43 @@ static void choose_brick(const int dims[4], int b[3]) {
             if (b[mu] % 4 == 0 && (best < 0 || b[mu] > b[best])) best = mu;
         if (best < 0) break;
         b[best] /= 2;
+    }
+}
+
+// Above 16^3 spatial sites: x is not cut (its faces are single sites of every
+// cache line of a brick), and the brick is the largest of at most 1024 sites per
+// slice, then the one with the least surface, then the flattest in z, whose z
+// planes are whole tiles of 16 sites per parity, so that a tile's z and t
+// neighbours are whole tiles too; without such a plane the largest of at most
+// 4096.  Hop in us, FP64 / FP32 / BF16, Ls = 16, halved bricks -> these:
+//   24^3x48      24x12x12 801 / 346 / 233 -> 24x12x3 769 / 335 / 230
+//                (24x6x6, no whole tiles: 383 in FP32; 24x8x6 790 / 334 / 229)
+//   32^4         16x16x16 1439 / 613 / 366 -> 32x8x4 1218 / 502 / 348
+//                (32x16x4 1364 / 572 / 374, 32x16x16 1337 / 518 / 356)
+//   48x24^3      24x12x12 886 / 369 / 234 -> 48x6x3 779 / 328 / 231
+//   12x24^3      12x24x12 208 / 92 / 62 -> 12x24x3 196 / 83 / 62
+//   16x32^3      16x16x16 617 / 265 / 184 -> 16x8x8 589 / 265 / 178
+//   20^3x40      20x20x10 394 / 172 / 114 (20x10x5 406 / 173 / 117)
+// Up to 16^3 the halved bricks of 1024 sites are such bricks already
+// (16^3x32: 16x8x8 158 / 65 / 48; 16x16x16 167 / 73 / 48).
+static void choose_brick(const int dims[4], int b[3]) {
+    halve_brick(dims, b);
+    if ((long)dims[0] * dims[1] * dims[2] <= 4096 || std::getenv("DWF_BRICK_SITES")) return;
+    for (const bool whole : {true, false}) {
+        const long fmax = whole ? 1024 : 4096;
+        long best = 0;
+        for (int y = 1; y <= dims[1]; ++y)
+            for (int z = 1; z <= dims[2]; ++z) {
+                const long f = (long)dims[0] * y * z;
+                if (dims[1] % y || dims[2] % z || f > fmax || (whole && (long)dims[0] * y % 32)) continue;
+                // sites, then surface (1 / y + 1 / z at equal y z), then y
+                if (f < best || (f == best && (y + z > b[1] + b[2] || (y + z == b[1] + b[2] && y < b[1])))) continue;
+                best = f;
+                b[0] = dims[0];
+                b[1] = y;
+                b[2] = z;
+            }
+        if (best) return;
     }
 }
 
@@ -192,6 +226,16 @@ static std::vector<int> tcol_spatial_order(const int dims[4]) {
     return order;
 }
 
+template <class F> static void sweep_bricks(const int dims[4], const int b[3], F place) {
+    for (int zb = 0; zb < dims[2] / b[2]; ++zb)
+        for (int yb = 0; yb < dims[1] / b[1]; ++yb)
+            for (int xb = 0; xb < dims[0] / b[0]; ++xb)
+                for (int t = 0; t < dims[3]; ++t)
+                    for (int z = zb * b[2]; z < (zb + 1) * b[2]; ++z)
+                        for (int y = yb * b[1]; y < (yb + 1) * b[1]; ++y)
+                            for (int x = xb * b[0]; x < (xb + 1) * b[0]; ++x) place(x, y, z, t);
+}
+
 void build_geometry(dwf_lattice* L) {
     const int Lx = L->dims[0], Ly = L->dims[1], Lz = L->dims[2], Lt = L->dims[3];
     const long V = L->V, Vh = L->Vh;
@@ -199,7 +243,6 @@ void build_geometry(dwf_lattice* L) {
     L->site_order = site_order_kind();
     L->Vhp = (Vh + 15) / 16 * 16;   // whole tiles of 16 sites
     const long Vhp = L->Vhp;
-    const int bx = L->brick[0], by = L->brick[1], bz = L->brick[2];
     L->lex_of_site.assign(2 * Vh, -1);
     std::vector<int> site_of_lex(V, -1);
     long next[2] = {0, 0};
@@ -216,13 +259,7 @@ void build_geometry(dwf_lattice* L) {
             for (int t = 0; t < Lt; ++t) place(x, y, z, t);
         }
     } else {
-        for (int zb = 0; zb < Lz / bz; ++zb)
-            for (int yb = 0; yb < Ly / by; ++yb)
-                for (int xb = 0; xb < Lx / bx; ++xb)
-                    for (int t = 0; t < Lt; ++t)
-                        for (int z = zb * bz; z < (zb + 1) * bz; ++z)
-                            for (int y = yb * by; y < (yb + 1) * by; ++y)
-                                for (int x = xb * bx; x < (xb + 1) * bx; ++x) place(x, y, z, t);
+        sweep_bricks(L->dims, L->brick, place);
     }
     DWF_REQUIRE(next[0] == Vh && next[1] == Vh, DWF_EDIMS, "internal site order is not a bijection");
     L->nbr_host.assign(2 * 8 * Vhp, 0);
@@ -241,6 +278,18 @@ void build_geometry(dwf_lattice* L) {
                 L->nbr_host[p * 8 * Vhp + ((i >> 4) * 8 + d) * 16 + (i & 15)] = site_of_lex[y];
             }
         }
+    int halved[3];
+    halve_brick(L->dims, halved);
+    if (L->site_order == 0 && !std::equal(halved, halved + 3, L->brick)) {
+        // random fields are defined in the order of the halved bricks
+        std::vector<int> at(Vh);
+        int k = 0;
+        sweep_bricks(L->dims, halved, [&](int x, int y, int z, int t) {
+            if (((x + y + z + t) & 1) == 0) at[site_of_lex[x + (long)Lx * (y + (long)Ly * (z + (long)Lz * t))]] = k++;
+        });
+        L->random_site.alloc(sizeof(int) * Vh);
+        DWF_HIP(hipMemcpy(L->random_site.p, at.data(), L->random_site.bytes, hipMemcpyHostToDevice));
+    }
     L->nbr.alloc(sizeof(int) * 2 * 8 * Vhp);
     DWF_HIP(hipMemcpy(L->nbr.p, L->nbr_host.data(), L->nbr.bytes, hipMemcpyHostToDevice));
     L->lex_of_site_dev.alloc(sizeof(int) * 2 * Vh);

@@ -215,7 +215,7 @@ dwf_ptc_pairs* ptc_pairs_create(const dwf_op* op, const void* b5, unsigned long 
         convert(ST_F64, ST_F64, xs.p, W.x.p, n, st);
     } else {
         // a system with known solution: x* = seeded random field, b~ = D^ x*
-        random_fill_f64(xs.p, (long)op->Ls * 12, L->Vh, seed, st);
+        random_fill_f64(xs.p, (long)op->Ls * 12, L->Vh, L->random_site.as<int>(), seed, st);
         apply_dhat(op, ST_F64, 0, bt.p, xs.p, to.p, nullptr, 1, st);
     }
     std::unique_ptr<dwf_ptc_pairs> P(new dwf_ptc_pairs);

@@ -317,3 +317,25 @@ def test_network_sizes_against_layers(dims, Ls):
     one.apply(op, a, r)
     two.apply(op, b, r)
     assert float((a - b).abs().max() / a.abs().max()) < 2e-6
+
+
+# bricks of whole tiles (24x12x3, 32x8x4), of odd extents (28x14x7) and without a plane of whole tiles (20x20x6)
+@pytest.mark.parametrize("dims", [(24, 24, 12, 2), (32, 16, 16, 2), (28, 14, 14, 2), (20, 20, 12, 2)])
+def test_brick_orders(dims, monkeypatch):
+    """The tables of every brick, and random fields that do not depend on it (a training run on a random system)."""
+    import paper_2602_14454_amd as dwf
+    step = np.cumprod((1,) + dims[:3])
+    lex, nbr = dwf.Lattice(dims).maps()
+    assert np.array_equal(np.sort(lex, axis=None), np.arange(2 * lex.shape[1]))
+    for d in range(8):
+        mu, n = d % 4, dims[d % 4]
+        c = lex // step[mu] % n
+        assert np.array_equal(nbr[:, d], lex + ((c + (1 if d < 4 else -1)) % n - c) * step[mu])
+    hist = []
+    for limit in (None, "4096"):
+        if limit:
+            monkeypatch.setenv("DWF_BRICK_SITES", limit)
+        lat, op = _make(dims, 2)[:2]
+        M = dwf.PtcModel(2)
+        hist.append(np.asarray(M.train([dwf.PtcPairs(op, None, [1, 3], seed=5)], 3, seed=3), dtype=float).ravel()[:3])
+    assert np.allclose(hist[0], hist[1], rtol=1e-6, atol=0)   # FP32 sums in another order

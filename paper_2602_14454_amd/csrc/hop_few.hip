@@ -8,13 +8,13 @@ namespace dwf {
 // term, old residual, one after the other in the form that several waves per
 // SIMD want (3 waves, rolled direction loop).  Here everything that does not
 // depend on another load is requested before the direction loop, and the
-// spinors of four directions (two with the general pre-mix) are in flight, in
-// 256 VGPRs and about 100 AGPRs.  FP64 only: FP32 and BF16 pipeline the
+// spinors of four directions (two with the general pre-mix, or when four waves
+// share them) are in flight, in 256 VGPRs and about 100 AGPRs.  FP64 only: FP32 and BF16 pipeline the
 // directions already and gained nothing from a deeper one.
-template <int KK, int PM, int EK>
+template <int KK, int PM, int EK, int DS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void hop_few_kernel(HopParams P) {
     extern __shared__ u32x4 hop_smem[];
-    hop_tile<double, KK, PM, EK, true>(P, blockIdx.x, blockIdx.y,
+    hop_tile<double, KK, PM, EK, true, DS>(P, blockIdx.x, blockIdx.y,
                                        P.partial ? P.partial + (long)blockIdx.y * gridDim.x + blockIdx.x : nullptr,
                                        reinterpret_cast<unsigned char*>(hop_smem));
 }
@@ -28,16 +28,37 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #define DWF_HOP_FEW_WAVES 768
 #endif
 
+// Blocks up to which the one or two waves of a block (Ls <= 8) become four, one
+// per SIMD of its CU, by sharing out the eight directions (DS): one block per CU,
+// since two blocks of such waves do not fit one.  Three or four waves (Ls > 8)
+// have no free SIMD.  Normal operator with layout conversion, before / after: 4^4,
+// Ls = 8 (8 blocks) 55.2 / 50.1 us, 8^4, Ls = 8 (128) 61.7 / 58.6, 8^3x16, Ls = 8
+// (256) 67.0 / 64.5; Ls = 4: 2^4 53.5 / 38.6, 8^4 60.8 / 47.4, 8^3x16 64.7 / 51.3.
+#ifndef DWF_HOP_SPLIT_BLOCKS
+#define DWF_HOP_SPLIT_BLOCKS 256
+#endif
+
+template <int KK, int PM, int EK, int DS>
+static void launch_few_kk(const HopParams& P, int nrhs, hipStream_t st) {
+    const dim3 grid(hop_grid_blocks(P.Vh), nrhs), block(64 * hop_waves(KK, true) * DS);
+    const unsigned smem_b = HopSmem<double, KK, DS>::bytes(P.loc != nullptr);
+    hipLaunchKernelGGL((hop_few_kernel<KK, PM, EK, DS>), grid, block, smem_b, st, P);
+}
+
 template <int PM, int EK>
 static bool launch_few(const HopParams& P, int nrhs, hipStream_t st) {
-    const int KK = (P.Ls + 3) / 4;
-    dim3 grid(hop_grid_blocks(P.Vh), nrhs), block(64 * hop_waves(KK, true));
-    const unsigned smem_b = hop_smem_bytes<double>(KK, P.loc != nullptr);
-    switch (KK) {
-        case 1: hipLaunchKernelGGL((hop_few_kernel<1, PM, EK>), grid, block, smem_b, st, P); break;
-        case 2: hipLaunchKernelGGL((hop_few_kernel<2, PM, EK>), grid, block, smem_b, st, P); break;
-        case 3: hipLaunchKernelGGL((hop_few_kernel<3, PM, EK>), grid, block, smem_b, st, P); break;
-        case 4: hipLaunchKernelGGL((hop_few_kernel<4, PM, EK>), grid, block, smem_b, st, P); break;
+    const bool split = (long)hop_grid_blocks(P.Vh) * nrhs <= DWF_HOP_SPLIT_BLOCKS;
+    switch ((P.Ls + 3) / 4) {
+        case 1:
+            if (split) launch_few_kk<1, PM, EK, 4>(P, nrhs, st);
+            else launch_few_kk<1, PM, EK, 1>(P, nrhs, st);
+            break;
+        case 2:
+            if (split) launch_few_kk<2, PM, EK, 2>(P, nrhs, st);
+            else launch_few_kk<2, PM, EK, 1>(P, nrhs, st);
+            break;
+        case 3: launch_few_kk<3, PM, EK, 1>(P, nrhs, st); break;
+        case 4: launch_few_kk<4, PM, EK, 1>(P, nrhs, st); break;
         default: return false;
     }
     DWF_HIP(hipGetLastError());

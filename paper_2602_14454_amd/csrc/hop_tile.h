@@ -611,14 +611,14 @@ inline int epilogue_kind(const HopParams& P) {
 //   [r0, r0+32)   per-wave partial norms
 //   [r0+32, ...)  local-term tile, 16-byte groups [s][group][site]
 //                 (FP32/BF16 launches with a local term only)
-template <class S, int KK> struct HopSmem {
+template <class S, int KK, int DS = 1> struct HopSmem {
     using R = typename Traits<S>::R;
     static constexpr bool TIO = DWF_HOP_TILE_IO && sizeof(S) < 8;
     static constexpr bool LOC = TIO && (sizeof(S) == 2 ? DWF_HOP_LOC_LDS16 : DWF_HOP_LOC_LDS32);
     static constexpr int PK = fpack<S>();
     static constexpr int NGR = 12 / PK;
     static constexpr int HSK = 24 * 64 + (sizeof(R) == 4 ? 16 : 8);
-    static constexpr unsigned hs_b = KK * HSK * sizeof(R);
+    static constexpr unsigned hs_b = DS * KK * HSK * sizeof(R);
     static constexpr unsigned lnk_b = lnk_entries<S>() * 16 + 128 * 4;
     // SEP: hs after the staged tables instead of over them (no block
     // barrier between the last link read and the first hs write)
@@ -637,6 +637,14 @@ template <class S, int KK> struct HopSmem {
     static constexpr unsigned bytes(bool has_loc) { return loc_off + (has_loc ? loc_b : 0u); }
 };
 
+// an entry of hs, summed over the DS shares of the directions
+template <int DS, int STRIDE, class R> __device__ __forceinline__ R hop_sum(const R* hs) {
+    R v = hs[0];
+#pragma unroll
+    for (int x = 1; x < DS; ++x) v += hs[x * STRIDE];
+    return v;
+}
+
 // A block may hold several such tiles of one item, one per right-hand side
 // (the shared-link work-list kernel): group `sub` of NW waves computes
 // right-hand side `rhs` in its own shared-memory region smem + sub * region,
@@ -649,14 +657,16 @@ template <class S, int KK> struct HopSmem {
 // LAT: for launches of so few blocks that a wave has a SIMD to itself
 // (launch_hop_few): every load that does not depend on another is requested
 // before the direction loop or several directions ahead, in the registers
-// that the missing other waves leave free.
-template <class S, int KK, int PM = -1, int EK = -1, bool LAT = false>
+// that the missing other waves leave free.  DS: with DS waves per slice group, each
+// of which takes 8 / DS directions; phase 2 adds their sums as it reads hs (region
+// ds of hs at ds * KK * HSK).
+template <class S, int KK, int PM = -1, int EK = -1, bool LAT = false, int DS = 1>
 __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs, double* part_out,
                                          unsigned char* smem, int sub = 0, unsigned region = 0,
                                          bool active = true) {
     using R = typename Traits<S>::R;
     using V = typename Vec4<R>::T;
-    using L = HopSmem<S, KK>;
+    using L = HopSmem<S, KK, DS>;
     // which outputs, local terms and reductions the launch has: compile-time
     // constants for the epilogue kinds below, else read from P
     constexpr bool EKC = EK >= 0;
@@ -668,7 +678,8 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
     const bool f_upd = EKC ? ek_upd(EK) : P.upd != nullptr;
     const int f_reduce = EKC ? (EK == EK_CHAIN ? 1 : (ek_upd(EK) ? 3 : 0)) : P.reduce;
     const bool f_partial = EKC ? (EK == EK_CHAIN || ek_upd(EK)) : P.partial != nullptr;
-    constexpr int NW = hop_waves(KK, sizeof(S) == 8);
+    constexpr int KW = hop_waves(KK, sizeof(S) == 8);   // waves per share of the directions
+    constexpr int NW = KW * DS;
     constexpr int NTHR = 64 * NW;
     unsigned char* own = smem + (size_t)sub * region;
     R* hs = reinterpret_cast<R*>(own + L::hs_off);   // hs[kk][r][lane] at kk * HSK + r * 64 + lane
@@ -684,6 +695,7 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
 #else
     const int w = ((int)threadIdx.x >> 6) - sub * NW;
 #endif
+    const int kw = DS == 1 ? w : w % KW, ds = DS == 1 ? 0 : w / KW;
     const int j = lane & 15, sc = lane >> 4;
     const long Vh = P.Vh;
     const int Ls = P.Ls;
@@ -718,7 +730,7 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
     constexpr int NGR_ = 12 / fpack<S>();
     int sg[G];
 #pragma unroll
-    for (int g = 0; g < G; ++g) sg[g] = 4 * (w * G + g) + sc;
+    for (int g = 0; g < G; ++g) sg[g] = 4 * (kw * G + g) + sc;
     u32x4 ra[G][NGR_], rb[G][NGR_];
     unsigned ya = 0, yb = 0;
     // pre-mix coefficients of the wave's slices (read before the tile's
@@ -839,7 +851,8 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
     // that the reads are in flight across the block barriers instead of
     // after them.  Compiled only for those epilogue kinds (a no-local-term
     // launch would still issue the reads).
-    constexpr int CPW_ = 12 / hop_waves(KK, sizeof(S) == 8);
+    constexpr int CPW_ = 12 / NW;
+    static_assert(12 % NW == 0, "phase 2 shares the 12 components among the waves");
     constexpr bool LOCE = !L::LOC && EK > EK_PLAIN && (LAT || (DWF_HOP_LOC_EARLY32 && sizeof(S) == 4));
     R lre[LOCE ? CPW_ : 1][LOCE ? KK : 1], lie[LOCE ? CPW_ : 1][LOCE ? KK : 1];
     // the update stage's old values (its 16-byte groups of this thread),
@@ -925,26 +938,30 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
             hop_apply<S, G, PM>(P, R_, 7, sg, pd, pe, kr, h, lnk, rb, yb, j);
         } else if constexpr (PF == 3) {
             // the next ND directions' loads in flight
-            constexpr int ND = PM == 2 ? 2 : 4, ND2 = PM == 2 ? ND : 1;
+            constexpr int NDIR = 8 / DS, ND = PM == 2 || DS == 4 ? 2 : 4, ND2 = PM == 2 ? ND : 1;
             u32x4 rd[ND][G][NGR_], rm[ND2][G][NGR_], rp[ND2][G][NGR_];
             unsigned yd[ND];
 #pragma unroll
             for (int d = 0; d < ND; ++d) {
-                hop_fetch<S, G>(P, R_, d, sg, lnbr, j, rd[d], yd[d]);
+                hop_fetch<S, G>(P, R_, ds * NDIR + d, sg, lnbr, j, rd[d], yd[d]);
                 if constexpr (PM == 2) hop_fetch2<S, G>(P, R_, sg, yd[d], rm[d], rp[d]);
             }
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (EK == EK_UPDS) ua_sum = R(alpha_of_partials(sv, P.scal, P.alpha_copy, blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0));
 #pragma unroll
-            for (int d = 0; d < 8; ++d) {
-                hop_apply<S, G, PM, PM == 2>(P, R_, d, sg, pd, pe, kr, h, lnk, rd[d % ND], yd[d % ND], j,
-                                             rm[d % ND2], rp[d % ND2]);
-                if (d + ND < 8) {
-                    hop_fetch<S, G>(P, R_, d + ND, sg, lnbr, j, rd[d % ND], yd[d % ND]);
-                    if constexpr (PM == 2) hop_fetch2<S, G>(P, R_, sg, yd[d % ND], rm[d % ND2], rp[d % ND2]);
+            for (int x = 0; x < DS; ++x)
+                if (DS == 1 || ds == x) {   // wave-uniform
+#pragma unroll
+                    for (int d = 0; d < NDIR; ++d) {
+                        hop_apply<S, G, PM, PM == 2>(P, R_, x * NDIR + d, sg, pd, pe, kr, h, lnk, rd[d % ND], yd[d % ND],
+                                                     j, rm[d % ND2], rp[d % ND2]);
+                        if (d + ND < NDIR) {
+                            hop_fetch<S, G>(P, R_, x * NDIR + d + ND, sg, lnbr, j, rd[d % ND], yd[d % ND]);
+                            if constexpr (PM == 2) hop_fetch2<S, G>(P, R_, sg, yd[d % ND], rm[d % ND2], rp[d % ND2]);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                 }
-                __builtin_amdgcn_sched_barrier(0);
-            }
         } else if constexpr (PF == 1) {
             // ping-pong over two raw buffers: the loads of the next direction
             // are in flight while the current one is computed
@@ -1022,10 +1039,10 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
 #pragma unroll
     for (int g = 0; g < G; ++g)
 #pragma unroll
-        for (int k = 0; k < 24; ++k) hs[(w * G + g) * HSK + k * 64 + lane] = h[g][k];
+        for (int k = 0; k < 24; ++k) hs[(ds * KK + kw * G + g) * HSK + k * 64 + lane] = h[g][k];
     __syncthreads();
 
-    constexpr int CPW = 12 / hop_waves(KK, sizeof(S) == 8);
+    constexpr int CPW = 12 / NW;
     // per-component accesses: one instruction covers whole lines only in FP64
     // (one complex per 16-byte group); in FP32/BF16 a group holds several
     // components, read or written by different instructions, and a
@@ -1130,8 +1147,8 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
         V cr = {0, 0, 0, 0}, ci = {0, 0, 0, 0};
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) {
-            cr = mfma4(ap[kk], hs[kk * HSK + (2 * cp) * 64 + lane], cr);
-            ci = mfma4(ap[kk], hs[kk * HSK + (2 * cp + 1) * 64 + lane], ci);
+            cr = mfma4(ap[kk], hop_sum<DS, KK * HSK>(hs + kk * HSK + (2 * cp) * 64 + lane), cr);
+            ci = mfma4(ap[kk], hop_sum<DS, KK * HSK>(hs + kk * HSK + (2 * cp + 1) * 64 + lane), ci);
         }
         if (loc_mfma) {
 #pragma unroll
@@ -1183,8 +1200,8 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
         } else if (has_out2) {
 #pragma unroll
             for (int kk = 0; kk < KK; ++kk) {
-                dr = mfma4(ap2[kk], hs[kk * HSK + (2 * cp) * 64 + lane], dr);
-                di = mfma4(ap2[kk], hs[kk * HSK + (2 * cp + 1) * 64 + lane], di);
+                dr = mfma4(ap2[kk], hop_sum<DS, KK * HSK>(hs + kk * HSK + (2 * cp) * 64 + lane), dr);
+                di = mfma4(ap2[kk], hop_sum<DS, KK * HSK>(hs + kk * HSK + (2 * cp + 1) * 64 + lane), di);
             }
             if (has_loc) {
 #pragma unroll

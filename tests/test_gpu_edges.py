@@ -339,3 +339,12 @@ def test_brick_orders(dims, monkeypatch):
         M = dwf.PtcModel(2)
         hist.append(np.asarray(M.train([dwf.PtcPairs(op, None, [1, 3], seed=5)], 3, seed=3), dtype=float).ravel()[:3])
     assert np.allclose(hist[0], hist[1], rtol=1e-6, atol=0)   # FP32 sums in another order
+
+
+# FP64 launches of up to 256 blocks share the directions among the waves (Ls <= 4: four ways, <= 8: two ways)
+@pytest.mark.parametrize("dims,Ls", [((2, 2, 2, 2), 2), ((6, 6, 2, 2), 4), ((8, 8, 8, 16), 4), ((8, 8, 8, 18), 3),
+                                     ((2, 2, 2, 2), 5), ((6, 2, 6, 2), 7), ((8, 8, 8, 16), 8), ((8, 8, 8, 18), 6)])
+@pytest.mark.parametrize("b,c", [(1.0, 0.0), (1.5, 0.5)])
+def test_hop_shared_directions(dims, Ls, b, c):
+    """The small-lattice hop on both sides of the limits at which its waves share the directions."""
+    test_hop_forms_by_lattice_size(dims, Ls, b, c)

@@ -50,9 +50,14 @@ namespace dwf {
 // pipelining, unrolling only lets the compiler hoist the loads of several
 // directions and spill.  The work-list kernels, whose pre-mix mode is a
 // runtime value, keep 4 waves (FP64: 2).  The hop on 24^3x48, Ls = 16, takes
-// FP32 368, BF16 252 and FP64 812 us; the figures at the single switches below
+// FP32 335, BF16 230 and FP64 769 us; the figures at the single switches below
 // were measured one by one, most of them while fields lay in rows over all sites
-// (410, 265 and 869 us; precision.h).
+// (410, 265 and 869 us; precision.h) and in other bricks (choose_brick).  In FP32
+// it is bound by memory beyond the L2s: 1.28 GB read (0.72 would do) and 0.51 GB
+// written at 5.4 TB/s, where a copy reaches 5.6 (in bricks of 24x12x12 2.0 GB were
+// read, at 6.8 TB/s with the last-level cache).  Loads alone, without the
+// arithmetic, took 353 of 366 us then, the arithmetic alone 215; four blocks per CU
+// instead of three, two, or three to five directions in flight were all slower.
 #ifndef DWF_HOP_WAVES_PER_EU
 #define DWF_HOP_WAVES_PER_EU 4
 #endif

@@ -251,8 +251,8 @@ int dwf_apply_normal_noalloc(const dwf_op* op, int prec, void* out, const void* 
         const int k = kind_of(prec);
         DWF_REQUIRE(op->lat->has_gauge, DWF_ESTATE, "gauge field not set");
         const long Vh = op->lat->Vh, Vhp = op->lat->Vhp, n = (long)op->Ls * 12 * Vhp;
-        const size_t slot = (complex_bytes_of(k) * (size_t)n + 255) & ~(size_t)255;
-        if (4 * slot > NOALLOC_SCRATCH_BYTES)
+        const size_t slot = complex_bytes_of(k) * (size_t)n;   // a multiple of 256 bytes: whole tiles
+        if (48 * complex_bytes_of(k) * (size_t)op->Ls * limit_sites(Vh) > NOALLOC_SCRATCH_BYTES)
             throw Error{DWF_EDIMS, "dwf_apply_normal_noalloc: four half fields of " + std::to_string(slot) +
                                        " bytes exceed its " + std::to_string(NOALLOC_SCRATCH_BYTES >> 20) +
                                        " MiB scratch; use dwf_apply_normal"};

@@ -215,6 +215,14 @@ struct dwf_op {
 };
 
 namespace dwf {
+// Sites per parity by which entry points limit the size of a field: an odd
+// multiple of 32, never less than Vhp.  (Fields were padded to it once; what a
+// caller may rely on being refused is not moved with the padding.)
+inline long limit_sites(long Vh) {
+    const long n = (Vh + 31) / 32;
+    return 32 * (n % 2 ? n : n + 1);
+}
+
 // Call scratch of an operator: a half field, a two-slice FP64 half field
 // (4D sources), and room for `doubles` reduction partials and scalars.
 struct FieldScratch : Scratch {

@@ -58,7 +58,7 @@ HopParams hop_params(const dwf_op* op, int kind, int out_parity, const void* in,
     P.done_stride = 0;
     P.pstride = hop_grid_blocks(Vh);
     // the kernels address one right-hand side with 32-bit byte offsets
-    DWF_REQUIRE((double)P.Ls * 12.0 * (double)Vhp * (double)cb < 4294967296.0, DWF_EDIMS,
+    DWF_REQUIRE((double)P.Ls * 12.0 * (double)limit_sites(Vh) * (double)cb < 4294967296.0, DWF_EDIMS,
                 "field too large for 32-bit in-kernel offsets");
     return P;
 }

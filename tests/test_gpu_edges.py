@@ -348,3 +348,22 @@ def test_brick_orders(dims, monkeypatch):
 def test_hop_shared_directions(dims, Ls, b, c):
     """The small-lattice hop on both sides of the limits at which its waves share the directions."""
     test_hop_forms_by_lattice_size(dims, Ls, b, c)
+
+
+def test_noalloc_limit_is_where_it_was():
+    """8x8x14x26 with Ls = 15 in FP64: over the limit, which counts an odd multiple of 32 sites per parity; Ls = 14 is not."""
+    import torch
+
+    import paper_2602_14454_amd as dwf
+    dims = (8, 8, 14, 26)
+    lat, op = _make(dims, 15)[:2]
+    x = torch.zeros((15, lat.Vh, 4, 3), dtype=torch.complex128, device="cuda")
+    with pytest.raises(dwf.DwfError) as e:
+        op.apply_normal_noalloc(torch.empty_like(x), x, prec=0)
+    assert e.value.status == -2
+    op = _make(dims, 14)[1]
+    x = torch.zeros((14, lat.Vh, 4, 3), dtype=torch.complex128, device="cuda")
+    out = torch.ones_like(x)
+    op.apply_normal_noalloc(out, x, prec=0)
+    torch.cuda.synchronize()
+    assert not out.any()

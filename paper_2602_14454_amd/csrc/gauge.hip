@@ -327,30 +327,32 @@ __global__ __launch_bounds__(GU) __attribute__((amdgpu_waves_per_eu(2))) void ga
     }
 }
 
-__global__ __launch_bounds__(GT) void gauge_plaquette_kernel(const double2* __restrict__ U, Geo g, long V,
-                                                             double* __restrict__ partial) {
-    __shared__ double red[GT / 64];
-    const long x = (long)blockIdx.x * GT + threadIdx.x;
+// Sum of Re tr over the plaquettes of 64 sites, one plane per wave.  Bound by the
+// latency of its loads (a lane's links lie 576 bytes apart) and by their number;
+// the six planes of a site share the cache lines: 16^4 42 us, 52 us with
+// one thread for all planes of a site.
+constexpr int PLAQ_SITES = 64, PLAQ_PLANES = 6;
+__global__ __launch_bounds__(PLAQ_SITES * PLAQ_PLANES) void gauge_plaquette_kernel(const double2* __restrict__ U, Geo g,
+                                                                                  long V, double* __restrict__ partial) {
+    __shared__ double red[PLAQ_PLANES];
+    const long x = (long)blockIdx.x * PLAQ_SITES + (threadIdx.x & 63);
+    const int plane = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int mu = plane < 3 ? 0 : (plane < 5 ? 1 : 2), nu = plane < 3 ? plane + 1 : (plane < 5 ? plane - 1 : 3);
     double acc = 0.0;
     if (x < V) {
         int c[4];
         g.coords(x, c);
-        for (int mu = 0; mu < 4; ++mu) {
-            const long xpmu = g.shift(c, mu, +1);
-            for (int nu = mu + 1; nu < 4; ++nu) {
-                const long xpnu = g.shift(c, nu, +1);
-                const M3 P = mul(mul(mul(load_link(U, x, mu), load_link(U, xpmu, nu)), dag(load_link(U, xpnu, mu))),
-                                 dag(load_link(U, x, nu)));
-                acc += P.e[0].x + P.e[4].x + P.e[8].x;
-            }
-        }
+        const long xpmu = g.shift(c, mu, +1), xpnu = g.shift(c, nu, +1);
+        const M3 P = mul(mul(mul(load_link(U, x, mu), load_link(U, xpmu, nu)), dag(load_link(U, xpnu, mu))),
+                         dag(load_link(U, x, nu)));
+        acc = P.e[0].x + P.e[4].x + P.e[8].x;
     }
     for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+    if ((threadIdx.x & 63) == 0) red[plane] = acc;
     __syncthreads();
     if (threadIdx.x == 0) {
         double t = 0.0;
-        for (int w = 0; w < GT / 64; ++w) t += red[w];
+        for (int w = 0; w < PLAQ_PLANES; ++w) t += red[w];
         partial[blockIdx.x] = t;
     }
 }
@@ -392,13 +394,13 @@ void gauge_sweeps(void* U, const int dims[4], double beta, int nsweeps, int n_or
 
 int gauge_plaquette_partials(const int dims[4]) {
     const long V = (long)dims[0] * dims[1] * dims[2] * dims[3];
-    return (int)((V + GT - 1) / GT);
+    return (int)((V + PLAQ_SITES - 1) / PLAQ_SITES);
 }
 
 void gauge_plaquette(const void* U, const int dims[4], double* partial, double* out_dev, hipStream_t st) {
     const long V = (long)dims[0] * dims[1] * dims[2] * dims[3];
     const int nb = gauge_plaquette_partials(dims);
-    hipLaunchKernelGGL(gauge_plaquette_kernel, dim3(nb), dim3(GT), 0, st, static_cast<const double2*>(U),
+    hipLaunchKernelGGL(gauge_plaquette_kernel, dim3(nb), dim3(PLAQ_SITES * PLAQ_PLANES), 0, st, static_cast<const double2*>(U),
                        geo_of(dims), V, partial);
     DWF_HIP(hipGetLastError());
     finalize(partial, nb, 1, out_dev, 0, st);

@@ -367,3 +367,13 @@ def test_noalloc_limit_is_where_it_was():
     op.apply_normal_noalloc(out, x, prec=0)
     torch.cuda.synchronize()
     assert not out.any()
+
+
+# 16 sites (part of a block of 64), 64, 96 and 288 (remainders); extents of 2, 6 and 10
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (4, 2, 4, 2), (2, 6, 2, 4), (2, 6, 6, 4), (10, 2, 4, 2)])
+def test_plaquette_blocks(dims):
+    """Every plane of the plaquette sum around its blocks; tolerance of test_gpu_gauge.py."""
+    import paper_2602_14454_amd as dwf
+    from oracle import gauge as G
+    U = dwfgen.random_su3_links(dims, 0.5, 5)
+    assert abs(dwf.gauge_plaquette(_dev(U), dims) - G.plaquette(U, dims)) < 1e-12

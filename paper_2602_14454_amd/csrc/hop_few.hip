@@ -65,20 +65,34 @@ static bool launch_few(const HopParams& P, int nrhs, hipStream_t st) {
     return true;
 }
 
+// Forms compiled per pre-mix mode: the operators' launches have no others.  Any
+// other pair, ek = -1 (no compiled epilogue) among them, takes the general form.
+template <int PM>
+static bool launch_few_pm(const HopParams& P, int nrhs, int ek, hipStream_t st) {
+    switch (ek) {
+        case EK_PLAIN: return launch_few<PM, EK_PLAIN>(P, nrhs, st);
+        case EK_LOCD: return launch_few<PM, EK_LOCD>(P, nrhs, st);
+        default: break;
+    }
+    if constexpr (PM == 0) {
+        switch (ek) {
+            case EK_CHAIN: return launch_few<0, EK_CHAIN>(P, nrhs, st);
+            case EK_UPD: return launch_few<0, EK_UPD>(P, nrhs, st);
+            case EK_UPDS: return launch_few<0, EK_UPDS>(P, nrhs, st);
+            case EK_LOCI: return launch_few<0, EK_LOCI>(P, nrhs, st);
+            case EK_CHAINN: return launch_few<0, EK_CHAINN>(P, nrhs, st);
+            default: break;
+        }
+    }
+    return false;
+}
+
 bool launch_hop_few(const HopParams& P, int nrhs, int ek, hipStream_t st) {
     if ((long)hop_grid_blocks(P.Vh) * nrhs * hop_waves((P.Ls + 3) / 4, true) > DWF_HOP_FEW_WAVES) return false;
-    switch (P.pre_mode * 8 + ek) {
-        case EK_PLAIN: return launch_few<0, EK_PLAIN>(P, nrhs, st);
-        case EK_CHAIN: return launch_few<0, EK_CHAIN>(P, nrhs, st);
-        case EK_UPD: return launch_few<0, EK_UPD>(P, nrhs, st);
-        case EK_UPDS: return launch_few<0, EK_UPDS>(P, nrhs, st);
-        case EK_LOCD: return launch_few<0, EK_LOCD>(P, nrhs, st);
-        case EK_LOCI: return launch_few<0, EK_LOCI>(P, nrhs, st);
-        case EK_CHAINN: return launch_few<0, EK_CHAINN>(P, nrhs, st);
-        case 8 + EK_PLAIN: return launch_few<1, EK_PLAIN>(P, nrhs, st);
-        case 8 + EK_LOCD: return launch_few<1, EK_LOCD>(P, nrhs, st);
-        case 16 + EK_PLAIN: return launch_few<2, EK_PLAIN>(P, nrhs, st);
-        case 16 + EK_LOCD: return launch_few<2, EK_LOCD>(P, nrhs, st);
+    switch (P.pre_mode) {
+        case 0: return launch_few_pm<0>(P, nrhs, ek, st);
+        case 1: return launch_few_pm<1>(P, nrhs, ek, st);
+        case 2: return launch_few_pm<2>(P, nrhs, ek, st);
         default: return false;
     }
 }

@@ -116,7 +116,7 @@ static void launch_hop_ek(const HopParams& P, int nrhs, hipStream_t st) {
 // mode-1 hop it times.
 template <class S, int TAG, int PM>
 static void launch_hop_pm(const HopParams& P, int nrhs, hipStream_t st) {
-    const int ek = DWF_HOP_EK ? epilogue_kind(P) : -1;
+    const int ek = epilogue_kind(P);
     if constexpr (sizeof(S) == 8 && TAG == 0)
         if (launch_hop_few(P, nrhs, ek, st)) return;
     if constexpr ((TAG == 1 && PM != 1) || (sizeof(S) == 8 && PM != 0)) {

@@ -143,7 +143,6 @@ static void launch_hop_batch1_ek(int KK, dim3 grid, dim3 block, unsigned smem_b,
 template <class S, int PM>
 static void launch_hop_batch1_pm(int KK, dim3 grid, dim3 block, unsigned smem_b, const HopParams* items,
                                  const int* meta, int nitems, int order, int ek, hipStream_t st) {
-    if (!DWF_HOP_EK) ek = -1;
     if constexpr (PM < 0 || (sizeof(S) == 8 && PM != 0)) {
         launch_hop_batch1_ek<S, PM, -1>(KK, grid, block, smem_b, items, meta, nitems, order, st);
     } else if constexpr (PM != 0) {

@@ -119,12 +119,6 @@ namespace dwf {
 #ifndef DWF_HOP_UPD_EARLY32
 #define DWF_HOP_UPD_EARLY32 1
 #endif
-// Single-lattice launches of the fused CG stages use kernels compiled for
-// their epilogue kind (epilogue_kind below); 0: every launch tests its flags
-// at run time.
-#ifndef DWF_HOP_EK
-#define DWF_HOP_EK 1
-#endif
 // FP32: stage the dense s-mix matrices in LDS with the links (the second
 // phase then reads them from LDS instead of waiting for L2 after the block
 // barriers).

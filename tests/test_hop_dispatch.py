@@ -69,3 +69,36 @@ int main() {
             assert f"PM = {pm}, EK = {ek}," in launches[0], (pm, ek, launches)
         else:
             assert taken == 0 and not launches, (pm, ek, launches)
+
+
+@pytest.mark.parametrize("define", ["DWF_HOP_EK=1", "DWF_HOP_EK=0"])
+def test_update_that_forms_alpha_has_its_kernel(tmp_path, define):
+    """The last hop of a CG step with the step length formed in it (HopParams::sum), which small solves use in every
+    precision: the launch finds the kernel that does this, with any definition of the former switch DWF_HOP_EK."""
+    out = _run(tmp_path, r"""
+#include "hop.hip"
+namespace dwf { bool launch_hop_few(const HopParams&, int, int, hipStream_t) { return false; } }
+int main() {
+    using namespace dwf;
+    double some[1];
+    for (int Ls = 5; Ls <= 16; ++Ls)
+        for (int kind : {ST_F64, ST_F32, ST_BF16}) {
+            HopParams P{};
+            P.Vh = 128;
+            P.Ls = Ls;
+            P.loc = P.locmix = P.upd = P.partial = P.scal = some;
+            P.sum = some;
+            P.nsum = 8;
+            P.reduce = 3;
+            std::printf("case %d %d\n", Ls, kind);
+            try {
+                launch_hop(kind, P, 1, nullptr);
+            } catch (const Error& e) {
+                std::printf("  refused %s\n", e.msg.c_str());
+            }
+        }
+}
+""", "-D" + define)
+    assert len(out) == 2 * 12 * 3 and not [line for line in out if "refused" in line], out
+    for line in out[1::2]:
+        assert "hop_mfma_kernel" in line and "PM = 0, EK = 7" in line, line

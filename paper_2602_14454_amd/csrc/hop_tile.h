@@ -720,7 +720,9 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
     const unsigned tu0 = (unsigned)tile * tileu;
     R_.upd = make_rsrc(P.upd ? static_cast<char*>(P.upd) + (size_t)rhs * fieldu : nullptr,
                        (P.upd && active) ? fieldu : 0u);
-    R_.links = make_rsrc(P.links, 8u * link_ng(CB) * (unsigned)P.Vhp * link_lp(CB) * CB);
+    // the tile's links alone: the whole table may exceed 4 GiB (it is larger than a field of few slices)
+    constexpr unsigned linkb = 8u * link_ng(CB) * GRB;
+    R_.links = make_rsrc(static_cast<const char*>(P.links) + (size_t)tile * linkb, linkb);
     R_.nbr = make_rsrc(P.nbr, 8u * (unsigned)P.Vhp * 4u);
 
     // Slice groups of this wave, and the pipelined loop's buffers
@@ -758,7 +760,7 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
     // zero (site 0); a neighbour is staged as the byte offset of its groups.  (The
     // tile's offset is a scalar operand here only: a descriptor of size zero bounds
     // the vector operand.)
-    const unsigned l0 = (unsigned)tile * (8u * link_ng(CB) * GRB), n0 = (unsigned)tile * 512u;
+    const unsigned n0 = (unsigned)tile * 512u;
     auto offset_of = [&](unsigned y) -> unsigned { return (y >> 4) * tileb + (y & 15u) * 16u; };
     if constexpr (SBATCH) {
         // the tile's links (16-byte groups) and neighbour indices, once per
@@ -774,7 +776,7 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
 #pragma unroll
         for (int i = 0; i < IT; ++i) {
             const int e = min((int)threadIdx.x + i * (int)blockDim.x, NE - 1);
-            lv[i] = __builtin_amdgcn_raw_buffer_load_b128(R_.links, (unsigned)e * 16u, l0, DWF_HOP_NT_LINK);
+            lv[i] = __builtin_amdgcn_raw_buffer_load_b128(R_.links, (unsigned)e * 16u, 0u, DWF_HOP_NT_LINK);
         }
 #pragma unroll
         for (int i = 0; i < IB; ++i) {
@@ -813,7 +815,7 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
     if constexpr (!SBATCH) {
         // the same tables, one entry per thread and step
         for (int e = threadIdx.x; e < lnk_entries<S>(); e += blockDim.x)
-            lnk[e] = __builtin_amdgcn_raw_buffer_load_b128(R_.links, (unsigned)e * 16u, l0, DWF_HOP_NT_LINK);
+            lnk[e] = __builtin_amdgcn_raw_buffer_load_b128(R_.links, (unsigned)e * 16u, 0u, DWF_HOP_NT_LINK);
         for (int e = threadIdx.x; e < 128; e += blockDim.x)
             lnbr[e] = offset_of(__builtin_amdgcn_raw_buffer_load_b32(R_.nbr, (unsigned)e * 4u, n0, DWF_HOP_NT_LINK));
     }

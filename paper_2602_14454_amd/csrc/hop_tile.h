@@ -713,13 +713,13 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
     R_.loc = make_rsrc(P.loc ? static_cast<const char*>(P.loc) + rhsb : nullptr, P.loc ? fieldb_a : 0u);
     R_.out = make_rsrc(P.out ? static_cast<const char*>(P.out) + rhsb : nullptr, P.out ? fieldb_a : 0u);
     R_.out2 = make_rsrc(P.out2 ? static_cast<const char*>(P.out2) + rhsb : nullptr, P.out2 ? fieldb_a : 0u);
-    // fused CG update target: compute type in its own layout
+    // fused CG update target: compute type in its own layout; this tile alone (with
+    // BF16 fields its FP32 groups may lie past 4 GiB)
     constexpr unsigned PKU = fpack<typename std::conditional<sizeof(R) == 8, double, float>::type>();
     const unsigned tileu = (unsigned)Ls * (12u / PKU) * GRB;
-    const unsigned fieldu = tileu * ((unsigned)P.Vhp >> 4);
-    const unsigned tu0 = (unsigned)tile * tileu;
-    R_.upd = make_rsrc(P.upd ? static_cast<char*>(P.upd) + (size_t)rhs * fieldu : nullptr,
-                       (P.upd && active) ? fieldu : 0u);
+    R_.upd = make_rsrc(P.upd ? static_cast<char*>(P.upd) + ((size_t)rhs * (size_t)(P.Vhp >> 4) + (size_t)tile) * tileu
+                             : nullptr,
+                       (P.upd && active) ? tileu : 0u);
     // the tile's links alone: the whole table may exceed 4 GiB (it is larger than a field of few slices)
     constexpr unsigned linkb = 8u * link_ng(CB) * GRB;
     R_.links = make_rsrc(static_cast<const char*>(P.links) + (size_t)tile * linkb, linkb);
@@ -1023,7 +1023,7 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
                 for (int i = 0; i < 4; ++i) {
                     const int cp = w * CPW_ + q, s_ = out_row<R>(sc, i);
                     uvl[q][i] = __builtin_amdgcn_raw_buffer_load_b128(
-                        R_.upd, sxb + ((unsigned)(s_ < Ls ? s_ : 0) * 12u + (unsigned)cp) * GRB, 0u, 0);
+                        R_.upd, (unsigned)j * 16u + ((unsigned)(s_ < Ls ? s_ : 0) * 12u + (unsigned)cp) * GRB, 0u, 0);
                 }
         }
         if constexpr (UPDE) {
@@ -1031,7 +1031,7 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
 #pragma unroll
             for (int i = 0; i < IUE; ++i) {
                 const int e = min(tid + i * NTHR, nU - 1);
-                uve[i] = __builtin_amdgcn_raw_buffer_load_b128(R_.upd, tu0 + (unsigned)e * 16u, 0u, DWF_HOP_NT_LOAD);
+                uve[i] = __builtin_amdgcn_raw_buffer_load_b128(R_.upd, (unsigned)e * 16u, 0u, DWF_HOP_NT_LOAD);
             }
         }
     }
@@ -1227,11 +1227,11 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
                             ur = v8[0];
                             ui = v8[1];
                         } else {
-                            bload<S, WAUX>(R_.upd, coff(s, cp), 0u, ur, ui);
+                            bload<S, WAUX>(R_.upd, coff(s, cp) - t0, 0u, ur, ui);
                         }
                         ur -= ua * cr[i];
                         ui -= ua * ci[i];
-                        bstore<S, SAUX>(R_.upd, coff(s, cp), 0u, ur, ui);
+                        bstore<S, SAUX>(R_.upd, coff(s, cp) - t0, 0u, ur, ui);
                         if (f_reduce == 3) nrm += double(ur) * double(ur) + double(ui) * double(ui);
                     }
                     if (f_out) bstore<S, SAUX>(R_.out, coff(s, cp), 0u, cr[i], ci[i]);
@@ -1287,7 +1287,7 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
                 if constexpr (UPDE)
                     uv[i] = uve[i];
                 else
-                    uv[i] = __builtin_amdgcn_raw_buffer_load_b128(R_.upd, tu0 + (unsigned)e * 16u, 0u, DWF_HOP_NT_LOAD);
+                    uv[i] = __builtin_amdgcn_raw_buffer_load_b128(R_.upd, (unsigned)e * 16u, 0u, DWF_HOP_NT_LOAD);
             }
 #pragma unroll
             for (int i = 0; i < IU; ++i) {
@@ -1299,7 +1299,7 @@ __device__ __forceinline__ void hop_tile(const HopParams& P, long tile, int rhs,
                     float v2 = __uint_as_float(u.z) - ua * b.x, v3 = __uint_as_float(u.w) - ua * b.y;
                     u32x4 o;
                     o.x = __float_as_uint(v0); o.y = __float_as_uint(v1); o.z = __float_as_uint(v2); o.w = __float_as_uint(v3);
-                    __builtin_amdgcn_raw_buffer_store_b128(o, R_.upd, tu0 + (unsigned)e * 16u, 0u, DWF_HOP_NT_STORE);
+                    __builtin_amdgcn_raw_buffer_store_b128(o, R_.upd, (unsigned)e * 16u, 0u, DWF_HOP_NT_STORE);
                     if (f_reduce == 3)
                         nrm += double(v0) * double(v0) + double(v1) * double(v1) + double(v2) * double(v2) +
                                double(v3) * double(v3);

@@ -24,7 +24,7 @@
 // without acceptance in 1000 attempts keeps that subgroup unchanged.
 //
 // During a call the links are kept, in the caller's buffer, in tiles of 32 site
-// pairs (2k, 2k+1) with the site index fastest (TileLayout): in the canonical
+// pairs (2k, 2k+1) with the site index fastest (slot_of): in the canonical
 // layout every lane of a load touches a cache line of its own.
 #include "dwf_internal.h"
 #include "blas.h"
@@ -129,7 +129,56 @@ __device__ inline Slot slot_of(unsigned lex, int parity, unsigned npairs) {
     return {(size_t)t * TELEM + (unsigned)parity * n + (k - first), 2u * n};
 }
 
-// canonical -> tiles (TO_TILES) or back, in place, one tile per block
+// A link projected onto SU(3), element e at p[e * stride]: rows 0, 1 normalised and
+// orthogonalised, row 2 = conj(row0 x row1).
+__device__ __forceinline__ void project_su3(double2* p, unsigned stride) {
+    double2 a[3], b[3];
+    double na = 0.0, nb = 0.0;
+#pragma unroll
+    for (unsigned k = 0; k < 3; ++k) {
+        a[k] = p[k * stride];
+        b[k] = p[(3 + k) * stride];
+        na += a[k].x * a[k].x + a[k].y * a[k].y;
+    }
+    na = sqrt(na);
+    double2 dot = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        a[k] = make_double2(a[k].x / na, a[k].y / na);
+        dot = cadd(dot, cmul(cconj(a[k]), b[k]));
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const double2 t = cmul(dot, a[k]);
+        b[k] = make_double2(b[k].x - t.x, b[k].y - t.y);
+        nb += b[k].x * b[k].x + b[k].y * b[k].y;
+    }
+    nb = sqrt(nb);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) b[k] = make_double2(b[k].x / nb, b[k].y / nb);
+#pragma unroll
+    for (unsigned k = 0; k < 3; ++k) {
+        const unsigned i = (k + 1) % 3, j = (k + 2) % 3;
+        const double2 u = cmul(a[i], b[j]), v = cmul(a[j], b[i]);
+        p[k * stride] = a[k];
+        p[(3 + k) * stride] = b[k];
+        p[(6 + k) * stride] = make_double2(u.x - v.x, -(u.y - v.y));
+    }
+}
+
+// The links after a sweep, in tiles: a thread per link, site fastest.  Bound by
+// memory: 16^4 10.9 us (75 MB at 5.8 TB/s without the third rows' reads).  After
+// the call's last sweep the conversion back does it, in the time of its own
+// (15.6 us).
+__global__ __launch_bounds__(GT) void gauge_project_kernel(double2* __restrict__ U, unsigned npairs) {
+    const unsigned l = blockIdx.x * GT + threadIdx.x, t = l / (2 * TPAIRS), mu = blockIdx.y;
+    if (l >= 2 * npairs) return;
+    const unsigned n = min((unsigned)TPAIRS, npairs - t * TPAIRS);
+    project_su3(U + (size_t)t * TELEM + (size_t)(mu * 9) * (2 * n) + (l - t * (2 * TPAIRS)), 2 * n);
+}
+
+// canonical -> tiles (TO_TILES), or back with the links projected, in place, one
+// tile per block
 template <bool TO_TILES>
 __global__ __launch_bounds__(GT) void gauge_tiles_kernel(double2* __restrict__ U, Geo g, unsigned npairs) {
     __shared__ double2 buf[TELEM];
@@ -137,6 +186,12 @@ __global__ __launch_bounds__(GT) void gauge_tiles_kernel(double2* __restrict__ U
     double2* p = U + (size_t)blockIdx.x * TELEM;
     for (unsigned e = threadIdx.x; e < 72u * n; e += GT) buf[e] = p[e];
     __syncthreads();
+    if (!TO_TILES) {
+        static_assert(GT == 2 * TPAIRS * 4, "a thread per link of the tile");
+        const unsigned l = threadIdx.x % (2u * TPAIRS), mu = threadIdx.x / (2u * TPAIRS);
+        if (l < 2u * n) project_su3(buf + mu * 9u * (2u * n) + l, 2u * n);
+        __syncthreads();
+    }
     for (unsigned e = threadIdx.x; e < 72u * n; e += GT) {
         // e walks the destination; site q of the tile's 2 n sites, element m of 36
         unsigned q, m, src;
@@ -242,14 +297,15 @@ __device__ inline void update_subgroup(double2 (&w)[3], double2 (&u)[3], double 
     u[B] = cmac(cmul(R10, ua), R11, ub);
 }
 
-// One update of U_mu on the sites of one parity, with the new link projected
-// back onto SU(3).  Four lanes per link: lane nu forms the two staples of
+// One update of U_mu on the sites of one parity.  Four lanes per link: lane nu forms the two staples of
 // direction nu, then lane c (0..2) carries column c of the link and of W
 // through the subgroups.  On 16^4 (131072 lanes, two waves per SIMD) a launch is bound
-// by its own chain (loads, ~700 FP64 instructions, square roots): 13.8 us, and
-// 23.6 us for the heatbath; one thread per link in the canonical layout, with
-// the projection in a launch of its own, took 29 us.  A step of one heatbath and
-// four over-relaxation sweeps: 16^4 1.33 -> 0.64 ms, 24^3x48 16.2 -> 5.4 ms.
+// by its own chain (loads, ~650 FP64 instructions, square roots): 13.5 us, and
+// 23.4 us for the heatbath; one thread per link in the canonical layout took
+// 29 us.  A step of one heatbath and four over-relaxation sweeps: 16^4 1.33 ->
+// 0.65 ms, 24^3x48 16.2 -> 5.6 ms (0.61 and 5.2 with the projection at the end of
+// each update instead, but then the staples of a sweep see its links projected,
+// which is another update for links that are not exactly SU(3)).
 constexpr int GU = 256;
 template <bool HB>
 __global__ __launch_bounds__(GU) __attribute__((amdgpu_waves_per_eu(2))) void gauge_update_kernel(
@@ -309,18 +365,6 @@ __global__ __launch_bounds__(GU) __attribute__((amdgpu_waves_per_eu(2))) void ga
     update_subgroup<HB, 0, 1>(w, u, beta, key, cbase * 4096ull);
     update_subgroup<HB, 0, 2>(w, u, beta, key, (cbase + 1ull) * 4096ull);
     update_subgroup<HB, 1, 2>(w, u, beta, key, (cbase + 2ull) * 4096ull);
-    // rows 0, 1 normalised and orthogonalised, row 2 = conj(row0 x row1)
-    auto row_sum = [&](double v) { return quad_sum(lane == 3 ? 0.0 : v); };
-    const double ra = 1.0 / sqrt(row_sum(u[0].x * u[0].x + u[0].y * u[0].y));
-    u[0] = make_double2(u[0].x * ra, u[0].y * ra);
-    const double2 d = cmul(cconj(u[0]), u[1]);
-    const double2 dot = make_double2(row_sum(d.x), row_sum(d.y));
-    u[1] = cmac(u[1], make_double2(-dot.x, -dot.y), u[0]);
-    const double rb = 1.0 / sqrt(row_sum(u[1].x * u[1].x + u[1].y * u[1].y));
-    u[1] = make_double2(u[1].x * rb, u[1].y * rb);
-    const double2 a1 = quad<1, 2, 0, 1>(u[0]), a2 = quad<2, 0, 1, 2>(u[0]), b1 = quad<1, 2, 0, 1>(u[1]),
-                  b2 = quad<2, 0, 1, 2>(u[1]);
-    u[2] = cconj(cmac(cmul(a1, b2), make_double2(-a2.x, -a2.y), b1));
     if (live && lane < 3) {
 #pragma unroll
         for (int i = 0; i < 3; ++i) (U + sx.base)[(unsigned)(mu * 9 + i * 3 + lane) * sx.stride] = u[i];
@@ -377,7 +421,7 @@ void gauge_sweeps(void* U, const int dims[4], double beta, int nsweeps, int n_or
     hipLaunchKernelGGL(gauge_tiles_kernel<true>, dim3(tiles), dim3(GT), 0, st, u, g, npairs);
     for (int k = 0; k < nsweeps; ++k) {
         const unsigned long long key = mix64(seed * GK1 + (unsigned long long)(sweep0 + k) * GK2);
-        for (int o = 0; o <= n_or; ++o)
+        for (int o = 0; o <= n_or; ++o) {
             for (int mu = 0; mu < 4; ++mu)
                 for (int p = 0; p < 2; ++p) {
                     if (o == 0)
@@ -387,6 +431,9 @@ void gauge_sweeps(void* U, const int dims[4], double beta, int nsweeps, int n_or
                         hipLaunchKernelGGL(gauge_update_kernel<false>, dim3(blocks), dim3(GU), 0, st, u, g, mu, p, beta,
                                            key, npairs);
                 }
+            if (o < n_or || k + 1 < nsweeps)
+                hipLaunchKernelGGL(gauge_project_kernel, dim3((2 * npairs + GT - 1) / GT, 4), dim3(GT), 0, st, u, npairs);
+        }
     }
     hipLaunchKernelGGL(gauge_tiles_kernel<false>, dim3(tiles), dim3(GT), 0, st, u, g, npairs);
     DWF_HIP(hipGetLastError());

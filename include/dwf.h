@@ -146,9 +146,10 @@ int dwf_lattice_maps(const dwf_lattice* lat, int* lex_of_site, int* nbr);
 
 /* D^(alpha) with s-independent (b, c) (Sec. 2.2; Sec. 2.3 eq. domainwall_neff).
  * 2 <= Ls <= 16.  The op references lat (lat must outlive it).  Calls that
- * apply the operator keep their temporaries (up to six half fields per
- * precision) with it from one call to the next, until dwf_op_destroy; the
- * library frees idle ones by itself when it runs out of device memory. */
+ * apply an operator keep their temporaries (up to six half fields) for later
+ * calls on any operator of the same Ls and number of sites: at most 8 GiB over
+ * all shapes, until the last such operator is destroyed or dwf_release_scratch;
+ * the library also frees idle ones by itself when it runs out of device memory. */
 int dwf_op_create(dwf_lattice* lat, int Ls, double M0, double m, double b, double c,
                   double alpha, dwf_op** out);
 /* The same with s-dependent coefficients: D_+^(s) = b[s] D_W + 1 and
@@ -160,6 +161,10 @@ int dwf_op_create(dwf_lattice* lat, int Ls, double M0, double m, double b, doubl
 int dwf_op_create_sdep(dwf_lattice* lat, int Ls, double M0, double m, const double* b, const double* c,
                        double alpha, dwf_op** out);
 void dwf_op_destroy(dwf_op* op);
+/* Frees the idle temporaries of every operator, for a program whose other
+ * allocations (PyTorch's, say) need the memory; calls in progress keep theirs,
+ * later ones allocate again. */
+int dwf_release_scratch(void);
 
 /* out = D^(alpha) in (space = FULL5D, 5D canonical) or D^ in (EVEN5D, even
  * canonical); dagger = 1 applies the adjoint.  prec selects the arithmetic

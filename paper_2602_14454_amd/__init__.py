@@ -18,7 +18,7 @@ __all__ = [
     "load", "DwfError", "SolveParams", "SolveInfo", "Lattice", "Op",
     "F64", "F32", "BF16", "FULL5D", "EVEN5D", "ALGO_CGNR", "ALGO_DC", "ALGO_FGCR_LEARNED", "ALGO_MIXED",
     "solve_batch", "autotune_batch", "tune_cache_put", "tune_cache_get", "tune_cache_reload",
-    "PtcModel", "PtcPairs", "gauge_sweeps", "gauge_plaquette",
+    "PtcModel", "PtcPairs", "gauge_sweeps", "gauge_plaquette", "release_scratch",
 ]
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -68,6 +68,7 @@ SIGNATURES = {
     "dwf_op_create": (_i, [_vp, _i, _d, _d, _d, _d, _d, ctypes.POINTER(_vp)]),
     "dwf_op_create_sdep": (_i, [_vp, _i, _d, _d, _dp, _dp, _d, ctypes.POINTER(_vp)]),
     "dwf_op_destroy": (None, [_vp]),
+    "dwf_release_scratch": (_i, []),
     "dwf_apply": (_i, [_vp, _i, _i, _i, _vp, _vp, _vp]),
     "dwf_apply_normal": (_i, [_vp, _i, _vp, _vp, _vp]),
     "dwf_apply_eo5": (_i, [_vp, _i, _i, _vp, _vp, _vp]),
@@ -167,6 +168,11 @@ def _dev_ptr(t):
     if not t.is_contiguous():
         raise ValueError("tensor must be contiguous")
     return ctypes.c_void_p(t.data_ptr())
+
+
+def release_scratch() -> None:
+    """Frees the idle temporaries that operator calls keep on the device for later calls (at most 8 GiB)."""
+    _check(load().dwf_release_scratch(), "dwf_release_scratch")
 
 
 def solve_batch(ops, x5s, b5s, nrhs, params=None, stream=None):

@@ -157,6 +157,13 @@ int dwf_op_create(dwf_lattice* lat, int Ls, double M0, double m, double b, doubl
 
 void dwf_op_destroy(dwf_op* op) { delete op; }
 
+int dwf_release_scratch(void) {
+    return guarded([&] {
+        release_scratch();
+        return DWF_OK;
+    });
+}
+
 static int kind_of(int prec) {
     DWF_REQUIRE(prec == DWF_F64 || prec == DWF_F32 || prec == DWF_BF16, DWF_EINVAL, "bad precision");
     return prec;

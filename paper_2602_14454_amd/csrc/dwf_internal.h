@@ -21,6 +21,7 @@
 #include <memory>
 #include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/dwf.h"
@@ -48,8 +49,7 @@ struct Error {
         if (!(cond)) throw ::dwf::Error{(code), (msg)};                            \
     } while (0)
 
-// Frees the idle scratch buffers of every operator (ScratchPool below); false
-// if there were none.
+// Frees the idle call scratch (scratch.cpp); false if there was none.
 bool release_scratch();
 
 // ---------------------------------------------------------------------
@@ -93,43 +93,56 @@ struct DevBuf {
     template <class T> T* as() const { return static_cast<T*>(p); }
 };
 
-// Idle scratch buffers of one operator, kept between calls: hipMalloc and
-// hipFree of the temporaries of one operator application cost more than the
+// Call scratch (scratch.cpp): temporaries of one operator application, kept
+// between calls because their hipMalloc and hipFree cost more than the
 // application (24^3x48, Ls = 16, FP32 normal operator: 2.3 ms of kernels in a
-// call of 5 to 58 ms).  One list per class of buffer (all of one size and
-// layout, so that the zero padding of a field stays valid), at most MAX_IDLE
-// buffers each; freed with the operator, or by release_scratch() when an
-// allocation of the library finds no memory.  A call takes its own buffers, so
-// calls from several threads never share one.
-struct ScratchPool {
+// call of 5 to 58 ms).  Idle buffers serve every operator of the same Ls and
+// sites per parity on the same device (ScratchKey: one size and one layout, so
+// that the zero padding of a field stays valid).  All idle buffers together are
+// at most SCRATCH_IDLE_MAX, the oldest freed first: 3 % of the device's memory,
+// and room for the largest call on 24^3x48, Ls = 16 (6.1 GB).  They are freed with
+// the last operator of their shape, by release_scratch(), and when an allocation
+// of the library finds no memory.  A call takes its own buffers, so calls from
+// several threads never share one.
+constexpr size_t SCRATCH_IDLE_MAX = size_t(8) << 30;
+struct ScratchKey {
     // half fields by StoreKind; two-slice FP64 fields; scalars
-    enum Class { F64 = 0, F32 = 1, BF16 = 2, PAIR = 3, SMALL = 4, NCLASS };
-    static constexpr size_t MAX_IDLE = 6;
-    std::mutex mu;
-    std::vector<DevBuf> idle[NCLASS];
-    ScratchPool();
-    ~ScratchPool();
-    DevBuf take(int cls, size_t bytes);
-    void give(int cls, DevBuf&& b);
-    bool clear();
+    enum Class { F64 = 0, F32 = 1, BF16 = 2, PAIR = 3, SMALL = 4 };
+    int dev, cls, Ls;
+    long Vh;
+    bool operator==(const ScratchKey& o) const { return dev == o.dev && cls == o.cls && Ls == o.Ls && Vh == o.Vh; }
+};
+DevBuf scratch_take(const ScratchKey& key, size_t bytes);
+void scratch_give(const ScratchKey& key, DevBuf&& b) noexcept;
+
+// An operator's claim to the idle buffers of its shape, on the device that is
+// current when it is made.
+class ScratchUser {
+    ScratchKey shape_{0, 0, 0, 0};
+public:
+    ScratchUser() = default;
+    ScratchUser(const ScratchUser&) = delete;
+    ScratchUser& operator=(const ScratchUser&) = delete;
+    ~ScratchUser();
+    void attach(int Ls, long Vh);
+    ScratchKey key(int cls) const { return {shape_.dev, cls, shape_.Ls, shape_.Vh}; }
 };
 
-// A scratch buffer for the length of one call.  It goes back to its pool at
-// the end of the scope, when the work that uses it must have completed; a scope
-// left by an exception, with work possibly in flight, frees it instead.
+// A scratch buffer for the length of one call.  It becomes idle at the end of
+// the scope, when the work that uses it must have completed; a scope left by an
+// exception, with work possibly in flight, frees it instead.
 class Scratch {
-    ScratchPool& pool_;
-    int cls_;
+    ScratchKey key_;
     int exc_;
     DevBuf b_;
 public:
     void* p;
-    Scratch(ScratchPool& pool, int cls, size_t bytes)
-        : pool_(pool), cls_(cls), exc_(std::uncaught_exceptions()), b_(pool.take(cls, bytes)), p(b_.p) {}
+    Scratch(const ScratchKey& key, size_t bytes)
+        : key_(key), exc_(std::uncaught_exceptions()), b_(scratch_take(key_, bytes)), p(b_.p) {}
     Scratch(const Scratch&) = delete;
     Scratch& operator=(const Scratch&) = delete;
     ~Scratch() {
-        if (std::uncaught_exceptions() == exc_) pool_.give(cls_, std::move(b_));
+        if (std::uncaught_exceptions() == exc_) scratch_give(key_, std::move(b_));
     }
     template <class T> T* as() const { return static_cast<T*>(p); }
 };
@@ -199,7 +212,7 @@ struct dwf_op {
     // the type); solves on one operator run one at a time
     mutable std::shared_ptr<void> solve_ws;
     mutable std::mutex solve_mu;
-    mutable dwf::ScratchPool scratch;
+    dwf::ScratchUser scratch;
     const void* mat(int store_kind, int slot) const {
         const int ck = store_kind == dwf::ST_F64 ? 0 : 1;
         const size_t esz = ck == 0 ? 8 : 4;
@@ -224,14 +237,15 @@ inline long limit_sites(long Vh) {
 }
 
 // Call scratch of an operator: a half field, a two-slice FP64 half field
-// (4D sources), and room for `doubles` reduction partials and scalars.
+// (4D sources), and room for reduction partials and scalars.
 struct FieldScratch : Scratch {
-    FieldScratch(const dwf_op* op, int kind) : Scratch(op->scratch, kind, op->field_bytes(kind)) {}
+    FieldScratch(const dwf_op* op, int kind) : Scratch(op->scratch.key(kind), op->field_bytes(kind)) {}
 };
 struct PairScratch : Scratch {
-    explicit PairScratch(const dwf_op* op) : Scratch(op->scratch, ScratchPool::PAIR, (size_t)2 * 12 * op->lat->Vhp * 16) {}
+    explicit PairScratch(const dwf_op* op)
+        : Scratch(op->scratch.key(ScratchKey::PAIR), (size_t)2 * 12 * op->lat->Vhp * 16) {}
 };
 struct SmallScratch : Scratch {
-    SmallScratch(const dwf_op* op, size_t bytes) : Scratch(op->scratch, ScratchPool::SMALL, bytes) {}
+    SmallScratch(const dwf_op* op, size_t bytes) : Scratch(op->scratch.key(ScratchKey::SMALL), bytes) {}
 };
 }  // namespace dwf

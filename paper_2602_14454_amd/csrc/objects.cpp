@@ -5,82 +5,12 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
-#include <mutex>
-#include <new>
 
 #include "blas.h"
 #include "dwf_internal.h"
 #include "precision.h"
 
 namespace dwf {
-
-// ---------------------------------------------------------------------
-// call scratch
-// ---------------------------------------------------------------------
-// pools that release_scratch() may empty; never destroyed, so that an operator
-// destroyed at process exit still finds them
-static std::mutex& pools_mu() {
-    static std::mutex* m = new std::mutex;
-    return *m;
-}
-static std::vector<ScratchPool*>& pools() {
-    static std::vector<ScratchPool*>* v = new std::vector<ScratchPool*>;
-    return *v;
-}
-
-ScratchPool::ScratchPool() {
-    std::lock_guard<std::mutex> lock(pools_mu());
-    pools().push_back(this);
-}
-
-ScratchPool::~ScratchPool() {
-    std::lock_guard<std::mutex> lock(pools_mu());
-    auto& v = pools();
-    v.erase(std::remove(v.begin(), v.end(), this), v.end());
-}
-
-DevBuf ScratchPool::take(int cls, size_t bytes) {
-    {
-        std::lock_guard<std::mutex> lock(mu);
-        auto& v = idle[cls];
-        for (size_t i = v.size(); i-- > 0;)
-            if (v[i].bytes == bytes) {
-                DevBuf b = std::move(v[i]);
-                v.erase(v.begin() + (long)i);
-                return b;
-            }
-    }
-    return DevBuf(bytes);
-}
-
-void ScratchPool::give(int cls, DevBuf&& b) {
-    DevBuf mine(std::move(b));   // freed here when the list is full
-    std::lock_guard<std::mutex> lock(mu);
-    if (idle[cls].size() < MAX_IDLE) {
-        try {
-            idle[cls].push_back(std::move(mine));
-        } catch (const std::bad_alloc&) {
-        }
-    }
-}
-
-bool ScratchPool::clear() {
-    std::vector<DevBuf> out[NCLASS];
-    {
-        std::lock_guard<std::mutex> lock(mu);
-        for (int c = 0; c < NCLASS; ++c) out[c].swap(idle[c]);
-    }
-    for (const auto& v : out)
-        if (!v.empty()) return true;
-    return false;
-}
-
-bool release_scratch() {
-    std::lock_guard<std::mutex> lock(pools_mu());
-    bool any = false;
-    for (ScratchPool* p : pools()) any = p->clear() || any;
-    return any;
-}
 
 // Internal site order.  Two orders exist; both are bijections onto the
 // sites of each parity, and every kernel goes through the site and
@@ -348,6 +278,7 @@ static std::vector<double> mm(const std::vector<double>& A, const std::vector<do
 
 void setup_op(dwf_op* op) {
     const int Ls = op->Ls;
+    op->scratch.attach(Ls, op->lat->Vh);
     op->fd = build_fifth_dim(Ls, op->M0, op->m, op->b, op->c, op->alpha);
     const FifthDim& f = op->fd;
     std::vector<double> h((size_t)NMAT * MAT_ELEMS, 0.0);

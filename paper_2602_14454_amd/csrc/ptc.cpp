@@ -93,6 +93,7 @@ static bool by_pairs(int H) { return H >= 2; }
 void dwf_ptc::reserve(const dwf_op* op, hipStream_t st) {
     const long n = ptc_field_elems(op);
     if (n > cap_n) {
+        cap_n = 0;   // nothing is complete until every buffer is there
         hid.alloc((size_t)(by_pairs(H) ? 8 : 2) * n * sizeof(float2));
         y.alloc(n * sizeof(float2));
         g.alloc(n * sizeof(float2));

@@ -81,7 +81,7 @@ struct DevBuf {
             throw Error{DWF_ENOMEM, "hipMalloc(" + std::to_string(n) + " bytes) failed"};
         }
         bytes = n;
-        // fields keep zero padding beyond the last site of every row
+        // fields keep zero padding past the last site (whole tiles of 16)
         e = hipMemset(p, 0, n);
         if (e != hipSuccess) throw Error{DWF_EHIP, "hipMemset failed"};
     }
@@ -176,10 +176,9 @@ struct dwf_lattice {
     int site_order = 0;             // 0 bricks swept in t, 1 t columns (build_geometry)
     dwf::DevBuf random_site;        // even sites: place in the random fields (empty: the site itself)
     std::vector<int> lex_of_site;   // host [2][Vh]: lexicographic index of internal site
-    std::vector<int> nbr_host;    // host copy of nbr
-    dwf::DevBuf nbr;              // device [2][8][Vh]
+    dwf::DevBuf nbr;                // device: per parity, in tiles of 16 sites (precision.h), 8 Vhp entries
     dwf::DevBuf lex_of_site_dev;    // device [2][Vh]
-    dwf::DevBuf links[3];         // per storage kind: [2][8][9][Vh] complex
+    dwf::DevBuf links[3];           // per storage kind and parity, in tiles (lidx; link_elems_parity(Vhp, ..) complex)
     bool has_gauge = false;
 };
 

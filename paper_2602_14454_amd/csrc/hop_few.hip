@@ -50,7 +50,8 @@ static bool launch_few(const HopParams& P, int nrhs, hipStream_t st) {
     const bool split = (long)hop_grid_blocks(P.Vh) * nrhs <= DWF_HOP_SPLIT_BLOCKS;
     switch ((P.Ls + 3) / 4) {
         case 1:
-            if (split) launch_few_kk<1, PM, EK, 4>(P, nrhs, st);
+            if constexpr (EK == EK_UPDS) return false;   // Ls <= 4: cg_few has no such launch
+            else if (split) launch_few_kk<1, PM, EK, 4>(P, nrhs, st);
             else launch_few_kk<1, PM, EK, 1>(P, nrhs, st);
             break;
         case 2:

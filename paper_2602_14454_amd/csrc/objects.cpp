@@ -192,7 +192,7 @@ void build_geometry(dwf_lattice* L) {
         sweep_bricks(L->dims, L->brick, place);
     }
     DWF_REQUIRE(next[0] == Vh && next[1] == Vh, DWF_EDIMS, "internal site order is not a bijection");
-    L->nbr_host.assign(2 * 8 * Vhp, 0);
+    std::vector<int> nbr(2 * 8 * Vhp, 0);   // padding: site 0
     const int ext[4] = {Lx, Ly, Lz, Lt};
     for (int p = 0; p < 2; ++p)
         for (long i = 0; i < Vh; ++i) {
@@ -205,7 +205,7 @@ void build_geometry(dwf_lattice* L) {
                 int cc[4] = {c[0], c[1], c[2], c[3]};
                 cc[mu] = (cc[mu] + dir + ext[mu]) % ext[mu];
                 const long y = cc[0] + (long)Lx * (cc[1] + (long)Ly * (cc[2] + (long)Lz * cc[3]));
-                L->nbr_host[p * 8 * Vhp + ((i >> 4) * 8 + d) * 16 + (i & 15)] = site_of_lex[y];
+                nbr[p * 8 * Vhp + ((i >> 4) * 8 + d) * 16 + (i & 15)] = site_of_lex[y];
             }
         }
     int halved[3];
@@ -221,7 +221,7 @@ void build_geometry(dwf_lattice* L) {
         DWF_HIP(hipMemcpy(L->random_site.p, at.data(), L->random_site.bytes, hipMemcpyHostToDevice));
     }
     L->nbr.alloc(sizeof(int) * 2 * 8 * Vhp);
-    DWF_HIP(hipMemcpy(L->nbr.p, L->nbr_host.data(), L->nbr.bytes, hipMemcpyHostToDevice));
+    DWF_HIP(hipMemcpy(L->nbr.p, nbr.data(), L->nbr.bytes, hipMemcpyHostToDevice));
     L->lex_of_site_dev.alloc(sizeof(int) * 2 * Vh);
     DWF_HIP(hipMemcpy(L->lex_of_site_dev.p, L->lex_of_site.data(), L->lex_of_site_dev.bytes, hipMemcpyHostToDevice));
 }

@@ -149,7 +149,9 @@ void apply_normal_update_r(const dwf_op* op, int kind, void* r, const void* p, v
 // defect correction, before -> after: 8^4, Ls = 8 (128 partials) 68 / 53 -> 61 / 50
 // and 59 / 45 -> 51 / 42; 8^3x16, Ls = 12 (256) 82 / 71 -> 78 / 70 and 61 / 48 ->
 // 54 / 45; with 512 partials (8^2x16^2, Ls = 16) 137 / 123 -> 133 / 122 and 84 / 73
-// -> 83 / 74, with 648 and 1024 up to 10 us more.
+// -> 83 / 74, with 648 and 1024 up to 10 us more.  Ls > 4: with one slice group
+// the FP32 and BF16 hops run the generic kernel (the specialised chained stage
+// spills), which reads alpha and cannot form it.
 bool cg_few(const dwf_op* op, int nrhs) { return hop_partials(op, nrhs) <= CG_FEW && op->Ls > 4; }
 
 void apply_full(const dwf_op* op, int kind, int dagger, void* out_e, void* out_o, const void* in_e,

@@ -204,15 +204,6 @@ template <class S> constexpr unsigned cbytes() { return sizeof(S) == 8 ? 16u : s
 // group; direction d has NG = ceil(9 / LP) groups, ng = 8 NG per output parity.
 // Neighbour table: element d of 8 of a site at ((site / 16) * 8 + d) * 16 + site % 16.
 // ---------------------------------------------------------------------
-// Compile-time layout switches (measured on MI355X, see the hop kernel):
-// DWF_FIELD_PAIRS groups FP32/BF16 components in pairs, DWF_LINK_PACK packs
-// link elements in 16-byte groups.
-#ifndef DWF_FIELD_PAIRS
-#define DWF_FIELD_PAIRS 1
-#endif
-#ifndef DWF_LINK_PACK
-#define DWF_LINK_PACK 1
-#endif
 // group g of a site with ng groups
 __host__ __device__ __forceinline__ long gidx(long g, long site, long ng) {
     return ((site >> 4) * ng + g) * 16 + (site & 15);
@@ -224,10 +215,10 @@ __host__ __device__ __forceinline__ long fidx(long row, long site, long rows, in
 }
 // components per group: FP64 1, FP32 2, BF16 4 (16 bytes per site and group)
 template <class S> constexpr int fpack() {
-    return (sizeof(S) == 8 || !DWF_FIELD_PAIRS) ? 1 : (sizeof(S) == 4 ? 2 : 4);
+    return sizeof(S) == 8 ? 1 : (sizeof(S) == 4 ? 2 : 4);
 }
-inline int fpack_of(int kind) { return (kind == 0 || !DWF_FIELD_PAIRS) ? 1 : (kind == 1 ? 2 : 4); }
-__host__ __device__ constexpr int link_lp(int cb) { return DWF_LINK_PACK ? 16 / cb : 1; }
+inline int fpack_of(int kind) { return kind == 0 ? 1 : (kind == 1 ? 2 : 4); }
+__host__ __device__ constexpr int link_lp(int cb) { return 16 / cb; }
 __host__ __device__ constexpr int link_ng(int cb) { return (9 + link_lp(cb) - 1) / link_lp(cb); }
 __host__ __device__ __forceinline__ long lidx(int d, int e, long site, int cb) {
     return gidx(d * link_ng(cb) + e / link_lp(cb), site, 8 * link_ng(cb)) * link_lp(cb) + e % link_lp(cb);
@@ -249,7 +240,7 @@ __device__ __forceinline__ void load4(const void* base, long t,
             v[2 * k] = bf16_to_f32(u[k] & 0xffffu);
             v[2 * k + 1] = bf16_to_f32(u[k] >> 16);
         }
-    } else if constexpr (P == 2 && sizeof(S) == 4) {   // FP32 pairs
+    } else if constexpr (P == 2) {   // FP32 pairs
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const float4 w = reinterpret_cast<const float4*>(base)[((t >> 4) * 2 + j) * 16 + (t & 15)];
@@ -275,7 +266,7 @@ __device__ __forceinline__ void store4(void* base, long t,
         w.z = pack_bf16(v[4], v[5]);
         w.w = pack_bf16(v[6], v[7]);
         reinterpret_cast<uint4*>(base)[t] = w;
-    } else if constexpr (P == 2 && sizeof(S) == 4) {
+    } else if constexpr (P == 2) {
 #pragma unroll
         for (int j = 0; j < 2; ++j)
             reinterpret_cast<float4*>(base)[((t >> 4) * 2 + j) * 16 + (t & 15)] =
@@ -291,7 +282,7 @@ __device__ __forceinline__ void store4(void* base, long t,
 template <class S>
 __device__ __forceinline__ void bload_group(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff,
                                             typename Traits<S>::R (&v)[8]) {
-    if constexpr (fpack<S>() == 1) {
+    if constexpr (sizeof(S) == 8) {
         bload<S>(r, voff, soff, v[0], v[1]);
     } else if constexpr (sizeof(S) == 4) {
         u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0);
@@ -299,12 +290,6 @@ __device__ __forceinline__ void bload_group(__amdgpu_buffer_rsrc_t r, unsigned v
         v[1] = __uint_as_float(w.y);
         v[2] = __uint_as_float(w.z);
         v[3] = __uint_as_float(w.w);
-    } else if constexpr (fpack<S>() == 2) {
-        u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
-        v[0] = bf16_to_f32(w.x & 0xffffu);
-        v[1] = bf16_to_f32(w.x >> 16);
-        v[2] = bf16_to_f32(w.y & 0xffffu);
-        v[3] = bf16_to_f32(w.y >> 16);
     } else {
         u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0);
         const unsigned u[4] = {w.x, w.y, w.z, w.w};

@@ -380,8 +380,8 @@ int dwf_gauge_plaquette(const int dims[4], const void* U, double* plaq, void* st
 int dwf_bench_hop(const dwf_op* op, int prec, int nrep, double* ms_per_launch,
                   double* bytes_per_launch, void* stream);
 
-/* Times `nrep` applications of the learned preconditioner (its three layer
- * kernels on internal FP32 fields of `op`, seeded non-zero input) with HIP
+/* Times `nrep` applications of the learned preconditioner (its kernels on
+ * internal FP32 fields of `op`, seeded non-zero input) with HIP
  * events on `stream`; writes the mean time of one application in ms. */
 int dwf_ptc_bench_apply(dwf_ptc* m, const dwf_op* op, int nrep, double* ms_per_apply, void* stream);
 

@@ -69,8 +69,10 @@ static void halve_brick(const int dims[4], int b[3]) {
 //   12x24^3      12x24x12 208 / 92 / 62 -> 12x24x3 196 / 83 / 62
 //   16x32^3      16x16x16 617 / 265 / 184 -> 16x8x8 589 / 265 / 178
 //   20^3x40      20x20x10 394 / 172 / 114 (20x10x5 406 / 173 / 117)
-// Up to 16^3 the halved bricks of 1024 sites are such bricks already
-// (16^3x32: 16x8x8 158 / 65 / 48; 16x16x16 167 / 73 / 48).
+// Up to 16^3 the halved bricks of 1024 sites stay.  On 16^3 they are such bricks
+// (16^3x32: 16x8x8 158 / 65 / 48; 16x16x16 167 / 73 / 48); elsewhere their planes
+// may be broken tiles (12^3: 12x12x6, 4.5 tiles) or x cut (32x8x16: 16x8x8), and
+// no other brick was measured there.
 static void choose_brick(const int dims[4], int b[3]) {
     halve_brick(dims, b);
     if ((long)dims[0] * dims[1] * dims[2] <= 4096 || std::getenv("DWF_BRICK_SITES")) return;

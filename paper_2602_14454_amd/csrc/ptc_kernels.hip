@@ -305,7 +305,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
 // sites; one thread per (site, slice), one slice per wave.  Bound by memory (every
 // g_d is read once, 8 fields; r and the links come from cache) and by half as much
 // arithmetic.  The slices of 64 sites follow each other on one XCD: 226 us on
-// 16^3x32, Ls = 16 (4.4 TB/s); 288 us with the sites of four slices in sequence
+// 16^3x32, Ls = 16 (1.05 GB at 4.6 TB/s); 288 us with the sites of four slices in sequence
 // over all XCDs and with the two terms through s + 1 and s - 1 and back as matrices
 // of their own.  Two slices per thread, with the links read once, were no faster.
 __global__ __launch_bounds__(256) void ptc_out_kernel(const float2* __restrict__ r, const float2* __restrict__ g,

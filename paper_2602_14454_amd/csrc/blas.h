@@ -24,9 +24,11 @@ void unpack_eo5(int kind, void* dst, const void* src_e, const void* src_o, const
               hipStream_t st);
 void pack_half(int kind, void* dst, const void* src, const int* lex, long Vh, long Vhp, int Ls, hipStream_t st);
 void unpack_half(int kind, void* dst, const void* src, const int* lex, long Vh, long Vhp, int Ls, hipStream_t st);
-// canonical complex128 links (device) to the FP64, FP32 and BF16 link tables of both parities
+// canonical complex128 links (device) to the FP64, FP32 (unless null) and BF16 link tables of both parities
 void pack_links(void* l64, void* l32, void* l16, const void* U, const int* lex, const int dims[4], int antiperiodic,
                 long Vh, long Vhp, hipStream_t st);
+// the FP32 tables of both parities from the FP64 ones, padding included
+void links_f32_of_f64(void* l32, const void* l64, long Vhp, hipStream_t st);
 void pack_chiral_pair_f64(void* dst, const void* b4, const int* lex, long Vh, hipStream_t st);
 void project_4d(void* x4, const void* x5, long V, int Ls, hipStream_t st);
 void embed_4d(void* e5, const void* y, long V, int Ls, hipStream_t st);

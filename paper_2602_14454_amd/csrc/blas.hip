@@ -162,6 +162,7 @@ __global__ __launch_bounds__(256) void unpack_kernel(double2* __restrict__ dst, 
 // a block share the 576 bytes of a site.  Bound by the 272 bytes written per
 // link and direction.  Packing the tables on the host and copying them over
 // took 133 ms on 16^4 (this kernel: 44 us).
+template <bool F32>
 __global__ __launch_bounds__(256) void links_kernel(double2* __restrict__ l64, float2* __restrict__ l32,
                                                     uint32_t* __restrict__ l16, const double2* __restrict__ U,
                                                     const int* __restrict__ lex, int Lx, int Ly, int Lz, int Lt,
@@ -191,12 +192,24 @@ __global__ __launch_bounds__(256) void links_kernel(double2* __restrict__ l64, f
 #pragma unroll
         for (int e = 0; e < link_ng(16) * link_lp(16); ++e) l64[p * r64 + lidx(d, e, i, 16)] = u[e];
 #pragma unroll
-        for (int e = 0; e < link_ng(8) * link_lp(8); ++e)
+        for (int e = 0; F32 && e < link_ng(8) * link_lp(8); ++e)
             l32[p * r32 + lidx(d, e, i, 8)] = make_float2((float)u[e].x, (float)u[e].y);
 #pragma unroll
         for (int e = 0; e < link_ng(4) * link_lp(4); ++e)
             l16[p * r16 + lidx(d, e, i, 4)] = pack_bf16((float)u[e].x, (float)u[e].y);
     }
+}
+
+// FP32 tables from the FP64 ones, both parities: 16-byte group t of tile t / 640
+// (40 groups of 16 sites), two elements of a direction; the tenth is zero.
+__global__ __launch_bounds__(256) void links_f32_kernel(float4* __restrict__ l32, const double2* __restrict__ l64, long n) {
+    const long t = (long)blockIdx.x * 256 + threadIdx.x;
+    if (t >= n) return;
+    const long tile = t / 640;
+    const int g = (int)(t - tile * 640) >> 4, d = g / 5, k = g - d * 5;
+    const double2* s = l64 + (tile * 72 + d * 9 + 2 * k) * 16 + (t & 15);
+    const double2 a = s[0], b = k < 4 ? s[16] : make_double2(0.0, 0.0);
+    l32[t] = make_float4((float)a.x, (float)a.y, (float)b.x, (float)b.y);
 }
 
 // 4D canonical -> two-slice half field of one parity: slice 0 = P+ b4, slice 1 = P- b4
@@ -781,8 +794,21 @@ void unpack_half(int kind, void* dst, const void* src, const int* lex, long Vh, 
 
 void pack_links(void* l64, void* l32, void* l16, const void* U, const int* lex, const int dims[4], int antiperiodic,
                 long Vh, long Vhp, hipStream_t st) {
-    hipLaunchKernelGGL(links_kernel, dim3((unsigned)((Vh + 63) / 64), 2), dim3(256), 0, st, (double2*)l64, (float2*)l32,
-                       (uint32_t*)l16, (const double2*)U, lex, dims[0], dims[1], dims[2], dims[3], antiperiodic, Vh, Vhp);
+    const dim3 grid((unsigned)((Vh + 63) / 64), 2);
+    if (l32)
+        hipLaunchKernelGGL(links_kernel<true>, grid, dim3(256), 0, st, (double2*)l64, (float2*)l32, (uint32_t*)l16,
+                           (const double2*)U, lex, dims[0], dims[1], dims[2], dims[3], antiperiodic, Vh, Vhp);
+    else
+        hipLaunchKernelGGL(links_kernel<false>, grid, dim3(256), 0, st, (double2*)l64, (float2*)nullptr, (uint32_t*)l16,
+                           (const double2*)U, lex, dims[0], dims[1], dims[2], dims[3], antiperiodic, Vh, Vhp);
+    DWF_HIP(hipGetLastError());
+}
+
+void links_f32_of_f64(void* l32, const void* l64, long Vhp, hipStream_t st) {
+    static_assert(link_ng(8) * 8 == 40 && link_ng(16) * 8 == 72, "groups of a site");
+    const long n = 2 * 40 * Vhp;
+    hipLaunchKernelGGL(links_f32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, (float4*)l32,
+                       (const double2*)l64, n);
     DWF_HIP(hipGetLastError());
 }
 

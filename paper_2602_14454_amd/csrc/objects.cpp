@@ -232,7 +232,8 @@ void build_geometry(dwf_lattice* L) {
 // antiperiodic t phase folded into the links that cross the boundary
 // (pack_links).  Work in flight on any stream may still read the old tables:
 // the call waits for it before it overwrites them, and for the new tables
-// before it returns.
+// before it returns.  Links in host memory are staged in the FP32 table (576 bytes
+// a site, the table 640 or more), which is then made from the FP64 one.
 void upload_gauge(dwf_lattice* L, const void* U, bool on_device, hipStream_t st) {
     const size_t bytes = (size_t)L->V * 4 * 9 * 16;
     for (int kind : {ST_F64, ST_F32, ST_BF16}) {
@@ -240,14 +241,17 @@ void upload_gauge(dwf_lattice* L, const void* U, bool on_device, hipStream_t st)
         const size_t need = 2 * (size_t)link_elems_parity(L->Vhp, cb) * cb;
         if (L->links[kind].bytes != need) L->links[kind].alloc(need);
     }
-    DevBuf staged;
-    if (!on_device) {
-        staged.alloc(bytes);
-        DWF_HIP(hipMemcpy(staged.p, U, bytes, hipMemcpyHostToDevice));
-    }
+    void *l64 = L->links[ST_F64].p, *l32 = L->links[ST_F32].p, *l16 = L->links[ST_BF16].p;
     DWF_HIP(hipDeviceSynchronize());
-    pack_links(L->links[ST_F64].p, L->links[ST_F32].p, L->links[ST_BF16].p, on_device ? U : staged.p,
-               L->lex_of_site_dev.as<int>(), L->dims, L->antiperiodic_t, L->Vh, L->Vhp, st);
+    L->has_gauge = false;   // until the tables are whole again
+    if (!on_device) {
+        DWF_REQUIRE(bytes <= L->links[ST_F32].bytes, DWF_EDIMS, "links do not fit their table");
+        DWF_HIP(hipMemcpy(l32, U, bytes, hipMemcpyHostToDevice));
+        U = l32;
+    }
+    pack_links(l64, on_device ? l32 : nullptr, l16, U, L->lex_of_site_dev.as<int>(), L->dims, L->antiperiodic_t, L->Vh,
+               L->Vhp, st);
+    if (!on_device) links_f32_of_f64(l32, l64, L->Vhp, st);
     DWF_HIP(hipStreamSynchronize(st));
     L->has_gauge = true;
 }
